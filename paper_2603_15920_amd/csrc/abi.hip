@@ -222,6 +222,15 @@ static void upload_mesh(difvm_mesh* m) {
   d.face_perm = up_vec(m, L.face_perm);
   d.bface_perm = up_vec(m, L.bface_perm);
   d.face_flip = up_vec(m, L.face_flip);
+  auto inverse = [&](int n, const int32_t* perm) {
+    int32_t* inv = dalloc<int32_t>(ctx_of(m), n);
+    m->allocs.push_back(inv);
+    invert_permutation(m, n, perm, inv);
+    return inv;
+  };
+  d.cell_inv = inverse(d.nc, d.cell_perm);
+  d.face_inv = inverse(nfi, d.face_perm);
+  d.bface_inv = inverse(nfb, d.bface_perm);
   std::vector<double4> rO(nfi), rN(nfi);
   for (int f = 0; f < nfi; ++f) {
     const double* xf = &L.Cf[3 * f];

@@ -124,7 +124,8 @@ struct DMesh {
   int nseg, ntile;
   int32_t *cell_seg, *tile_lo, *tile_hi, *tile_seg, *seg_tile_first, *seg_tile_n;
   // permutations for user <-> internal conversions
-  int32_t *cell_perm, *face_perm, *bface_perm;
+  int32_t *cell_perm, *face_perm, *bface_perm;  // internal row -> user row
+  int32_t *cell_inv, *face_inv, *bface_inv;     // user row -> internal row
   uint8_t* face_flip;
   // internal faces: x_f - x_O and x_f - x_N (w unused), for the higher-order convection schemes
   double4 *face_rO, *face_rN;

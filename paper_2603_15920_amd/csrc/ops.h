@@ -6,6 +6,8 @@
 namespace difvm {
 
 void permute(const difvm_mesh* m, int dtype, int ncomp, int kind, int dir, const void* src, void* dst);
+// inv[perm[i]] = i for a permutation of n rows (device arrays)
+void invert_permutation(const difvm_mesh* m, int n, const int32_t* perm, int32_t* inv);
 void op_interp(const difvm_mesh* m, int dtype, int ncomp, int bc, const void* phi, const void* phib, void* out);
 void op_grad(const difvm_mesh* m, int dtype, int ncomp, int bc, const void* phi, const void* phib, void* out);
 void op_div(const difvm_mesh* m, int dtype, int scheme, int ncomp, int bc, const void* flux, const void* psi,
