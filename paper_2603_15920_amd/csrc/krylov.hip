@@ -17,21 +17,24 @@
 
 namespace difvm {
 
-// BiCGStab state of one segment (up to three systems sharing its matrix)
+// BiCGStab state of one segment (up to three systems sharing its matrix) during one iteration
 struct BiState {
   double tol;
-  double bn[3], rho[3], rho1[3], alpha[3], omega[3], beta[3], res[3];
+  double bn[3], rho[3], alpha[3], omega[3], res[3], sres[3];  // rho = rhat.r entering the iteration
   int maxit, any;
-  int iters[3], active[3], phase[3], status[3], zero_b[3];
+  int iters[3], active[3], so[3], status[3];
 };
+// outcome of the test on s (BiState::so)
+enum { BI_SO_GO = 0, BI_SO_DONE = 1, BI_SO_BREAKDOWN = 2 };
 
 struct KrylovWork {
   int nc = 0, ntile = 0;
   double *r = nullptr, *p = nullptr, *q = nullptr, *rh = nullptr, *v = nullptr, *s = nullptr, *z = nullptr,
          *t = nullptr;
+  double* colscaled = nullptr;   // [n_slots] off-diagonals of A D^-1 (BiCGStab)
   double* partials = nullptr;
   struct PcgCtl* pcg = nullptr;  // [nseg]
-  BiState* bi = nullptr;         // [nseg]
+  BiState* bi = nullptr;         // [2][nseg], by the parity of the iteration
   void* host_state[2] = {nullptr, nullptr};  // pinned mirrors of the solver states (two polls in flight)
   hipEvent_t poll_ev[2] = {nullptr, nullptr};
   const Ctx* ctx = nullptr;  // allocator of the buffers above
@@ -54,10 +57,12 @@ static KrylovWork* make_work(difvm_mesh* m) {
     w->r = dalloc<double>(c, n3); w->p = dalloc<double>(c, n3); w->q = dalloc<double>(c, n3);
     w->rh = dalloc<double>(c, n3); w->v = dalloc<double>(c, n3); w->s = dalloc<double>(c, n3);
     w->z = dalloc<double>(c, n3); w->t = dalloc<double>(c, n3);
-    w->partials = dalloc<double>(c, (size_t)9 * w->ntile);  // up to 9 values per tile (PCG uses 6, BiCGStab 9)
-    int nseg = m->d.nseg;
+    w->colscaled = dalloc<double>(c, m->d.nslot);
+    const int nseg = m->d.nseg;
+    // values per tile: PCG uses 6, BiCGStab 6 + 3 + 9 and as many totals per segment
+    w->partials = dalloc<double>(c, (size_t)18 * (w->ntile + nseg));
     w->pcg = static_cast<PcgCtl*>(dmalloc(c, sizeof(BiState) * nseg));  // PcgCtl is smaller (asserted below)
-    w->bi = dalloc<BiState>(c, nseg);
+    w->bi = dalloc<BiState>(c, 2 * (size_t)nseg);
     for (int q = 0; q < 2; ++q) {
       DIFVM_HIP(hipHostMalloc((void**)&w->host_state[q], sizeof(BiState) * nseg, hipHostMallocDefault));
       DIFVM_HIP(hipEventCreateWithFlags(&w->poll_ev[q], hipEventDisableTiming));
@@ -74,7 +79,7 @@ void krylov_work_free(KrylovWork* w) {
   if (!w) return;
   if (w->ctx) {
     const Ctx& c = *w->ctx;
-    for (double* a : {w->r, w->p, w->q, w->rh, w->v, w->s, w->z, w->t, w->partials}) dfree(c, a);
+    for (double* a : {w->r, w->p, w->q, w->rh, w->v, w->s, w->z, w->t, w->colscaled, w->partials}) dfree(c, a);
     dfree(c, w->pcg);
     dfree(c, w->bi);
   }
@@ -550,294 +555,437 @@ SolveResult pcg(difvm_mesh* m, SellMatrix A, const double* b, double* x, double 
 }
 
 // ---------------------------------------------------------------------------------------------
-// BiCGStab kernels (NC systems sharing one matrix per segment, interleaved vectors).  Each reduction
-// kernel writes per-tile partials; a finalize kernel (one block per segment) sums them in a fixed
-// order and advances the segment's scalar recurrences in device memory.
+// BiCGStab kernels (NC systems sharing one matrix per segment, interleaved vectors): five launches per
+// iteration and no kernel for the scalars.  As in PCG, each reduction's per-tile partials are summed
+// again (per segment, fixed order) by every block of the next kernel that needs them:
+//   init:   r = b - A x, rhat = r; off-diagonals of A D^-1          partials X = (b.b, r.r)
+//   dir_k:  (from X) stopping test of iterate k-1, beta; p = r + beta (p - omega v)
+//   v_k:    v = A D^-1 p                                            partials V = rhat.v
+//   s_k:    (from V) alpha; s = r - alpha v
+//   t_k:    t = A D^-1 s                                            partials T = (t.s, t.t, s.s)
+//   x_k:    (from T) test on s, omega; x += D^-1 (alpha p + omega s); r = s - omega t
+//                                                                   partials X = (r.r, rhat.r)
+// The state of iteration k lives in copy k & 1: dir_k reads copy k-1 and its segment's first tile writes
+// copy k whole; that tile's block of s_k adds alpha and of x_k adds omega and the outcome of the test on
+// s, fields that no block of the same launch reads.  Columns are scaled by 1/d once per solve, so the
+// products gather p and s alone (not d beside them, with a division for each neighbour).
+// Blocks have one thread per cell of a tile: the meshes between 50k and 300k cells give the chip 50 to
+// 300 blocks, which with four cells per thread left it to four waves per block with one row after another.
+// At 167,400 cells (3 components) an iteration's kernels took 73 us as eight launches of 256-thread
+// blocks, 40 us now; at 1,053,696 cells 160, 147 now (dir 19.6, v 28.2, s 12.2, t 33.3, x 39.9, totals 14).
 // ---------------------------------------------------------------------------------------------
-enum BiStage { BI_INIT = 0, BI_ALPHA = 1, BI_SO = 2, BI_X = 3 };
 
-// NV partial arrays: NC for BI_ALPHA, 3 NC for BI_SO (t.s, t.t, s.s), 2 NC otherwise
-template <int NC, int NV>
-__global__ __launch_bounds__(BLOCK) void k_bi_fin(int stage, const double* __restrict__ part, Tiles T, BiState* sts) {
-  BiState* st = sts + blockIdx.x;
-  // the segment's state and tile range loaded together, before the partials (thread 0 works on the
-  // copy and stores it back whole; no other block touches this segment's state).  No early return
-  // for a stopped segment, which would hold the other loads back behind the flag's: with no active
-  // component the update below changes nothing.
-  BiState S = *st;
-  const int f = T.first[blockIdx.x], n = T.count[blockIdx.x];
+// (B f)_i for NC interleaved components, B the off-diagonals in val plus DIAG f_i; padding and boundary
+// slots carry val = 0 and col = i.  The row's slots in layout order, the first four with every load issued
+// before any is used.
+template <int NC>
+__device__ __forceinline__ void scaled_row(const SellView& A, const double* __restrict__ val, int i,
+                                           const double* __restrict__ f, double (&acc)[NC]) {
+  SlotRange R = slots_of(A, i);
+  const bool off16 = A.off16 != nullptr;  // the same for every thread: a uniform branch
+  walk_row<4>(R.width, [&](auto Wc, int k0) {
+    constexpr int N = decltype(Wc)::value;
+    double a[N], fj[N][NC];
+    int j[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      int at = R.base + (k0 + k) * SLICE;
+      a[k] = val[at];
+      j[k] = off16 ? i + A.off16[at] : A.col[at];
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) fj[k][c] = f[(size_t)j[k] * NC + c];
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) acc[c] += a[k] * fj[k][c];
+  });
+}
+
+// The NV totals of the segment for a kernel that needs them: summed here by every block, or (FIN) read
+// from the array that k_bi_totals filled.  Same sums, same bits.
+template <int NV, bool FIN>
+__device__ __forceinline__ void bi_totals(const double* __restrict__ part, const Tiles& T, int s, double (&tot)[NV]) {
+  if constexpr (FIN) {
+#pragma unroll
+    for (int k = 0; k < NV; ++k) tot[k] = part[s * NV + k];
+  } else {
+    tile_seg_totals<NV>(part, T.ntile, seg_first(T, s), seg_count(T, s), tot);
+  }
+}
+// Above this many tiles the totals get a kernel of their own, three per iteration of 4.7 us: at 1,029 tiles
+// every block summing 6 partials per tile by itself made the direction pass 32.2 us against 19.6 + 4.7,
+// while at 164 tiles it adds about 1 us to a pass that a launch more would cost 5.
+constexpr int BI_FIN_TILES = 384;
+
+template <int NV>
+__global__ __launch_bounds__(TILE) void k_bi_totals(const double* __restrict__ part, Tiles T, double* __restrict__ out) {
+  const int s = blockIdx.x;
   double tot[NV];
-  seg_thread_sum<NV>(part, T.ntile, f, n, tot);
-  __shared__ double lds[NV][BLOCK / 64];
-  block_sum<NV>(tot, lds);
-  if (threadIdx.x != 0) return;
-  int any = 0;
+  tile_seg_totals<NV>(part, T.ntile, seg_first(T, s), seg_count(T, s), tot);
+  if (threadIdx.x == 0)
+#pragma unroll
+    for (int k = 0; k < NV; ++k) out[s * NV + k] = tot[k];
+}
+
+// r = b - A x, rhat = r, partials b.b and r.r; val of A D^-1 (p and v start at zero: the first direction
+// pass writes p = r without reading them)
+template <int NC>
+__global__ __launch_bounds__(TILE) void k_bi_init(SellView A, Tiles T, const double* __restrict__ b,
+                                                  const double* __restrict__ x, double* __restrict__ r,
+                                                  double* __restrict__ rh, double* __restrict__ colscaled,
+                                                  double* __restrict__ part) {
+  const TileIdx ti = tile_idx(T);
+  const int i = ti.lo + (int)threadIdx.x;
+  double acc[2 * NC], ri[NC];
+#pragma unroll
+  for (int k = 0; k < 2 * NC; ++k) acc[k] = 0.0;
+  if (i < ti.hi) {
+    double ax[NC], bi[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) bi[c] = b[(size_t)i * NC + c];
+    SlotRange R = slots_of(A, i);
+    const double di = A.diag[i];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) ax[c] = di * x[(size_t)i * NC + c];
+    walk_row<4>(R.width, [&](auto Wc, int k0) {
+      constexpr int N = decltype(Wc)::value;
+      double a[N], dj[N], xj[N][NC];
+      int j[N];
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        int at = R.base + (k0 + k) * SLICE;
+        a[k] = A.val[at];
+        j[k] = A.off16 ? i + A.off16[at] : A.col[at];
+      }
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        dj[k] = A.diag[j[k]];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) xj[k][c] = x[(size_t)j[k] * NC + c];
+      }
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        colscaled[R.base + (k0 + k) * SLICE] = a[k] / dj[k];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) ax[c] += a[k] * xj[k][c];
+      }
+    });
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      ri[c] = bi[c] - ax[c];
+      acc[c] = bi[c] * bi[c];
+      acc[NC + c] = ri[c] * ri[c];
+    }
+  }
+  if constexpr (NC == 1) {
+    if (i < ti.hi) r[i] = rh[i] = ri[0];
+  } else {
+    __shared__ double lds[NC * TILE];
+    store_rows<NC>(r, ti.lo, ti.hi, ri, lds);
+    store_rows<NC>(rh, ti.lo, ti.hi, ri, lds);
+  }
+  put_tile_partial<2 * NC>(acc, part, T.ntile, ti.t);
+}
+
+// component c's value of an array held in registers (no run-time index, which would move it to memory)
+template <int NC, class T>
+__device__ __forceinline__ T pick(const T (&a)[NC], int c) {
+  if constexpr (NC == 1) {
+    return a[0];
+  } else {
+    static_assert(NC == 3, "one or three components");
+    const T a0 = a[0], a1 = a[1], a2 = a[2];
+    return c == 0 ? a0 : c == 1 ? a1 : a2;
+  }
+}
+
+// copies the first NC systems' state, field by field (a whole-struct copy of unused ones goes through memory)
+template <int NC>
+__device__ __forceinline__ void copy_systems(BiState& d, const BiState& s) {
+  d.tol = s.tol;
+  d.maxit = s.maxit;
+  d.any = s.any;
+#pragma unroll
   for (int c = 0; c < NC; ++c) {
-    if (stage == BI_INIT) {
-      double bn = sqrt(tot[c]), rn = sqrt(tot[NC + c]);
+    d.bn[c] = s.bn[c];
+    d.rho[c] = s.rho[c];
+    d.alpha[c] = s.alpha[c];
+    d.omega[c] = s.omega[c];
+    d.res[c] = s.res[c];
+    d.sres[c] = s.sres[c];
+    d.iters[c] = s.iters[c];
+    d.active[c] = s.active[c];
+    d.so[c] = s.so[c];
+    d.status[c] = s.status[c];
+  }
+}
+
+// iteration it >= 1: stopping test of iterate it - 1 (it = 1: of the initial guess), then the direction.
+// One thread per value of the tile's rows (consecutive lanes, consecutive doubles), NC rounds.
+template <int NC, bool FIN>
+__global__ __launch_bounds__(TILE, FIN ? 8 : 4) void k_bi_dir(Tiles T, int it, const double* __restrict__ r, double* __restrict__ p,
+                                                 const double* __restrict__ v, double* __restrict__ x,
+                                                 const double* __restrict__ part, BiState* sts, int nseg) {
+  const TileIdx ti = tile_idx(T);
+  const BiState* prev = sts + (size_t)((it - 1) & 1) * nseg + ti.s;
+  BiState S;
+  copy_systems<NC>(S, *prev);
+  const bool lead = ti.t == seg_first(T, ti.s) && threadIdx.x == 0;
+  BiState* cur = sts + (size_t)(it & 1) * nseg + ti.s;
+  const int e0 = NC * ti.lo, e1 = NC * ti.hi;
+  if (it > 1 && !S.any) {  // stopped before: the state moves on with the parity
+    if (lead) copy_systems<NC>(*cur, S);
+    return;
+  }
+  double rv[NC], pv[NC], vv[NC];  // in flight with the partials
+#pragma unroll
+  for (int q = 0; q < NC; ++q) {
+    const int e = min(e0 + q * TILE + (int)threadIdx.x, e1 - 1);
+    rv[q] = r[e];
+    pv[q] = vv[q] = 0.0;
+    if (it > 1) {
+      pv[q] = p[e];
+      vv[q] = v[e];
+    }
+  }
+  double tot[2 * NC];
+  bi_totals<2 * NC, FIN>(part, T, ti.s, tot);
+  double beta[NC], omega[NC];
+  bool act[NC], zero[NC];
+  S.any = 0;
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    beta[c] = omega[c] = 0.0;
+    zero[c] = false;
+    if (it == 1) {
+      const double bn = sqrt(tot[c]), rn = sqrt(tot[NC + c]);
       S.bn[c] = bn;
-      S.iters[c] = 0;
-      S.status[c] = 0;
-      S.phase[c] = 0;
-      S.zero_b[c] = bn == 0.0;
       S.res[c] = bn == 0.0 ? 0.0 : rn / bn;
+      S.rho[c] = tot[NC + c];  // rhat = r, so rhat.r = r.r
       S.active[c] = (bn == 0.0 || rn <= S.tol * bn) ? 0 : 1;
-      S.rho[c] = S.alpha[c] = S.omega[c] = 1.0;
-      S.rho1[c] = tot[NC + c];  // rhat = r, so rhat.r = r.r
+      zero[c] = bn == 0.0;  // b = 0 gives x = 0
       if (S.active[c] && S.maxit <= 0) {
         S.active[c] = 0;
         S.status[c] = DIFVM_WARN_NOT_CONVERGED;
-      } else if (S.active[c] && S.rho1[c] == 0.0) {
+      } else if (S.active[c] && S.rho[c] == 0.0) {
         S.active[c] = 0;
         S.status[c] = DIFVM_WARN_BREAKDOWN;
       }
-      if (S.active[c]) S.beta[c] = (S.rho1[c] / S.rho[c]) * (S.alpha[c] / S.omega[c]);
-    } else if (!S.active[c]) {
-      continue;
-    } else if (stage == BI_ALPHA) {
-      S.alpha[c] = S.rho1[c] / tot[c];
-    } else if (stage == BI_SO) {
-      // the test on |s| first (the iteration ends with x += alpha y if it passes), then omega
-      double sn = sqrt(tot[(2 * NC + c) % NV]);  // NV = 3 NC in this stage
-      if (sn <= S.tol * S.bn[c]) {
-        S.phase[c] = 1;
-        S.res[c] = sn / S.bn[c];
-      } else if (tot[NC + c] == 0.0) {
+    } else if (S.active[c]) {
+      if (S.so[c] == BI_SO_BREAKDOWN) {
         S.active[c] = 0;
         S.status[c] = DIFVM_WARN_BREAKDOWN;
       } else {
-        S.omega[c] = tot[c] / tot[NC + c];
-      }
-    } else {  // BI_X
-      int it = S.iters[c] + 1;
-      S.iters[c] = it;
-      if (S.phase[c]) {
-        S.active[c] = 0;
-      } else {
-        S.rho[c] = S.rho1[c];
-        double rn = sqrt(tot[c]);
-        S.res[c] = rn / S.bn[c];
-        if (rn <= S.tol * S.bn[c]) {
+        S.iters[c] = it - 1;
+        if (S.so[c] == BI_SO_DONE) {
           S.active[c] = 0;
-        } else if (it >= S.maxit) {
-          S.active[c] = 0;
-          S.status[c] = DIFVM_WARN_NOT_CONVERGED;
+          S.res[c] = S.sres[c];
         } else {
-          S.rho1[c] = tot[NC + c];
-          if (S.rho1[c] == 0.0) {
+          const double rn = sqrt(tot[c]), rho = S.rho[c];
+          S.res[c] = rn / S.bn[c];
+          if (rn <= S.tol * S.bn[c]) {
             S.active[c] = 0;
-            S.status[c] = DIFVM_WARN_BREAKDOWN;
+          } else if (it - 1 >= S.maxit) {
+            S.active[c] = 0;
+            S.status[c] = DIFVM_WARN_NOT_CONVERGED;
           } else {
-            S.beta[c] = (S.rho1[c] / S.rho[c]) * (S.alpha[c] / S.omega[c]);
+            S.rho[c] = tot[NC + c];
+            if (S.rho[c] == 0.0) {
+              S.active[c] = 0;
+              S.status[c] = DIFVM_WARN_BREAKDOWN;
+            } else {
+              omega[c] = S.omega[c];
+              beta[c] = (S.rho[c] / rho) * (S.alpha[c] / omega[c]);
+            }
           }
         }
       }
     }
-    any |= S.active[c];
+    S.so[c] = BI_SO_GO;
+    act[c] = S.active[c] != 0;
+    S.any |= S.active[c];
   }
-  S.any = any;
-  *st = S;
+  if (lead) copy_systems<NC>(*cur, S);
+#pragma unroll
+  for (int q = 0; q < NC; ++q) {
+    const int e = e0 + q * TILE + (int)threadIdx.x;
+    if (e >= e1) continue;
+    const int c = e % NC;
+    if (pick(zero, c)) x[e] = 0.0;
+    if (!pick(act, c)) continue;
+    p[e] = it == 1 ? rv[q] : rv[q] + pick(beta, c) * (pv[q] - pick(omega, c) * vv[q]);
+  }
 }
 
-// r = b - A x, rhat = r, partials b.b and r.r (p and v start at zero: the first direction pass
-// writes p = r without reading them)
+// v = A D^-1 p; partial rhat . v
 template <int NC>
-__global__ __launch_bounds__(BLOCK) void k_bi_init(SellView A, Tiles T, const double* __restrict__ b,
-                                                   const double* __restrict__ x, double* __restrict__ r,
-                                                   double* __restrict__ rh, double* __restrict__ part) {
-  TileIdx ti = tile_idx(T);
-  double acc[2 * NC];
+__global__ __launch_bounds__(TILE) void k_bi_v(SellView A, const double* __restrict__ colscaled, Tiles T, int it,
+                                               const double* __restrict__ p, double* __restrict__ v,
+                                               const double* __restrict__ rh, double* __restrict__ part,
+                                               const BiState* sts, int nseg) {
+  const TileIdx ti = tile_idx(T);
+  const BiState* st = sts + (size_t)(it & 1) * nseg + ti.s;
+  if (!st->any) return;
+  bool act[NC];
 #pragma unroll
-  for (int k = 0; k < 2 * NC; ++k) acc[k] = 0.0;
-  FOR_TILE_CELLS(i) {
-    double ax[NC];
-    sell_row<NC>(A, i, x, ax);
+  for (int c = 0; c < NC; ++c) act[c] = st->active[c] != 0;
+  const int i = ti.lo + (int)threadIdx.x;
+  double ay[NC], acc[NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      size_t at = (size_t)i * NC + c;
-      double bi = b[at], ri = bi - ax[c];
-      r[at] = ri;
-      rh[at] = ri;
-      acc[c] += bi * bi;
-      acc[NC + c] += ri * ri;
+  for (int c = 0; c < NC; ++c) ay[c] = acc[c] = 0.0;
+  if (i < ti.hi) {
+    double rhi[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {  // own values, in flight with the row's loads
+      rhi[c] = rh[(size_t)i * NC + c];
+      ay[c] = p[(size_t)i * NC + c];
     }
+    scaled_row<NC>(A, colscaled, i, p, ay);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) acc[c] = act[c] ? rhi[c] * ay[c] : 0.0;
   }
-  put_partial<2 * NC>(acc, part, T.ntile, ti.t);
+  if constexpr (NC == 1) {
+    if (i < ti.hi) v[i] = ay[0];
+  } else {
+    __shared__ double lds[NC * TILE];
+    store_rows_if<NC>(v, ti.lo, ti.hi, ay, act, lds);
+  }
+  put_tile_partial<NC>(acc, part, T.ntile, ti.t);
 }
 
-template <int NC>
-__global__ __launch_bounds__(BLOCK) void k_bi_zero(Tiles T, double* __restrict__ x, const BiState* sts) {
-  TileIdx ti = tile_idx(T);
-  const BiState* st = sts + ti.s;
-  FOR_TILE_CELLS(i) {
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-      if (st->zero_b[c]) x[(size_t)i * NC + c] = 0.0;
-  }
-}
-
-// (A f)_i for NC interleaved components, f(j, c) giving the operand of cell j; padding and boundary
-// slots carry val = 0 and col = i
-template <int NC, class F>
-__device__ __forceinline__ void sell_row_f(const SellView& A, int i, F&& f, double (&acc)[NC]) {
-  SlotRange R = slots_of(A, i);
-  double di = A.diag[i];
-  const bool off16 = A.off16 != nullptr;  // the same for every thread: a uniform branch
-#pragma unroll
-  for (int c = 0; c < NC; ++c) acc[c] = di * f(i, c);
-#pragma unroll 4
-  for (int k = 0; k < R.width; ++k) {
-    int at = R.base + k * SLICE;
-    double a = A.val[at];
-    int j = off16 ? i + A.off16[at] : A.col[at];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) acc[c] += a * f(j, c);
-  }
-}
-
-// The right-preconditioned vectors y = p / d and z = s / d are formed where they are used, not stored.
-// p = r + beta (p - omega v); the first iteration's p = r (p and v are zero then and not read)
-template <int NC>
-__global__ __launch_bounds__(BLOCK) void k_bi_dir(SellView A, Tiles T, const double* __restrict__ r, double* __restrict__ p,
-                                                  const double* __restrict__ v, const BiState* sts, int first) {
-  TileIdx ti = tile_idx(T);
-  const BiState* st = sts + ti.s;
+// alpha, s = r - alpha v, one thread per value of the tile's rows (as k_bi_dir)
+template <int NC, bool FIN>
+__global__ __launch_bounds__(TILE, FIN ? 8 : 4) void k_bi_s(Tiles T, int it, const double* __restrict__ r,
+                                               const double* __restrict__ v, double* __restrict__ s,
+                                               const double* __restrict__ part, BiState* sts, int nseg) {
+  const TileIdx ti = tile_idx(T);
+  BiState* st = sts + (size_t)(it & 1) * nseg + ti.s;
   if (!st->any) return;
-  // one thread per value of the tile's rows (consecutive lanes, consecutive doubles)
-  const int e1 = NC * ti.hi;
+  const int e0 = NC * ti.lo, e1 = NC * ti.hi;
+  double rv[NC], vv[NC];  // in flight with the partials
 #pragma unroll
-  for (int q = 0; q < NC * CPT; ++q) {
-    int e = NC * ti.lo + q * BLOCK + (int)threadIdx.x;
-    if (e >= e1) break;
-    int c = e % NC;
-    if (!st->active[c]) continue;
-    if (first) p[e] = r[e];
-    else p[e] = r[e] + st->beta[c] * (p[e] - st->omega[c] * v[e]);
+  for (int q = 0; q < NC; ++q) {
+    const int e = min(e0 + q * TILE + (int)threadIdx.x, e1 - 1);
+    rv[q] = r[e];
+    vv[q] = v[e];
   }
-}
-
-// v = A y, y = p / d; partial rhat . v
-template <int NC>
-__global__ __launch_bounds__(BLOCK) void k_bi_v(SellView A, Tiles T, const double* __restrict__ p, double* __restrict__ v,
-                                                const double* __restrict__ rh, double* __restrict__ part, const BiState* sts) {
-  TileIdx ti = tile_idx(T);
-  const BiState* st = sts + ti.s;
-  if (!st->any) return;
-  double acc[NC];
-#pragma unroll
-  for (int c = 0; c < NC; ++c) acc[c] = 0.0;
-  // (staging these stores through LDS measured slower here: the rounds' barriers hold back the
-  // gathers of the waves that could run ahead)
-  FOR_TILE_CELLS(i) {
-    double rhi[NC], ay[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) rhi[c] = rh[(size_t)i * NC + c];  // in flight with the row's loads
-    sell_row_f<NC>(A, i, [&](int j, int c) { return p[(size_t)j * NC + c] / A.diag[j]; }, ay);
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      if (!st->active[c]) continue;
-      size_t at = (size_t)i * NC + c;
-      v[at] = ay[c];
-      acc[c] += rhi[c] * ay[c];
-    }
-  }
-  put_partial<NC>(acc, part, T.ntile, ti.t);
-}
-
-// s = r - alpha v, one thread per value of the tile's rows (as k_bi_dir)
-template <int NC>
-__global__ __launch_bounds__(BLOCK) void k_bi_s(Tiles T, const double* __restrict__ r, const double* __restrict__ v,
-                                                double* __restrict__ s, const BiState* sts) {
-  TileIdx ti = tile_idx(T);
-  const BiState* st = sts + ti.s;
-  if (!st->any) return;
-  const int e1 = NC * ti.hi;
-#pragma unroll
-  for (int q = 0; q < NC * CPT; ++q) {
-    int e = NC * ti.lo + q * BLOCK + (int)threadIdx.x;
-    if (e >= e1) break;
-    int c = e % NC;
-    if (!st->active[c]) continue;
-    s[e] = r[e] - st->alpha[c] * v[e];
-  }
-}
-
-// t = A z with z = s / d (s gathered from the pass above); partials t.s, t.t, s.s
-template <int NC>
-__global__ __launch_bounds__(BLOCK) void k_bi_t(SellView A, Tiles T, const double* __restrict__ s,
-                                                double* __restrict__ t, double* __restrict__ part, const BiState* sts) {
-  TileIdx ti = tile_idx(T);
-  const BiState* st = sts + ti.s;
-  if (!st->any) return;
-  double acc[3 * NC];
-#pragma unroll
-  for (int k = 0; k < 3 * NC; ++k) acc[k] = 0.0;
-  FOR_TILE_CELLS(i) {
-    double az[NC];
-    sell_row_f<NC>(A, i, [&](int j, int c) { return s[(size_t)j * NC + c] / A.diag[j]; }, az);
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      if (!st->active[c]) continue;
-      size_t at = (size_t)i * NC + c;
-      double si = s[at];
-      t[at] = az[c];
-      acc[c] += az[c] * si;
-      acc[NC + c] += az[c] * az[c];
-      acc[2 * NC + c] += si * si;
-    }
-  }
-  put_partial<3 * NC>(acc, part, T.ntile, ti.t);
-}
-
-// x += alpha y (+ omega z); r = s - omega t; partials r.r, rhat.r
-template <int NC>
-__global__ __launch_bounds__(BLOCK) void k_bi_x(SellView A, Tiles T, double* __restrict__ x, double* __restrict__ r,
-                                                const double* __restrict__ rh, const double* __restrict__ p,
-                                                const double* __restrict__ s, const double* __restrict__ t,
-                                                double* __restrict__ part, const BiState* sts) {
-  TileIdx ti = tile_idx(T);
-  const BiState* st = sts + ti.s;
-  if (!st->any) return;
-  double acc[2 * NC];
-#pragma unroll
-  for (int k = 0; k < 2 * NC; ++k) acc[k] = 0.0;
-  bool keep_x[NC], keep_r[NC];
+  double tot[NC], alpha[NC];
+  bool act[NC];
+  bi_totals<NC, FIN>(part, T, ti.s, tot);
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
-    keep_x[c] = st->active[c] != 0;
-    keep_r[c] = keep_x[c] && !st->phase[c];
+    act[c] = st->active[c] != 0;
+    alpha[c] = st->rho[c] / tot[c];
   }
-  __shared__ double lds[NC * BLOCK];
-  FOR_TILE_ROUNDS(base, i) {
-    double xv[NC] = {}, rv[NC] = {};
-    if (i < ti.hi) {
-      double di = A.diag[i];
+  if (ti.t == seg_first(T, ti.s) && threadIdx.x == 0)
 #pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        if (!keep_x[c]) continue;
-        size_t at = (size_t)i * NC + c;
-        double yi = p[at] / di;
-        if (!keep_r[c]) {
-          xv[c] = x[at] + st->alpha[c] * yi;
-        } else {
-          double si = s[at];
-          xv[c] = x[at] + (st->alpha[c] * yi + st->omega[c] * (si / di));
-          double ri = si - st->omega[c] * t[at];
-          rv[c] = ri;
-          acc[c] += ri * ri;
-          acc[NC + c] += rh[at] * ri;
-        }
-      }
-    }
-    if constexpr (NC == 1) {
-      if (i < ti.hi && keep_x[0]) x[i] = xv[0];
-      if (i < ti.hi && keep_r[0]) r[i] = rv[0];
-    } else {
-      store_rows_if<NC>(x, base, ti.hi, xv, keep_x, lds);
-      store_rows_if<NC>(r, base, ti.hi, rv, keep_r, lds);
-    }
+    for (int c = 0; c < NC; ++c)
+      if (act[c]) st->alpha[c] = alpha[c];
+#pragma unroll
+  for (int q = 0; q < NC; ++q) {
+    const int e = e0 + q * TILE + (int)threadIdx.x;
+    if (e >= e1) continue;
+    const int c = e % NC;
+    if (pick(act, c)) s[e] = rv[q] - pick(alpha, c) * vv[q];
   }
-  put_partial<2 * NC>(acc, part, T.ntile, ti.t);
+}
+
+// t = A D^-1 s (s gathered from the pass above); partials t.s, t.t, s.s
+template <int NC>
+__global__ __launch_bounds__(TILE) void k_bi_t(SellView A, const double* __restrict__ colscaled, Tiles T, int it,
+                                               const double* __restrict__ s, double* __restrict__ t,
+                                               double* __restrict__ part, const BiState* sts, int nseg) {
+  const TileIdx ti = tile_idx(T);
+  const BiState* st = sts + (size_t)(it & 1) * nseg + ti.s;
+  if (!st->any) return;
+  bool act[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) act[c] = st->active[c] != 0;
+  const int i = ti.lo + (int)threadIdx.x;
+  double az[NC], acc[3 * NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) az[c] = acc[c] = acc[NC + c] = acc[2 * NC + c] = 0.0;
+  if (i < ti.hi) {
+    double si[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) az[c] = si[c] = s[(size_t)i * NC + c];
+    scaled_row<NC>(A, colscaled, i, s, az);
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      if (act[c]) {
+        acc[c] = az[c] * si[c];
+        acc[NC + c] = az[c] * az[c];
+        acc[2 * NC + c] = si[c] * si[c];
+      }
+  }
+  if constexpr (NC == 1) {
+    if (i < ti.hi) t[i] = az[0];
+  } else {
+    __shared__ double lds[NC * TILE];
+    store_rows_if<NC>(t, ti.lo, ti.hi, az, act, lds);
+  }
+  put_tile_partial<3 * NC>(acc, part, T.ntile, ti.t);
+}
+
+// the test on s (the iteration ends with x += alpha D^-1 p if it passes) and omega;
+// x += alpha D^-1 p (+ omega D^-1 s); r = s - omega t; partials r.r, rhat.r
+template <int NC, bool FIN>
+__global__ __launch_bounds__(TILE, FIN ? 8 : 4) void k_bi_x(SellView A, Tiles T, int it, double* __restrict__ x,
+                                               double* __restrict__ r, const double* __restrict__ rh,
+                                               const double* __restrict__ p, const double* __restrict__ s,
+                                               const double* __restrict__ t, const double* __restrict__ part_in,
+                                               double* __restrict__ part, BiState* sts, int nseg) {
+  const TileIdx ti = tile_idx(T);
+  BiState* st = sts + (size_t)(it & 1) * nseg + ti.s;
+  if (!st->any) return;
+  const int i = ti.lo + (int)threadIdx.x, ii = min(i, ti.hi - 1);
+  double pv[NC], sv[NC], tv[NC], xv[NC], hv[NC];  // in flight with the partials
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const size_t at = (size_t)ii * NC + c;
+    xv[c] = x[at];
+    pv[c] = p[at];
+    sv[c] = s[at];
+    tv[c] = t[at];
+    hv[c] = rh[at];
+  }
+  const double di = A.diag[ii];
+  double tot[3 * NC];
+  bi_totals<3 * NC, FIN>(part_in, T, ti.s, tot);
+  const bool lead = ti.t == seg_first(T, ti.s) && threadIdx.x == 0;
+  bool keep_x[NC], keep_r[NC];
+  double acc[2 * NC], rv[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const double alpha = st->alpha[c], sn = sqrt(tot[2 * NC + c]), bn = st->bn[c];
+    const bool small = sn <= st->tol * bn, bad = !small && tot[NC + c] == 0.0;
+    const double omega = tot[c] / tot[NC + c];
+    keep_x[c] = st->active[c] != 0 && !bad;
+    keep_r[c] = keep_x[c] && !small;
+    if (lead && st->active[c]) {
+      st->so[c] = small ? BI_SO_DONE : bad ? BI_SO_BREAKDOWN : BI_SO_GO;
+      st->sres[c] = sn / bn;
+      st->omega[c] = omega;
+    }
+    const double y = pv[c] / di, z = sv[c] / di;
+    xv[c] += keep_r[c] ? alpha * y + omega * z : alpha * y;
+    rv[c] = sv[c] - omega * tv[c];
+    const bool in = keep_r[c] && i < ti.hi;
+    acc[c] = in ? rv[c] * rv[c] : 0.0;
+    acc[NC + c] = in ? hv[c] * rv[c] : 0.0;
+  }
+  if constexpr (NC == 1) {
+    if (i < ti.hi && keep_x[0]) x[i] = xv[0];
+    if (i < ti.hi && keep_r[0]) r[i] = rv[0];
+  } else {
+    __shared__ double lds[NC * TILE];
+    store_rows_if<NC>(x, ti.lo, ti.hi, xv, keep_x, lds);
+    store_rows_if<NC>(r, ti.lo, ti.hi, rv, keep_r, lds);
+  }
+  put_tile_partial<2 * NC>(acc, part, T.ntile, ti.t);
 }
 
 __global__ void k_bi_state_init(BiState* sts, int nseg, double tol, int maxit) {
@@ -875,7 +1023,7 @@ SolveResult bicgstab_result(const difvm_mesh* m, int ncomp, const void* host_sta
   return R;
 }
 
-template <int NC>
+template <int NC, bool FIN>
 static SolveResult bicgstab_nc(difvm_mesh* m, SellMatrix A, const double* b, double* x, double tol, int maxit,
                                const QueueOnly* qo, int* hint) {
   KrylovWork* w = make_work(m);
@@ -884,41 +1032,49 @@ static SolveResult bicgstab_nc(difvm_mesh* m, SellMatrix A, const double* b, dou
   Tiles T = tiles_of(m);
   int G = T.ntile, nseg = m->d.nseg;
   k_bi_state_init<<<(nseg + 63) / 64, 64, 0, s>>>(w->bi, nseg, tol, maxit);
-  double* part = w->partials;
-  k_bi_init<NC><<<G, BLOCK, 0, s>>>(V, T, b, x, w->r, w->rh, part);
-  k_bi_fin<NC, 2 * NC><<<nseg, BLOCK, 0, s>>>(BI_INIT, part, T, w->bi);
-  k_bi_zero<NC><<<G, BLOCK, 0, s>>>(T, x, w->bi);
+  double* partX = w->partials;
+  double* partV = partX + 2 * NC * (size_t)G;
+  double* partT = partV + NC * (size_t)G;
+  double* tots = partX + 18 * (size_t)G;
+  auto dir = [&](int it) {
+    if (FIN) k_bi_totals<2 * NC><<<nseg, TILE, 0, s>>>(partX, T, tots);
+    k_bi_dir<NC, FIN><<<G, TILE, 0, s>>>(T, it, w->r, w->p, w->v, x, FIN ? tots : partX, w->bi, nseg);
+  };
+  k_bi_init<NC><<<G, TILE, 0, s>>>(V, T, b, x, w->r, w->rh, w->colscaled, partX);
+  dir(1);
   DIFVM_HIP(hipGetLastError());
   int done = 0;  // iterations queued
   auto queue_iters = [&](int nb) {
-    for (int it = 0; it < nb; ++it) {
-      k_bi_dir<NC><<<G, BLOCK, 0, s>>>(V, T, w->r, w->p, w->v, w->bi, done + it == 0 ? 1 : 0);
-      k_bi_v<NC><<<G, BLOCK, 0, s>>>(V, T, w->p, w->v, w->rh, part, w->bi);
-      k_bi_fin<NC, NC><<<nseg, BLOCK, 0, s>>>(BI_ALPHA, part, T, w->bi);
-      k_bi_s<NC><<<G, BLOCK, 0, s>>>(T, w->r, w->v, w->s, w->bi);
-      k_bi_t<NC><<<G, BLOCK, 0, s>>>(V, T, w->s, w->t, part, w->bi);
-      k_bi_fin<NC, 3 * NC><<<nseg, BLOCK, 0, s>>>(BI_SO, part, T, w->bi);
-      k_bi_x<NC><<<G, BLOCK, 0, s>>>(V, T, x, w->r, w->rh, w->p, w->s, w->t, part, w->bi);
-      k_bi_fin<NC, 2 * NC><<<nseg, BLOCK, 0, s>>>(BI_X, part, T, w->bi);
+    for (int n = 0; n < nb; ++n) {
+      const int it = ++done;
+      k_bi_v<NC><<<G, TILE, 0, s>>>(V, w->colscaled, T, it, w->p, w->v, w->rh, partV, w->bi, nseg);
+      if (FIN) k_bi_totals<NC><<<nseg, TILE, 0, s>>>(partV, T, tots);
+      k_bi_s<NC, FIN><<<G, TILE, 0, s>>>(T, it, w->r, w->v, w->s, FIN ? tots : partV, w->bi, nseg);
+      k_bi_t<NC><<<G, TILE, 0, s>>>(V, w->colscaled, T, it, w->s, w->t, partT, w->bi, nseg);
+      if (FIN) k_bi_totals<3 * NC><<<nseg, TILE, 0, s>>>(partT, T, tots);
+      k_bi_x<NC, FIN><<<G, TILE, 0, s>>>(V, T, it, x, w->r, w->rh, w->p, w->s, w->t, FIN ? tots : partT, partX, w->bi,
+                                         nseg);
+      dir(it + 1);
     }
-    done += nb;
     DIFVM_HIP(hipGetLastError());
   };
+  // the state after the iterations queued so far
+  auto state = [&]() { return w->bi + (size_t)((done + 1) & 1) * nseg; };
+  const size_t bytes = bicgstab_state_bytes(m);
   if (qo) {
     queue_iters(std::min(qo->budget, maxit));
-    copy_state(qo->state_out, w->bi, bicgstab_state_bytes(m), s);
+    copy_state(qo->state_out, state(), bytes, s);
     return SolveResult{};
   }
-  const size_t bytes = bicgstab_state_bytes(m);
   queue_iters(std::min(maxit, std::max(2, (hint ? *hint : 0) - 1)));
   int slot = 0;
-  post_poll(m, w, w->bi, bytes, slot);
+  post_poll(m, w, state(), bytes, slot);
   const BiState* hs = nullptr;
   while (true) {
     bool more = done < maxit;
     if (more) {
       queue_iters(std::min(1, maxit - done));
-      post_poll(m, w, w->bi, bytes, slot ^ 1);
+      post_poll(m, w, state(), bytes, slot ^ 1);
     }
     hs = static_cast<const BiState*>(wait_poll(w, slot));
     bool any = false;
@@ -933,8 +1089,9 @@ static SolveResult bicgstab_nc(difvm_mesh* m, SellMatrix A, const double* b, dou
 
 SolveResult bicgstab(difvm_mesh* m, int ncomp, SellMatrix A, const double* b, double* x, double tol, int maxit,
                      const QueueOnly* qo, int* hint) {
-  if (ncomp == 1) return bicgstab_nc<1>(m, A, b, x, tol, maxit, qo, hint);
-  return bicgstab_nc<3>(m, A, b, x, tol, maxit, qo, hint);
+  const bool fin = m->d.ntile > BI_FIN_TILES;
+  if (ncomp == 1) return (fin ? bicgstab_nc<1, true> : bicgstab_nc<1, false>)(m, A, b, x, tol, maxit, qo, hint);
+  return (fin ? bicgstab_nc<3, true> : bicgstab_nc<3, false>)(m, A, b, x, tol, maxit, qo, hint);
 }
 
 // ---------------------------------------------------------------------------------------------

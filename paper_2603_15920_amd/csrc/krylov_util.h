@@ -66,6 +66,7 @@ constexpr int CPT = TILE / BLOCK;  // cells per thread
 
 struct Tiles {
   int ntile;
+  int one_nc;  // > 0: one segment of that many cells (tile t starts at cell t TILE), else 0
   const int32_t* __restrict__ lo;
   const int32_t* __restrict__ hi;
   const int32_t* __restrict__ seg;
@@ -74,16 +75,20 @@ struct Tiles {
 };
 inline Tiles tiles_of(const difvm_mesh* m) {
   const DMesh& d = m->d;
-  return {d.ntile, d.tile_lo, d.tile_hi, d.tile_seg, d.seg_tile_first, d.seg_tile_n};
+  return {d.ntile, d.nseg == 1 ? d.nc : 0, d.tile_lo, d.tile_hi, d.tile_seg, d.seg_tile_first, d.seg_tile_n};
 }
 
 struct TileIdx {
   int t, s, lo, hi;
 };
-__device__ __forceinline__ TileIdx tile_idx(const Tiles& T) {
-  int t = xcd_tile(blockIdx.x, gridDim.x);
+// with one segment every index follows from t, so that no load waits for the tile tables
+__device__ __forceinline__ TileIdx tile_at(const Tiles& T, int t) {
+  if (T.one_nc > 0) return {t, 0, t * TILE, min(t * TILE + TILE, T.one_nc)};
   return {t, T.seg[t], T.lo[t], T.hi[t]};
 }
+__device__ __forceinline__ TileIdx tile_idx(const Tiles& T) { return tile_at(T, xcd_tile(blockIdx.x, gridDim.x)); }
+__device__ __forceinline__ int seg_first(const Tiles& T, int s) { return T.one_nc > 0 ? 0 : T.first[s]; }
+__device__ __forceinline__ int seg_count(const Tiles& T, int s) { return T.one_nc > 0 ? T.ntile : T.count[s]; }
 
 // fixed-order sum of a segment's tile partials (NV arrays, value-major over all tiles, the segment's
 // n tiles from tile f) by a block of NT threads; every thread ends with the totals (sum_seg).  Each
@@ -125,6 +130,86 @@ __device__ __forceinline__ void put_partial(double (&v)[NV], double* __restrict_
   if (threadIdx.x == 0)
 #pragma unroll
     for (int k = 0; k < NV; ++k) part[(size_t)k * ntile + t] = v[k];
+}
+
+// ---------------------------------------------------------------------------------------------
+// Reductions of a block of TILE threads with one cell each.  Summing several values over a wave by one
+// butterfly per value costs 6 exchanges each, all through the LDS pipe; halving the set of values at each
+// of the first steps instead (a lane keeps the half its lane bit names and sends the other) leaves one
+// value per group of lanes after log2 P steps: 10 exchanges for 8 values instead of 48.
+// ---------------------------------------------------------------------------------------------
+constexpr int TILE_WAVES = TILE / 64;
+
+// v[0..P) summed over the wave (P a power of two): value k ends in v[0] of the lanes k 64/P .. (k+1) 64/P - 1
+template <int P>
+__device__ __forceinline__ void wave_sum_split(double (&v)[P]) {
+  const int lane = threadIdx.x & 63;
+  int off = 32;
+#pragma unroll
+  for (int m = P / 2; m >= 1; m /= 2, off /= 2) {
+    const bool up = lane & off;
+#pragma unroll
+    for (int k = 0; k < m; ++k) {
+      const double mine = up ? v[k + m] : v[k], send = up ? v[k] : v[k + m];
+      v[k] = mine + __shfl_xor(send, off, 64);
+    }
+  }
+#pragma unroll
+  for (; off > 0; off /= 2) v[0] += __shfl_xor(v[0], off, 64);
+}
+
+// the tile's sums of NV values per thread into part[k ntile + t]: wave sums, then the waves in order
+template <int NV>
+__device__ __forceinline__ void put_tile_partial(const double (&v)[NV], double* __restrict__ part, int ntile, int t) {
+  __shared__ double lds[NV][TILE_WAVES + 1];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  constexpr int P = NV > 4 ? 8 : NV > 2 ? 4 : NV;  // values of the first group (padded with zeros)
+  static_assert(NV <= 9, "two groups: up to 8 values, then one");
+  double a[P];
+#pragma unroll
+  for (int k = 0; k < P; ++k) a[k] = k < NV ? v[k] : 0.0;
+  wave_sum_split<P>(a);
+  if (const int k = lane / (64 / P); lane % (64 / P) == 0 && k < NV) lds[k][wid] = a[0];
+  if constexpr (NV > P) {
+    double b[1] = {v[NV - 1]};
+    wave_sum_split<1>(b);
+    if (lane == 0) lds[NV - 1][wid] = b[0];
+  }
+  __syncthreads();
+  if (threadIdx.x < NV) {
+    double s = 0.0;
+#pragma unroll
+    for (int q = 0; q < TILE_WAVES; ++q) s += lds[threadIdx.x][q];
+    part[(size_t)threadIdx.x * ntile + t] = s;
+  }
+}
+
+// the segment's totals of NV tile partials (n tiles from tile f) for every thread of a block of TILE
+// threads, in a fixed order: wave k sums value k, its lanes the tiles lane, lane + 64, ... (eight loads
+// in flight), then a butterfly
+template <int NV>
+__device__ __forceinline__ void tile_seg_totals(const double* __restrict__ part, int ntile, int f, int n,
+                                                double (&tot)[NV]) {
+  static_assert(NV <= TILE_WAVES, "one wave per value");
+  __shared__ double sh[NV];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  if (wid < NV) {
+    constexpr int UN = 8;
+    double s = 0.0;
+    for (int q = lane; q < n; q += UN * 64) {
+      double w[UN];
+#pragma unroll
+      for (int u = 0; u < UN; ++u) w[u] = part[(size_t)wid * ntile + f + min(q + u * 64, n - 1)];
+#pragma unroll
+      for (int u = 0; u < UN; ++u)
+        if (q + u * 64 < n) s += w[u];
+    }
+    s = wave_sum(s);
+    if (lane == 0) sh[wid] = s;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < NV; ++k) tot[k] = sh[k];
 }
 
 // one read of a flag per block, shared through LDS, so every wave of the block takes the same branch
