@@ -251,18 +251,17 @@ __global__ __launch_bounds__(BLOCK) void k_amg_cheb_post1(SellView K, const doub
 }
 
 // level 0, up, second pass: z = t + d0 + d1 with rh1 = theta d0 - D^-1 K d0, and per-tile partials
-// of r.z.  A block per tile and one cell per thread, like the other finest-level passes (four cells
-// per thread in 256-thread blocks left each thread's rows one after another).
-constexpr int POST2_NT = TILE;
-template <bool OFF16>
-__global__ __launch_bounds__(POST2_NT) void k_amg_cheb_post2(SellView K, Tiles T, const double* __restrict__ r,
+// of r.z (part[k] by tile or by quarter, as the CG reads them).  One cell per thread, like the other
+// finest-level passes (four cells per thread left each thread's rows one after another).
+template <bool OFF16, bool FINE>
+__global__ __launch_bounds__(FINE ? QUARTER : TILE) void k_amg_cheb_post2(SellView K, Tiles T, const double* __restrict__ r,
                                                              const double* __restrict__ t, const double* __restrict__ d0,
                                                              double* __restrict__ z, double* __restrict__ part, Cheb c,
                                                              StopFlags ctl) {
-  TileIdx ti = tile_idx(T);
+  const Span sp = span_of<FINE>(T);
   if (stopped(ctl)) return;
   double v[1] = {0.0};
-  if (const int i = ti.lo + (int)threadIdx.x; i < ti.hi) {
+  if (const int i = sp.lo + (int)threadIdx.x; i < sp.hi) {
     SlotRange R = slots_of(K, i);
     const double di = K.diag[i], d0i = d0[i], ti = t[i], ri = r[i];
     double kd0 = di * d0i + sell_offdiag<OFF16>(K, i, R, [&](int j) { return d0[j]; });
@@ -271,15 +270,7 @@ __global__ __launch_bounds__(POST2_NT) void k_amg_cheb_post2(SellView K, Tiles T
     z[i] = zi;
     v[0] = ri * zi;
   }
-  if (part) put_partial<1, POST2_NT>(v, part, T.ntile, ti.t);
-}
-
-// SW lanes per row: partial sums of the row's entries, then a fixed xor-shuffle tree
-template <int SW>
-__device__ __forceinline__ double lane_sum(double s) {
-#pragma unroll
-  for (int off = SW / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, SW);
-  return s;
+  if (part) put_partial<1, FINE ? QUARTER : TILE, FINE>(v, part, T.ntile, sp);
 }
 
 // Coarse levels smooth with the same degree-2 Chebyshev sweep as level 0 (interval [hi / 10, hi],
@@ -309,7 +300,7 @@ __global__ __launch_bounds__(BLOCK) void k_amg_restrict(int n, const int32_t* __
   DIFVM_AMG_ROW(ptr, n);
   const double dg = diag ? diag[rr] : 1.0;
   double s = csr_lane_dot<SW>(lo, hi, col, val, [&](int j) { return xin[j]; });
-  s = lane_sum<SW>(s);
+  s = lanes_sum<SW>(s);
   if (row < n && lane == 0) {
     out[row] = s;
     if (diag) outd[row] = s / dg;
@@ -325,7 +316,7 @@ __global__ __launch_bounds__(BLOCK) void k_amg_cpre1(int n, const int32_t* __res
   DIFVM_AMG_ROW(ptr, n);
   const double di = diag[rr], rh0 = bd[rr];
   double s = csr_lane_dot<SW>(lo, hi, col, val, [&](int j) { return bd[j]; });
-  s = lane_sum<SW>(s);
+  s = lanes_sum<SW>(s);
   if (row < n && lane == 0) {
     double d0 = rh0 * c.inv_theta;
     double kd0 = di * d0 + s * c.inv_theta;
@@ -344,7 +335,7 @@ __global__ __launch_bounds__(BLOCK) void k_amg_cpre2(int n, const int32_t* __res
   DIFVM_AMG_ROW(ptr, n);
   const double bi = b[rr], di = diag[rr], xi = xs[rr];
   double s = csr_lane_dot<SW>(lo, hi, col, val, [&](int j) { return xs[j]; });
-  s = lane_sum<SW>(s);
+  s = lanes_sum<SW>(s);
   if (row < n && lane == 0) res[row] = bi - di * xi - s;
 }
 
@@ -361,8 +352,8 @@ __global__ __launch_bounds__(BLOCK) void k_amg_cup1(int n, const int32_t* __rest
   const double xi = xs[rr], ri = res[rr], di = diag[rr];
   double sp, sq;
   csr_lane_dot2<SW>(lo, hi, col, pv, ap, [&](int j) { return xc[j]; }, sp, sq);
-  sp = lane_sum<SW>(sp);
-  sq = lane_sum<SW>(sq);
+  sp = lanes_sum<SW>(sp);
+  sq = lanes_sum<SW>(sq);
   if (row < n && lane == 0) {
     t[row] = xi + sp;
     d0[row] = (ri - sq) / di * c.inv_theta;
@@ -379,7 +370,7 @@ __global__ __launch_bounds__(BLOCK) void k_amg_cup2(int n, const int32_t* __rest
   DIFVM_AMG_ROW(ptr, n);
   const double di = diag[rr], d0i = d0[rr], ti = t[rr];
   double s = csr_lane_dot<SW>(lo, hi, col, val, [&](int j) { return d0[j]; });
-  s = lane_sum<SW>(s);
+  s = lanes_sum<SW>(s);
   if (row < n && lane == 0) {
     double rh1 = c.theta * d0i - (di * d0i + s) / di;
     x[row] = ti + d0i + (c.c_d * d0i + c.c_r * rh1);
@@ -422,7 +413,7 @@ __global__ __launch_bounds__(BLOCK) void k_amg_coarsest(int n, const double* __r
 #pragma unroll
   for (int u = 0; u < U; ++u)
     if ((int)threadIdx.x + u * BLOCK < n) s += v[u] * w[u];
-  s = lane_sum<64>(s);
+  s = lanes_sum<64>(s);
   if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = s;
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -699,13 +690,13 @@ static void launch_vcycle(const AmgDev* a, hipStream_t s, SellMatrix Km, const d
     k_amg_prolong<<<grid_for(P.n), BLOCK, 0, s>>>(P.n, P.ptr, P.col, P.val, a->xs[0], a->x[1], a->t[0], ctl);
   }
   Tiles T = tiles_of(m);
-  if (K.off16) {
-    k_amg_cheb_post1<true><<<grid_for(nc), BLOCK, 0, s>>>(K, r, a->t[0], a->d0[0], c[0], ctl);
-    k_amg_cheb_post2<true><<<T.ntile, POST2_NT, 0, s>>>(K, T, r, a->t[0], a->d0[0], z, part, c[0], ctl);
-  } else {
-    k_amg_cheb_post1<false><<<grid_for(nc), BLOCK, 0, s>>>(K, r, a->t[0], a->d0[0], c[0], ctl);
-    k_amg_cheb_post2<false><<<T.ntile, POST2_NT, 0, s>>>(K, T, r, a->t[0], a->d0[0], z, part, c[0], ctl);
-  }
+  const bool fine = fine_spans(m);
+  (K.off16 ? k_amg_cheb_post1<true> : k_amg_cheb_post1<false>)<<<grid_for(nc), BLOCK, 0, s>>>(K, r, a->t[0], a->d0[0],
+                                                                                               c[0], ctl);
+  (K.off16 ? fine ? k_amg_cheb_post2<true, true> : k_amg_cheb_post2<true, false>
+           : fine ? k_amg_cheb_post2<false, true> : k_amg_cheb_post2<false, false>)<<<n_spans(m), fine ? QUARTER : TILE, 0,
+                                                                                       s>>>(K, T, r, a->t[0], a->d0[0], z,
+                                                                                            part, c[0], ctl);
   DIFVM_HIP(hipGetLastError());
 }
 

@@ -229,12 +229,64 @@ __device__ __forceinline__ void store_rows_if(T* __restrict__ out, int base, int
 }
 
 // ---------------------------------------------------------------------------------------------
-// deterministic reductions: wave64 butterfly, then the 4 waves of a 256-thread block in order
+// deterministic reductions.  A wave's sum pairs lanes at distance 32, 16, 8, 1, 2, 4 in that order, with
+// register exchanges only (the gfx950 permlane swaps and DPP; a __shfl_xor goes through the LDS pipe, about
+// seven times the latency of such a step).  At distance 4 the mirrored half row stands for the other quad,
+// whose lanes all hold its sum by then.  Every lane of the wave must be active.
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+template <int CTRL>
+__device__ __forceinline__ double dpp_mov(double v) {
+  int lo = __double2loint(v), hi = __double2hiint(v);
+  lo = __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false);
+  hi = __builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_ROR8 = 0x128;  // ROR8: lane ^ 8
+
+// a + its value in the other half (32) or neighbouring row (16) of the wave, b's taken by the upper half
+// (odd rows): lanes of the lower half (even rows) end with a's pair sum, the others with b's
+__device__ __forceinline__ double swap_add32(double a, double b) {
+#pragma clang fp contract(off)
+  auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+  auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+__device__ __forceinline__ double swap_add16(double a, double b) {
+#pragma clang fp contract(off)
+  auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+  auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+// sum over groups of SW consecutive lanes (a power of two): every lane ends with its group's
+// (no contraction: a lane's own product fused into a sum would make the lanes' results differ)
+template <int SW>
+__device__ __forceinline__ double lanes_sum(double v) {
+#pragma clang fp contract(off)
+  if constexpr (SW >= 64) v = swap_add32(v, v);
+  if constexpr (SW >= 32) v = swap_add16(v, v);
+  if constexpr (SW >= 16) v += dpp_mov<DPP_ROR8>(v);
+  if constexpr (SW >= 2) v += dpp_mov<DPP_XOR1>(v);
+  if constexpr (SW >= 4) v += dpp_mov<DPP_XOR2>(v);
+  if constexpr (SW >= 8) v += dpp_mov<DPP_HALF_MIRROR>(v);
   return v;
+}
+__device__ __forceinline__ double wave_sum(double v) { return lanes_sum<64>(v); }
+// sum over rows of 16 lanes, pairing at distance 1, 2, 4, 8: quads of lanes first
+__device__ __forceinline__ double quad_sum(double v) {
+#pragma clang fp contract(off)
+  v += dpp_mov<DPP_XOR1>(v);
+  return v + dpp_mov<DPP_XOR2>(v);
+}
+__device__ __forceinline__ double row_sum(double v) {
+#pragma clang fp contract(off)
+  v = quad_sum(v);
+  v += dpp_mov<DPP_HALF_MIRROR>(v);
+  return v + dpp_mov<DPP_ROR8>(v);
+}
+// lane 0's value for the whole wave
+__device__ __forceinline__ double wave_first(double v) {
+  return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
+                          __builtin_amdgcn_readfirstlane(__double2loint(v)));
 }
 
 // block of NT threads: every thread ends with the block total (fixed summation order)

@@ -15,6 +15,10 @@
 #include "krylov_util.h"
 #include "ops.h"
 
+// One arithmetic for every form of a solver (by tile, by quarter, a segment per block): products and sums
+// are fused where an fma is written and nowhere else.
+#pragma clang fp contract(off)
+
 namespace difvm {
 
 // BiCGStab state of one segment (up to three systems sharing its matrix) during one iteration
@@ -59,8 +63,8 @@ static KrylovWork* make_work(difvm_mesh* m) {
     w->z = dalloc<double>(c, n3); w->t = dalloc<double>(c, n3);
     w->colscaled = dalloc<double>(c, m->d.nslot);
     const int nseg = m->d.nseg;
-    // values per tile: PCG uses 6, BiCGStab 6 + 3 + 9 and as many totals per segment
-    w->partials = dalloc<double>(c, (size_t)18 * (w->ntile + nseg));
+    // values per span: PCG uses 6, BiCGStab 6 + 3 + 9 and as many totals per segment
+    w->partials = dalloc<double>(c, (size_t)18 * (n_spans(m) + nseg));
     w->pcg = static_cast<PcgCtl*>(dmalloc(c, sizeof(BiState) * nseg));  // PcgCtl is smaller (asserted below)
     w->bi = dalloc<BiState>(c, 2 * (size_t)nseg);
     for (int q = 0; q < 2; ++q) {
@@ -149,98 +153,127 @@ void sell_spmv(const difvm_mesh* m, int ncomp, SellMatrix A, const double* x, do
 //                                                     partials A = (p.q); first tile publishes rho
 //   upd_k:  alpha = rho_{k-1}/(p.q); x += alpha p; r -= alpha q; z = r/d   partials B
 // The segment's first tile records iterations / residual / status; its kernels return at once
-// after its stop.  The product runs 512 threads x 2 cells per 1024-cell tile, the update 256 x 4
-// (measured best on gfx950 for these two memory patterns); the first four slots of a row are
+// after its stop.  Large meshes: the product runs 512 threads x 2 cells per 1024-cell tile, the update
+// 256 x 4 (measured best on gfx950 for these two memory patterns); the first four slots of a row are
 // unrolled so their loads are in flight together.
+//
+// Up to FINE_TILES tiles a block takes a quarter of a tile (see Span), a thread a cell, and every load that
+// does not wait for the scalars (row, neighbours' z and p, own values) is issued before the partials are
+// summed: there a kernel's time is its chain of dependent loads, while at 1,029 tiles the registers of the
+// loads in flight halve the resident blocks (25.6 us and more for the product against 19.8).  Jacobi-CG per
+// iteration at 93,750 cells: 12.7 us with blocks of a tile, 9.0 now (product 7.2 to 5.0 us).
+//
+// Meshes whose segments have at most SEG_TILES tiles do not come here at all: see k_pcg_segment.  The
+// arithmetic of an iteration is the same in every form, operation by operation (written with explicit fma,
+// reduced in one order), so a member of a batch has its bits whichever form its neighbours bring about.
 // ---------------------------------------------------------------------------------------------
 static_assert(sizeof(PcgCtl) <= sizeof(BiState), "PCG states share the BiState-sized allocation");
 
 constexpr int PCG_SPMV_NT = 512;  // threads per block of the product kernel (TILE / NT cells each)
 
-__global__ __launch_bounds__(BLOCK) void k_pcg_init1(SellView A, Tiles T, const double* __restrict__ b,
-                                                     const double* __restrict__ x, double* __restrict__ r,
-                                                     double* __restrict__ part) {
-  TileIdx ti = tile_idx(T);
+__device__ __forceinline__ double cg_dir(double z, double beta, double p) { return __builtin_fma(beta, p, z); }
+
+template <bool FINE>
+__global__ __launch_bounds__(FINE ? QUARTER : TILE) void k_pcg_init1(SellView A, Tiles T, const double* __restrict__ b,
+                                                                     const double* __restrict__ x,
+                                                                     double* __restrict__ r,
+                                                                     double* __restrict__ part) {
+  const Span ti = span_of<FINE>(T);
+  const int i = ti.lo + (int)threadIdx.x;
   double v[2] = {0.0, 0.0};
-  FOR_TILE_CELLS(i) {
-    double ax[1];
-    sell_row<1>(A, i, x, ax);
-    double bi = b[i], ri = bi - ax[0];
+  if (i < ti.hi) {
+    const double bi = b[i];
+    double ax = A.diag[i] * x[i];
+    SlotRange R = slots_of(A, i);
+    const bool off16 = A.off16 != nullptr;  // the same for every thread: a uniform branch
+    walk_row<4>(row_len(A, i, R), [&](auto Wc, int k0) {
+      constexpr int N = decltype(Wc)::value;
+      double a[N], xj[N];
+      int j[N];
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        int at = R.base + (k0 + k) * SLICE;
+        a[k] = A.val[at];
+        j[k] = off16 ? i + A.off16[at] : A.col[at];
+      }
+#pragma unroll
+      for (int k = 0; k < N; ++k) xj[k] = x[j[k]];
+#pragma unroll
+      for (int k = 0; k < N; ++k) ax = __builtin_fma(a[k], xj[k], ax);
+    });
+    const double ri = bi - ax;
     r[i] = ri;
-    v[0] += bi * bi;
-    v[1] += ri * ri;
+    v[0] = bi * bi;
+    v[1] = ri * ri;
   }
-  put_partial<2>(v, part, T.ntile, ti.t);
+  put_partial<2, FINE ? QUARTER : TILE, FINE>(v, part, T.ntile, ti);
 }
 
 // JAC: Jacobi preconditioner (z = r/d here); otherwise z and the r.z partials come from the V-cycle
 // that follows, and this kernel stores only the r.r partials
-template <bool JAC>
-__global__ __launch_bounds__(BLOCK) void k_pcg_init2(SellView A, Tiles T, double* __restrict__ x, const double* __restrict__ r,
-                                                     double* __restrict__ z, double* __restrict__ p0,
-                                                     const double* __restrict__ part_in, double* __restrict__ partB,
-                                                     PcgCtl* ctls) {
-  TileIdx ti = tile_idx(T);
+template <bool JAC, bool FINE>
+__global__ __launch_bounds__(FINE ? QUARTER : TILE) void k_pcg_init2(
+    SellView A, Tiles T, double* __restrict__ x, const double* __restrict__ r, double* __restrict__ z,
+    double* __restrict__ p0, const double* __restrict__ part_in, double* __restrict__ partB, PcgCtl* ctls) {
+  constexpr int NT = FINE ? QUARTER : TILE;
+  const Span ti = span_of<FINE>(T);
   PcgCtl* ctl = ctls + ti.s;
+  const int i = ti.lo + (int)threadIdx.x, ii = min(i, ti.end - 1);
+  const double ri = r[ii], di = JAC ? A.diag[ii] : 1.0, tol = ctl->tol;
   double s[2];
-  sum_seg<2>(part_in, T, ti.s, s);
+  seg_totals<2, NT, FINE>(part_in, T.ntile, seg_first(T, ti.s), seg_count(T, ti.s), s);
   double bn = sqrt(s[0]), rn = sqrt(s[1]);
   bool zero_b = bn == 0.0;
-  bool stop = zero_b || rn <= ctl->tol * bn;
-  if (ti.t == T.first[ti.s] && threadIdx.x == 0) {
+  bool stop = zero_b || rn <= tol * bn;
+  if (ti.t == seg_first(T, ti.s) && ti.j == 0 && threadIdx.x == 0) {
     ctl->bn = bn;
     ctl->res = zero_b ? 0.0 : rn / bn;
     ctl->iters = 0;
     ctl->status = 0;
     ctl->done = stop ? 1 : 0;
   }
-  if (zero_b) {
-    FOR_TILE_CELLS(i) x[i] = 0.0;
-  }
+  if (zero_b && i < ti.hi) x[i] = 0.0;
   if (stop) return;
+  if (i < ti.hi) p0[i] = 0.0;  // p_1 = z_0 + 0 * p_0
   if constexpr (JAC) {
-    double v[2] = {0.0, 0.0};
-    FOR_TILE_CELLS(i) {
-      double ri = r[i], zi = ri / A.diag[i];
-      z[i] = zi;
-      p0[i] = 0.0;  // p_1 = z_0 + 0 * p_0
-      v[0] += ri * ri;
-      v[1] += ri * zi;
-    }
-    put_partial<2>(v, partB, T.ntile, ti.t);
+    const double zi = ri / di;
+    if (i < ti.hi) z[i] = zi;
+    double v[2] = {i < ti.hi ? ri * ri : 0.0, i < ti.hi ? ri * zi : 0.0};
+    put_partial<2, NT, FINE>(v, partB, T.ntile, ti);
   } else {
-    double v[1] = {0.0};
-    FOR_TILE_CELLS(i) {
-      double ri = r[i];
-      p0[i] = 0.0;
-      v[0] += ri * ri;
-    }
-    put_partial<1>(v, partB, T.ntile, ti.t);
+    double v[1] = {i < ti.hi ? ri * ri : 0.0};
+    put_partial<1, NT, FINE>(v, partB, T.ntile, ti);
   }
 }
 
-// (A (z + beta p))_i with the slot loads of a width-W row issued together
+// (A (z + beta p))_i added to acc, with the loads of the row's first m <= W slots issued together
 // OFF16: columns read as 16-bit offsets from the row (half the index bytes of the 32-bit columns)
 template <int W, bool OFF16>
-__device__ __forceinline__ double dir_row(const SellView& A, int i, int base, double acc, double beta,
-                                          const double* __restrict__ z, const double* __restrict__ pp) {
+struct CgRow {
   double a[W], zj[W], pj[W];
-  int j[W];
+  __device__ __forceinline__ void load(const SellView& A, int i, int base, const double* __restrict__ z,
+                                       const double* __restrict__ pp, int m = W) {
+    int j[W];
 #pragma unroll
-  for (int sl = 0; sl < W; ++sl) {
-    a[sl] = A.val[base + sl * SLICE];
-    if constexpr (OFF16) j[sl] = i + A.off16[base + sl * SLICE];
-    else j[sl] = A.col[base + sl * SLICE];
+    for (int sl = 0; sl < W; ++sl) {
+      const int at = base + (sl < m ? sl : 0) * SLICE;  // past m the first slot again, not added
+      a[sl] = A.val[at];
+      if constexpr (OFF16) j[sl] = i + A.off16[at];
+      else j[sl] = A.col[at];
+    }
+#pragma unroll
+    for (int sl = 0; sl < W; ++sl) {
+      zj[sl] = z[j[sl]];
+      pj[sl] = pp[j[sl]];
+    }
   }
+  __device__ __forceinline__ double add(double acc, double beta, int m = W) const {
 #pragma unroll
-  for (int sl = 0; sl < W; ++sl) {
-    zj[sl] = z[j[sl]];
-    pj[sl] = pp[j[sl]];
+    for (int sl = 0; sl < W; ++sl)
+      if (sl < m) acc = __builtin_fma(a[sl], cg_dir(zj[sl], beta, pj[sl]), acc);
+    return acc;
   }
-#pragma unroll
-  for (int sl = 0; sl < W; ++sl) acc += a[sl] * (zj[sl] + beta * pj[sl]);
-  return acc;
-}
+};
 
 // Tiles of this block: one tile per block when the grid has one block per tile (XCD-aware order),
 // otherwise (a grid of G < ntile blocks, G a multiple of 8) block b walks tiles lo + b/8, lo + b/8 +
@@ -260,36 +293,53 @@ __device__ __forceinline__ TileWalk tile_walk(int ntile) {
   return {lo + (b >> 3), per, hi};
 }
 
-// iteration k >= 1: stopping test of iterate k-1, then p_k and q = A p_k
-template <bool OFF16>
-__global__ __launch_bounds__(PCG_SPMV_NT) void k_pcg_spmv(SellView A, Tiles T, int k, const double* __restrict__ z,
-                                                          const double* __restrict__ p_prev, double* __restrict__ p_cur,
-                                                          double* __restrict__ q, const double* __restrict__ partB,
-                                                          double* __restrict__ partA, PcgCtl* ctls) {
-  constexpr int NT = PCG_SPMV_NT, C = TILE / NT;
-  TileWalk tw = tile_walk(T.ntile);
+// iteration k >= 1: stopping test of iterate k-1, then p_k and q = A p_k.  FINE: a quarter of a tile per
+// block, every load issued before the partial sums (at most four slots of a row; the rest after).
+template <bool OFF16, bool FINE>
+__global__ __launch_bounds__(FINE ? QUARTER : PCG_SPMV_NT) void k_pcg_spmv(
+    SellView A, Tiles T, int k, const double* __restrict__ z, const double* __restrict__ p_prev,
+    double* __restrict__ p_cur, double* __restrict__ q, const double* __restrict__ partB, double* __restrict__ partA,
+    PcgCtl* ctls) {
+  constexpr int NT = FINE ? QUARTER : PCG_SPMV_NT, C = FINE ? 1 : TILE / NT;
+  const TileWalk tw = FINE ? TileWalk{xcd_tile(blockIdx.x, gridDim.x), 1, 0} : tile_walk(T.ntile);
   int cur = -1;
   bool skip = true;
   double beta = 0.0;
-  for (int t = tw.t; t < tw.end; t += tw.step) {
-    const int s = T.seg[t], lo = T.lo[t], hi = T.hi[t];
+  __shared__ int done_sh;
+  for (int b = tw.t; b < (FINE ? tw.t + 1 : tw.end); b += tw.step) {
+    const Span ti = span_at<FINE>(T, b);
+    const int s = ti.s;
+    // FINE: the row's loads, in flight with the segment's
+    CgRow<4, OFF16> row;
+    SlotRange R0{0, 0};
+    int n0 = 0;
+    double zi = 0.0, pi0 = 0.0, di = 0.0;
+    if constexpr (FINE) {
+      const int i = min(ti.lo + (int)threadIdx.x, ti.end - 1);
+      R0 = slots_of(A, i);
+      n0 = row_len(A, i, R0);
+      zi = z[i];
+      pi0 = p_prev[i];
+      di = A.diag[i];
+      if (n0 > 0) row.load(A, i, R0.base, z, p_prev, n0);
+    }
     if (s != cur) {
       // first tile of segment s for this block: the segment's stopping test and beta.  Every load
       // that needs only s (the flag's included) is issued at once, then the partials', so the block
       // waits for two load latencies before its sum instead of five.
       cur = s;
       PcgCtl* ctl = ctls + s;
-      const int f = T.first[s], n = T.count[s], maxit = ctl->maxit, done = ctl->done;
+      const int f = seg_first(T, s), n = seg_count(T, s), maxit = ctl->maxit, done = ctl->done;
       const double tol = ctl->tol, bn = ctl->bn, rho_older = ctl->rho[k & 1];  // rho_{k-2}
       double s2[2];  // (r_{k-1}.r_{k-1}, r_{k-1}.z_{k-1})
-      seg_thread_sum<2, NT>(partB, T.ntile, f, n, s2);
-      // thread 0's read decides for the block: the segment's first tile may be setting the flag
-      // during this launch
-      skip = block_share(done);
-      __shared__ double lds[2][NT / 64];
-      block_sum<2, NT>(s2, lds);
+      // thread 0's read of the flag decides for the block: the segment's first tile may be setting it
+      // during this launch (the totals' barriers order it; the one before them frees the previous value)
+      __syncthreads();
+      if (threadIdx.x == 0) done_sh = done;
+      seg_totals<2, NT, FINE>(partB, T.ntile, f, n, s2);
+      skip = done_sh != 0;
       if (!skip) {
-        bool lead = t == f && threadIdx.x == 0;  // the block holding the segment's first tile
+        bool lead = ti.t == f && ti.j == 0 && threadIdx.x == 0;  // the segment's first block
         double rho = s2[1];
         if (lead) ctl->rho[(k - 1) & 1] = rho;
         beta = 0.0;
@@ -317,85 +367,367 @@ __global__ __launch_bounds__(PCG_SPMV_NT) void k_pcg_spmv(SellView A, Tiles T, i
       }
     }
     if (skip) continue;
-    double v[1] = {0.0};
+    double v[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-      int i = lo + c * NT + threadIdx.x;
-      if (i < hi) {
-        double pi = z[i] + beta * p_prev[i];
-        SlotRange R = slots_of(A, i);
-        const int nrow = row_len(A, i, R);
-        double acc = A.diag[i] * pi;
-        walk_row<4>(nrow, [&](auto Wc, int k0) {
-          acc = dir_row<decltype(Wc)::value, OFF16>(A, i, R.base + k0 * SLICE, acc, beta, z, p_prev);
-        });
+      const int i = ti.lo + c * NT + (int)threadIdx.x;
+      v[c] = 0.0;
+      if (i < ti.hi) {
+        double pi, acc;
+        if constexpr (FINE) {
+          pi = cg_dir(zi, beta, pi0);
+          acc = row.add(di * pi, beta, n0);
+          for (int k0 = 4; k0 < n0; ++k0) {
+            CgRow<1, OFF16> one;
+            one.load(A, i, R0.base + k0 * SLICE, z, p_prev);
+            acc = one.add(acc, beta);
+          }
+        } else {
+          pi = cg_dir(z[i], beta, p_prev[i]);
+          SlotRange R = slots_of(A, i);
+          acc = A.diag[i] * pi;
+          walk_row<4>(row_len(A, i, R), [&](auto Wc, int k0) {
+            CgRow<decltype(Wc)::value, OFF16> chunk;
+            chunk.load(A, i, R.base + k0 * SLICE, z, p_prev);
+            acc = chunk.add(acc, beta);
+          });
+        }
         p_cur[i] = pi;
         q[i] = acc;
-        v[0] += pi * acc;
+        v[c] = pi * acc;
       }
     }
-    put_partial<1, NT>(v, partA, T.ntile, t);
+    put_partial<1, NT, FINE>(v, partA, T.ntile, ti);
   }
 }
 
+// G blocks walking the tiles, or (G = 0) a block per quarter
 static void launch_pcg_spmv(int G, hipStream_t s, const SellView& V, const Tiles& T, int k, const double* z,
                             const double* p_prev, double* p_cur, double* q, const double* partB, double* partA,
                             PcgCtl* ctls) {
-  if (V.off16) k_pcg_spmv<true><<<G, PCG_SPMV_NT, 0, s>>>(V, T, k, z, p_prev, p_cur, q, partB, partA, ctls);
-  else k_pcg_spmv<false><<<G, PCG_SPMV_NT, 0, s>>>(V, T, k, z, p_prev, p_cur, q, partB, partA, ctls);
+  if (G == 0) {
+    if (V.off16) k_pcg_spmv<true, true><<<4 * T.ntile, QUARTER, 0, s>>>(V, T, k, z, p_prev, p_cur, q, partB, partA, ctls);
+    else k_pcg_spmv<false, true><<<4 * T.ntile, QUARTER, 0, s>>>(V, T, k, z, p_prev, p_cur, q, partB, partA, ctls);
+  } else {
+    if (V.off16) k_pcg_spmv<true, false><<<G, PCG_SPMV_NT, 0, s>>>(V, T, k, z, p_prev, p_cur, q, partB, partA, ctls);
+    else k_pcg_spmv<false, false><<<G, PCG_SPMV_NT, 0, s>>>(V, T, k, z, p_prev, p_cur, q, partB, partA, ctls);
+  }
 }
 
 // iteration k: alpha, x and r updates, z = r/d, partials of r.r and r.z (streaming loads issued
-// before the partial sum so they overlap its latency)
-template <bool JAC>
-__global__ __launch_bounds__(BLOCK) void k_pcg_update(SellView A, Tiles T, double* __restrict__ x, double* __restrict__ r,
-                                                      double* __restrict__ z, const double* __restrict__ p_cur,
-                                                      const double* __restrict__ q, const double* __restrict__ partA,
-                                                      double* __restrict__ partB, int k, PcgCtl* ctls) {
-  TileIdx ti = tile_idx(T);
+// before the partial sum so they overlap its latency).  FINE: a quarter of a
+// tile per block, and the loads do not wait for the stop flag either.
+template <bool JAC, bool FINE>
+__global__ __launch_bounds__(FINE ? QUARTER : BLOCK) void k_pcg_update(
+    SellView A, Tiles T, double* __restrict__ x, double* __restrict__ r, double* __restrict__ z,
+    const double* __restrict__ p_cur, const double* __restrict__ q, const double* __restrict__ partA,
+    double* __restrict__ partB, int k, PcgCtl* ctls) {
+  constexpr int NT = FINE ? QUARTER : BLOCK, C = FINE ? 1 : TILE / NT, NV = JAC ? 2 : 1;
+  const Span ti = span_of<FINE>(T);
   PcgCtl* ctl = ctls + ti.s;
   // only earlier launches write the flag, so every wave reads the same value and the block needs
   // no barrier to agree on it
-  if (ctl->done) return;
-  const int f = T.first[ti.s], n = T.count[ti.s];
+  const int done = ctl->done;
+  if (!FINE && done) return;
+  const int f = seg_first(T, ti.s), n = seg_count(T, ti.s);
   const double rho = ctl->rho[(k - 1) & 1];
-  double xv[CPT], pv[CPT], rv[CPT], qv[CPT], dv[CPT];
+  double xv[C], pv[C], rv[C], qv[C], dv[C];
 #pragma unroll
-  for (int c = 0; c < CPT; ++c) {
-    int i = min(ti.lo + c * BLOCK + (int)threadIdx.x, ti.hi - 1);  // tiles are never empty
+  for (int c = 0; c < C; ++c) {
+    int i = min(ti.lo + c * NT + (int)threadIdx.x, ti.end - 1);  // tiles are never empty
     xv[c] = x[i];
     pv[c] = p_cur[i];
     rv[c] = r[i];
     qv[c] = q[i];
-    dv[c] = A.diag[i];
+    dv[c] = JAC ? A.diag[i] : 1.0;
   }
   double pq[1];
-  seg_thread_sum<1>(partA, T.ntile, f, n, pq);
-  __shared__ double lds[1][BLOCK / 64];
-  block_sum<1, BLOCK>(pq, lds);
+  seg_totals<1, NT, FINE>(partA, T.ntile, f, n, pq);
+  if (FINE && done) return;
   double alpha = rho / pq[0];
-  double v[2] = {0.0, 0.0};
+  double v[NV * C];
 #pragma unroll
-  for (int c = 0; c < CPT; ++c) {
-    int i = ti.lo + c * BLOCK + threadIdx.x;
+  for (int c = 0; c < C; ++c) {
+    int i = ti.lo + c * NT + (int)threadIdx.x;
+#pragma unroll
+    for (int e = 0; e < NV; ++e) v[e * C + c] = 0.0;
     if (i < ti.hi) {
-      x[i] = xv[c] + alpha * pv[c];
-      double ri = rv[c] - alpha * qv[c];
+      x[i] = __builtin_fma(alpha, pv[c], xv[c]);
+      double ri = __builtin_fma(-alpha, qv[c], rv[c]);
       r[i] = ri;
-      v[0] += ri * ri;
+      v[c] = ri * ri;
       if constexpr (JAC) {
         double zi = ri / dv[c];
         z[i] = zi;
-        v[1] += ri * zi;
+        v[C + c] = ri * zi;
       }
     }
   }
-  if constexpr (JAC) {
-    put_partial<2>(v, partB, T.ntile, ti.t);
-  } else {
-    double v1[1] = {v[0]};
-    put_partial<1>(v1, partB, T.ntile, ti.t);
+  put_partial<NV, NT, FINE>(v, partB, T.ntile, ti);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Jacobi-PCG of small segments, one block per segment and the whole solve in one launch: the direction
+// vector in LDS, x, r, z (q in z's place) and the diagonal in registers (thread tid holds cells
+// tid + c NT), uniform rows of three or four slots too.  An iteration is three block barriers and two
+// reductions instead of two kernels; its time is their latency, which few waves keep short (every wave
+// repeats the scalar work).  Per iteration, two kernels -> this: 968 and 2,048 prisms 6.9 -> 1.9 us, 3,872
+// prisms 6.9 -> 2.7, 3,072 tets 7.2 -> 3.0, 1,728 hexes (rows read from L2 each time) 8.2 -> 5.4.  Above
+// four tiles the rows do not fit one compute unit's registers; read from L2 they took 8 to 9 us at five
+// to eight tiles and 16 at eleven against 7.1, so those segments take the two kernels.
+// A launch makes at most `chunk` iterations; what a further launch needs is stored when it ends unconverged.
+// ---------------------------------------------------------------------------------------------
+constexpr int SEG_TILES = 4;     // most tiles of a segment
+constexpr int SEG_CHUNK = 2048;  // most iterations per launch: a launch stays under some 12 ms
+
+// NT threads with C cells each; W: slots of every row, kept in registers (0: rows of any length, read in every
+// iteration)
+template <int NT, int C, int W>
+__global__ __launch_bounds__(NT) void k_pcg_segment(SellView A, Tiles T, const double* __restrict__ b,
+                                                    double* __restrict__ x, double* __restrict__ rbuf,
+                                                    double* __restrict__ zbuf, double* __restrict__ pbuf, int chunk,
+                                                    PcgCtl* ctls) {
+  constexpr int NTILE = NT * C / TILE, WAVES = NT / 64;
+  constexpr bool REG = W > 0;
+  static_assert(NTILE <= 4, "the tiles' sums fill one wave");
+  __shared__ double sp[C * NT];
+  __shared__ double gs[2][64];
+  const int s = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  PcgCtl* ctl = ctls + s;
+  if (ctl->done) return;
+  const int f = seg_first(T, s), nt = seg_count(T, s);
+  const TileIdx t0 = tile_at(T, f), t1 = tile_at(T, f + nt - 1);
+  const int lo = t0.lo, n = t1.hi - lo;  // the segment's cells are consecutive
+  const double tol = ctl->tol;
+  const int maxit = ctl->maxit, k0 = ctl->next;
+  double xv[C], r[C], z[C], d[C];
+  double own[REG ? C : 1];  // this thread's entries of sp
+  // the totals of NV values per cell over the segment, in the order of the tiles' partials; v(k, c): value k
+  // of this thread's cell c, formed when its group of values is summed
+  auto totals = [&](auto&& v, auto& tot) {
+#pragma clang fp contract(off)
+    constexpr int NV = sizeof(tot) / sizeof(double);
+    wave_sums<NV * C>([&](int e) { return e % C * NT + tid < n ? v(e / C, e % C) : 0.0; },
+                      [&](int e, double sum) { gs[e / C][e % C * WAVES + wid] = sum; });
+    __syncthreads();
+    // every wave: the tiles' 16 groups in rows of lanes, then the order of a wave sum over the tiles
+    // (distance 1, then 2)
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      double t = row_sum(gs[k][lane]);
+      if (lane / TILE_WAVES >= nt) t = 0.0;
+      t = swap_add16(t, t);
+      tot[k] = wave_first(NTILE > 2 ? swap_add32(t, t) : t);
+    }
+  };
+  constexpr int WR = REG ? W : 1;
+  double av[REG ? C : 1][WR];
+  int jv[REG ? C : 1][WR];
+  if constexpr (REG) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      // cells past the segment: an empty row, so that no branch is needed for them
+      const bool in = c * NT + tid < n;
+      const int i = in ? lo + c * NT + tid : lo, base = (i >> 6) * (SLICE * W) + (i & (SLICE - 1));  // uniform rows
+#pragma unroll
+      for (int k = 0; k < W; ++k) {
+        const double a = A.val[base + k * SLICE];
+        const int j = A.off16[base + k * SLICE];
+        av[c][k] = in ? a : 0.0;
+        jv[c][k] = c * NT + tid + (in ? j : 0);
+      }
+    }
   }
+  // out(c, (A w)_c) for this thread's cells c, w the vector in sp
+  auto rows = [&](auto&& out) {
+    if constexpr (REG) {
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        double acc = d[c] * own[c];
+#pragma unroll
+        for (int k = 0; k < W; ++k) acc = __builtin_fma(av[c][k], sp[jv[c][k]], acc);
+        out(c, acc);
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+        if (const int me = c * NT + tid; me < n) {
+          const int i = lo + me;
+          SlotRange R = slots_of(A, i);
+          double acc = d[c] * sp[me];
+          walk_row<4>(row_len(A, i, R), [&](auto Wc, int q0) {
+            constexpr int N = decltype(Wc)::value;
+            double a[N];
+            int j[N];
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+              a[k] = A.val[R.base + (q0 + k) * SLICE];
+              j[k] = me + A.off16[R.base + (q0 + k) * SLICE];
+            }
+#pragma unroll
+            for (int k = 0; k < N; ++k) acc = __builtin_fma(a[k], sp[j[k]], acc);
+          });
+          out(c, acc);
+        }
+    }
+  };
+  double bn, rr, rho, rho_old;
+  auto rr_rz = [&](int k, int c) { return k == 0 ? r[c] * r[c] : r[c] * z[c]; };
+  double t1v[1], t2v[2];
+  auto mine = [&](int c) {
+    if constexpr (REG) return own[c];
+    else return sp[c * NT + tid];
+  };
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const bool in = c * NT + tid < n;
+    const int i = lo + c * NT + tid;
+    xv[c] = in ? x[i] : 0.0;
+    d[c] = in ? A.diag[i] : 1.0;
+    const double w0 = k0 == 0 ? xv[c] : in ? pbuf[i] : 0.0;
+    sp[c * NT + tid] = w0;
+    if constexpr (REG) own[c] = w0;
+    if (k0 > 0) {
+      r[c] = in ? rbuf[i] : 0.0;
+      z[c] = in ? zbuf[i] : 0.0;
+    }
+  }
+  if (k0 == 0) {
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < C; ++c) r[c] = z[c] = 0.0;  // z: b
+    rows([&](int c, double ax) {
+      const int e = c * NT + tid;
+      if (e < n) z[c] = b[lo + e];
+      r[c] = z[c] - ax;
+    });
+    totals([&](int k, int c) { return k == 0 ? z[c] * z[c] : r[c] * r[c]; }, t2v);
+    bn = sqrt(t2v[0]);
+    const double rn = sqrt(t2v[1]);
+    const bool zero_b = bn == 0.0, stop = zero_b || rn <= tol * bn;
+    if (tid == 0) {
+      ctl->bn = bn;
+      ctl->res = zero_b ? 0.0 : rn / bn;
+      ctl->done = stop ? 1 : 0;
+    }
+    if (zero_b)
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+        if (c * NT + tid < n) x[lo + c * NT + tid] = 0.0;
+    if (stop) return;
+    __syncthreads();  // gs is read, sp too
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      z[c] = r[c] / d[c];
+      sp[c * NT + tid] = 0.0;
+      if constexpr (REG) own[c] = 0.0;
+    }
+    totals(rr_rz, t2v);
+    rr = t2v[0];
+    rho = t2v[1];
+    rho_old = 0.0;
+  } else {
+    bn = ctl->bn;
+    rr = ctl->rr;
+    rho = ctl->rho[0];
+    rho_old = ctl->rho[1];
+  }
+  int k = k0 + 1;
+  bool done = false;
+  for (;; ++k) {
+    double beta = 0.0;
+    if (k >= 2) {
+      const double rn = sqrt(rr);
+      const bool conv = rn <= tol * bn;
+      if (conv || k - 1 >= maxit) {
+        done = true;
+        if (tid == 0) {
+          ctl->done = 1;
+          ctl->iters = k - 1;
+          ctl->res = rn / bn;
+          ctl->status = conv ? 0 : DIFVM_WARN_NOT_CONVERGED;
+        }
+        break;
+      }
+      beta = rho / rho_old;
+    } else if (maxit <= 0) {
+      done = true;
+      if (tid == 0) {
+        ctl->done = 1;
+        ctl->status = DIFVM_WARN_NOT_CONVERGED;
+      }
+      break;
+    }
+    if (k - k0 > chunk) break;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {  // read by others only after the barrier, and before the sums' own
+      const double p = cg_dir(z[c], beta, mine(c));
+      sp[c * NT + tid] = p;
+      if constexpr (REG) own[c] = p;
+    }
+    __syncthreads();
+    if constexpr (!REG)
+#pragma unroll
+      for (int c = 0; c < C; ++c) z[c] = 0.0;
+    rows([&](int c, double q) { z[c] = q; });  // z holds q until r is updated
+    totals([&](int, int c) { return mine(c) * z[c]; }, t1v);
+    const double alpha = rho / t1v[0];
+    __syncthreads();  // gs is read
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      xv[c] = __builtin_fma(alpha, mine(c), xv[c]);
+      r[c] = __builtin_fma(-alpha, z[c], r[c]);
+      z[c] = r[c] / d[c];
+    }
+    totals(rr_rz, t2v);
+    rr = t2v[0];
+    rho_old = rho;
+    rho = t2v[1];
+    // (the next iteration's barrier after the directions also separates these sums' reads from the
+    // next ones' writes)
+  }
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+    if (const int e = c * NT + tid; e < n) {
+      x[lo + e] = xv[c];
+      if (!done) {
+        rbuf[lo + e] = r[c];
+        zbuf[lo + e] = z[c];
+        pbuf[lo + e] = sp[e];
+      }
+    }
+  if (!done && tid == 0) {
+    ctl->next = k - 1;
+    ctl->rr = rr;
+    ctl->rho[0] = rho;
+    ctl->rho[1] = rho_old;
+  }
+}
+
+// most tiles of a segment
+static int max_seg_tiles(const difvm_mesh* m) {
+  int n = 0;
+  for (int32_t c : m->host.seg_tile_n) n = std::max(n, (int)c);
+  return n;
+}
+
+static void launch_pcg_segment(const difvm_mesh* m, int nt, const SellView& V, const Tiles& T, const double* b,
+                               double* x, KrylovWork* w, int chunk) {
+  const int G = m->d.nseg;
+  hipStream_t s = stream_of(m);
+#define DIFVM_SEG(NT, C, W) \
+  k_pcg_segment<NT, C, W><<<G, NT, 0, s>>>(V, T, b, x, w->r, w->z, w->p, chunk, w->pcg)
+  if (V.uw == 4) {
+    if (nt <= 2) DIFVM_SEG(256, 8, 4);
+    else DIFVM_SEG(512, 8, 4);
+  } else if (V.uw == 3) {
+    if (nt <= 2) DIFVM_SEG(256, 8, 3);
+    else DIFVM_SEG(512, 8, 3);
+  } else {
+    DIFVM_SEG(512, 8, 0);
+  }
+#undef DIFVM_SEG
+  DIFVM_HIP(hipGetLastError());
 }
 
 // per-segment control state set on the device (no host buffer, so the launch can be captured)
@@ -427,6 +759,10 @@ int pcg_spmv_grid(const difvm_mesh* m) {
   if (g <= 0 || g >= nt) return nt;
   return std::max(8, g & ~7);
 }
+
+// the same as launch_pcg_spmv takes it: 0 (a block per quarter of a tile) on meshes of few tiles, which no
+// persistent grid suits
+static int pcg_spmv_launch_grid(const difvm_mesh* m) { return fine_spans(m) ? 0 : pcg_spmv_grid(m); }
 
 SolveResult pcg_result(const difvm_mesh* m, const void* host_state, bool* complete) {
   const PcgCtl* hs = static_cast<const PcgCtl*>(host_state);
@@ -467,17 +803,44 @@ SolveResult pcg(difvm_mesh* m, SellMatrix A, const double* b, double* x, double 
   hipStream_t s = stream_of(m);
   SellView V = sview(m, A);
   Tiles T = tiles_of(m);
-  int G = T.ntile, nseg = m->d.nseg;
+  const int nseg = m->d.nseg;
   const size_t prof_mark = ctx_of(m).prof.pending.size();  // timed launches of this solve start here
   k_pcg_ctl_init<<<(nseg + 63) / 64, 64, 0, s>>>(w->pcg, nseg, tol, maxit);
-  const int GS = pcg_spmv_grid(m);
+  if (const int nt = max_seg_tiles(m); !amg && nt <= SEG_TILES && !ctx_of(m).prof.on) {
+    // one block per segment makes the whole solve (while the kernels of an iteration are being timed, it
+    // is made by them: the same results)
+    const int budget = qo ? std::min(qo->budget, maxit) : maxit;
+    const size_t bytes = pcg_state_bytes(m);
+    int made = 0;
+    do {
+      const int chunk = std::min(SEG_CHUNK, budget - made);
+      launch_pcg_segment(m, nt, V, T, b, x, w, chunk);
+      made += chunk;
+      if (qo) continue;
+      post_poll(m, w, w->pcg, bytes, 0);
+      const PcgCtl* hs = static_cast<const PcgCtl*>(wait_poll(w, 0));
+      bool all = true;
+      for (int g = 0; g < nseg; ++g) all = all && hs[g].done;
+      if (all) break;
+    } while (made < budget);
+    if (qo) {
+      copy_state(qo->state_out, w->pcg, bytes, s);
+      return SolveResult{};
+    }
+    SolveResult R = pcg_result(m, w->host_state[0], nullptr);
+    if (hint) *hint = R.iters[0];
+    return R;
+  }
+  const int GS = pcg_spmv_launch_grid(m);
+  const bool fine = fine_spans(m);
+  const int NP = n_spans(m), NTB = fine ? QUARTER : TILE;  // partials of one value; threads of the init kernels
   double* r = w->r;
   double* q = w->q;
   double* z = w->z;
   double* Pk[2] = {w->p, w->v};  // p_k at parity k & 1
   double* partA = w->partials;
-  double* partB = w->partials + 2 * (size_t)G;
-  double* part0 = w->partials + 4 * (size_t)G;
+  double* partB = w->partials + 2 * (size_t)NP;
+  double* part0 = w->partials + 4 * (size_t)NP;
   // z = M^-1 r: Jacobi inside the init / update kernels, or one V-cycle after them (which also stores
   // the r.z partials)
   // (the V-cycle's kernels skip their work once every segment has stopped; while some segment runs
@@ -485,18 +848,20 @@ SolveResult pcg(difvm_mesh* m, SellMatrix A, const double* b, double* x, double 
   auto precondition = [&](int kk) {
     if (!amg) return;
     ProfScope ps(m, "pcg_amg_vcycle", kk);
-    amg_vcycle(amg, A, r, z, partB + G, w->pcg);
+    amg_vcycle(amg, A, r, z, partB + NP, w->pcg);
   };
-  k_pcg_init1<<<G, BLOCK, 0, s>>>(V, T, b, x, r, part0);
-  if (amg) k_pcg_init2<false><<<G, BLOCK, 0, s>>>(V, T, x, r, z, Pk[0], part0, partB, w->pcg);
-  else k_pcg_init2<true><<<G, BLOCK, 0, s>>>(V, T, x, r, z, Pk[0], part0, partB, w->pcg);
+  (fine ? k_pcg_init1<true> : k_pcg_init1<false>)<<<NP, NTB, 0, s>>>(V, T, b, x, r, part0);
+  (amg ? fine ? k_pcg_init2<false, true> : k_pcg_init2<false, false>
+       : fine ? k_pcg_init2<true, true> : k_pcg_init2<true, false>)<<<NP, NTB, 0, s>>>(V, T, x, r, z, Pk[0], part0, partB,
+                                                                                        w->pcg);
   DIFVM_HIP(hipGetLastError());
   precondition(0);
   auto update = [&](int kk) {
     {
       ProfScope ps(m, "pcg_update_dot", kk);
-      if (amg) k_pcg_update<false><<<G, BLOCK, 0, s>>>(V, T, x, r, z, Pk[kk & 1], q, partA, partB, kk, w->pcg);
-      else k_pcg_update<true><<<G, BLOCK, 0, s>>>(V, T, x, r, z, Pk[kk & 1], q, partA, partB, kk, w->pcg);
+      auto kernel = fine ? (amg ? k_pcg_update<false, true> : k_pcg_update<true, true>)
+                         : (amg ? k_pcg_update<false, false> : k_pcg_update<true, false>);
+      kernel<<<NP, fine ? QUARTER : BLOCK, 0, s>>>(V, T, x, r, z, Pk[kk & 1], q, partA, partB, kk, w->pcg);
     }
     precondition(kk);
   };
@@ -569,10 +934,10 @@ SolveResult pcg(difvm_mesh* m, SellMatrix A, const double* b, double* x, double 
 // copy k whole; that tile's block of s_k adds alpha and of x_k adds omega and the outcome of the test on
 // s, fields that no block of the same launch reads.  Columns are scaled by 1/d once per solve, so the
 // products gather p and s alone (not d beside them, with a division for each neighbour).
-// Blocks have one thread per cell of a tile: the meshes between 50k and 300k cells give the chip 50 to
-// 300 blocks, which with four cells per thread left it to four waves per block with one row after another.
+// Blocks have one thread per cell, of a tile or of a quarter of one (see Span): four cells per thread left
+// each thread's rows one after another.
 // At 167,400 cells (3 components) an iteration's kernels took 73 us as eight launches of 256-thread
-// blocks, 40 us now; at 1,053,696 cells 160, 147 now (dir 19.6, v 28.2, s 12.2, t 33.3, x 39.9, totals 14).
+// blocks, 36 us now; at 1,053,696 cells 160, 129 now (dir 19.4, v 25.2, s 12.0, t 24.0, x 34.1, totals 14).
 // ---------------------------------------------------------------------------------------------
 
 // (B f)_i for NC interleaved components, B the off-diagonals in val plus DIAG f_i; padding and boundary
@@ -600,31 +965,28 @@ __device__ __forceinline__ void scaled_row(const SellView& A, const double* __re
 #pragma unroll
     for (int k = 0; k < N; ++k)
 #pragma unroll
-      for (int c = 0; c < NC; ++c) acc[c] += a[k] * fj[k][c];
+      for (int c = 0; c < NC; ++c) acc[c] = __builtin_fma(a[k], fj[k][c], acc[c]);
   });
 }
 
-// The NV totals of the segment for a kernel that needs them: summed here by every block, or (FIN) read
-// from the array that k_bi_totals filled.  Same sums, same bits.
-template <int NV, bool FIN>
+// The NV totals of the segment for a kernel that needs them: summed here by every block (FINE), or read from
+// the array that k_bi_totals filled.  Same sums, same bits.
+template <int NV, bool FINE>
 __device__ __forceinline__ void bi_totals(const double* __restrict__ part, const Tiles& T, int s, double (&tot)[NV]) {
-  if constexpr (FIN) {
+  if constexpr (FINE) {
+    seg_totals<NV, QUARTER, true>(part, T.ntile, seg_first(T, s), seg_count(T, s), tot);
+  } else {
 #pragma unroll
     for (int k = 0; k < NV; ++k) tot[k] = part[s * NV + k];
-  } else {
-    tile_seg_totals<NV>(part, T.ntile, seg_first(T, s), seg_count(T, s), tot);
   }
 }
-// Above this many tiles the totals get a kernel of their own, three per iteration of 4.7 us: at 1,029 tiles
-// every block summing 6 partials per tile by itself made the direction pass 32.2 us against 19.6 + 4.7,
-// while at 164 tiles it adds about 1 us to a pass that a launch more would cost 5.
-constexpr int BI_FIN_TILES = 384;
-
+// Above FINE_TILES tiles the totals get a kernel of their own, three per iteration of 4.7 us: at 1,029 tiles
+// every block summing 6 partials per tile by itself made the direction pass 32.2 us against 19.6 + 4.7.
 template <int NV>
 __global__ __launch_bounds__(TILE) void k_bi_totals(const double* __restrict__ part, Tiles T, double* __restrict__ out) {
   const int s = blockIdx.x;
   double tot[NV];
-  tile_seg_totals<NV>(part, T.ntile, seg_first(T, s), seg_count(T, s), tot);
+  seg_totals<NV, TILE, false>(part, T.ntile, seg_first(T, s), seg_count(T, s), tot);
   if (threadIdx.x == 0)
 #pragma unroll
     for (int k = 0; k < NV; ++k) out[s * NV + k] = tot[k];
@@ -632,12 +994,13 @@ __global__ __launch_bounds__(TILE) void k_bi_totals(const double* __restrict__ p
 
 // r = b - A x, rhat = r, partials b.b and r.r; val of A D^-1 (p and v start at zero: the first direction
 // pass writes p = r without reading them)
-template <int NC>
-__global__ __launch_bounds__(TILE) void k_bi_init(SellView A, Tiles T, const double* __restrict__ b,
+template <int NC, bool FINE>
+__global__ __launch_bounds__(FINE ? QUARTER : TILE) void k_bi_init(SellView A, Tiles T, const double* __restrict__ b,
                                                   const double* __restrict__ x, double* __restrict__ r,
                                                   double* __restrict__ rh, double* __restrict__ colscaled,
                                                   double* __restrict__ part) {
-  const TileIdx ti = tile_idx(T);
+  constexpr int NT = FINE ? QUARTER : TILE;
+  const Span ti = span_of<FINE>(T);
   const int i = ti.lo + (int)threadIdx.x;
   double acc[2 * NC], ri[NC];
 #pragma unroll
@@ -670,7 +1033,7 @@ __global__ __launch_bounds__(TILE) void k_bi_init(SellView A, Tiles T, const dou
       for (int k = 0; k < N; ++k) {
         colscaled[R.base + (k0 + k) * SLICE] = a[k] / dj[k];
 #pragma unroll
-        for (int c = 0; c < NC; ++c) ax[c] += a[k] * xj[k][c];
+        for (int c = 0; c < NC; ++c) ax[c] = __builtin_fma(a[k], xj[k][c], ax[c]);
       }
     });
 #pragma unroll
@@ -683,11 +1046,11 @@ __global__ __launch_bounds__(TILE) void k_bi_init(SellView A, Tiles T, const dou
   if constexpr (NC == 1) {
     if (i < ti.hi) r[i] = rh[i] = ri[0];
   } else {
-    __shared__ double lds[NC * TILE];
+    __shared__ double lds[NC * NT];
     store_rows<NC>(r, ti.lo, ti.hi, ri, lds);
     store_rows<NC>(rh, ti.lo, ti.hi, ri, lds);
   }
-  put_tile_partial<2 * NC>(acc, part, T.ntile, ti.t);
+  put_partial<2 * NC, NT, FINE>(acc, part, T.ntile, ti);
 }
 
 // component c's value of an array held in registers (no run-time index, which would move it to memory)
@@ -725,15 +1088,16 @@ __device__ __forceinline__ void copy_systems(BiState& d, const BiState& s) {
 
 // iteration it >= 1: stopping test of iterate it - 1 (it = 1: of the initial guess), then the direction.
 // One thread per value of the tile's rows (consecutive lanes, consecutive doubles), NC rounds.
-template <int NC, bool FIN>
-__global__ __launch_bounds__(TILE, FIN ? 8 : 4) void k_bi_dir(Tiles T, int it, const double* __restrict__ r, double* __restrict__ p,
+template <int NC, bool FINE>
+__global__ __launch_bounds__(FINE ? QUARTER : TILE, FINE ? 1 : 8) void k_bi_dir(Tiles T, int it, const double* __restrict__ r, double* __restrict__ p,
                                                  const double* __restrict__ v, double* __restrict__ x,
                                                  const double* __restrict__ part, BiState* sts, int nseg) {
-  const TileIdx ti = tile_idx(T);
+  constexpr int NT = FINE ? QUARTER : TILE;
+  const Span ti = span_of<FINE>(T);
   const BiState* prev = sts + (size_t)((it - 1) & 1) * nseg + ti.s;
   BiState S;
   copy_systems<NC>(S, *prev);
-  const bool lead = ti.t == seg_first(T, ti.s) && threadIdx.x == 0;
+  const bool lead = ti.t == seg_first(T, ti.s) && ti.j == 0 && threadIdx.x == 0;
   BiState* cur = sts + (size_t)(it & 1) * nseg + ti.s;
   const int e0 = NC * ti.lo, e1 = NC * ti.hi;
   if (it > 1 && !S.any) {  // stopped before: the state moves on with the parity
@@ -743,7 +1107,7 @@ __global__ __launch_bounds__(TILE, FIN ? 8 : 4) void k_bi_dir(Tiles T, int it, c
   double rv[NC], pv[NC], vv[NC];  // in flight with the partials
 #pragma unroll
   for (int q = 0; q < NC; ++q) {
-    const int e = min(e0 + q * TILE + (int)threadIdx.x, e1 - 1);
+    const int e = min(e0 + q * NT + (int)threadIdx.x, NC * ti.end - 1);
     rv[q] = r[e];
     pv[q] = vv[q] = 0.0;
     if (it > 1) {
@@ -752,7 +1116,7 @@ __global__ __launch_bounds__(TILE, FIN ? 8 : 4) void k_bi_dir(Tiles T, int it, c
     }
   }
   double tot[2 * NC];
-  bi_totals<2 * NC, FIN>(part, T, ti.s, tot);
+  bi_totals<2 * NC, FINE>(part, T, ti.s, tot);
   double beta[NC], omega[NC];
   bool act[NC], zero[NC];
   S.any = 0;
@@ -811,22 +1175,24 @@ __global__ __launch_bounds__(TILE, FIN ? 8 : 4) void k_bi_dir(Tiles T, int it, c
   if (lead) copy_systems<NC>(*cur, S);
 #pragma unroll
   for (int q = 0; q < NC; ++q) {
-    const int e = e0 + q * TILE + (int)threadIdx.x;
+    const int e = e0 + q * NT + (int)threadIdx.x;
     if (e >= e1) continue;
     const int c = e % NC;
     if (pick(zero, c)) x[e] = 0.0;
     if (!pick(act, c)) continue;
-    p[e] = it == 1 ? rv[q] : rv[q] + pick(beta, c) * (pv[q] - pick(omega, c) * vv[q]);
+    p[e] = it == 1 ? rv[q]
+                   : __builtin_fma(pick(beta, c), __builtin_fma(-pick(omega, c), vv[q], pv[q]), rv[q]);
   }
 }
 
 // v = A D^-1 p; partial rhat . v
-template <int NC>
-__global__ __launch_bounds__(TILE) void k_bi_v(SellView A, const double* __restrict__ colscaled, Tiles T, int it,
+template <int NC, bool FINE>
+__global__ __launch_bounds__(FINE ? QUARTER : TILE) void k_bi_v(SellView A, const double* __restrict__ colscaled, Tiles T, int it,
                                                const double* __restrict__ p, double* __restrict__ v,
                                                const double* __restrict__ rh, double* __restrict__ part,
                                                const BiState* sts, int nseg) {
-  const TileIdx ti = tile_idx(T);
+  constexpr int NT = FINE ? QUARTER : TILE;
+  const Span ti = span_of<FINE>(T);
   const BiState* st = sts + (size_t)(it & 1) * nseg + ti.s;
   if (!st->any) return;
   bool act[NC];
@@ -850,55 +1216,57 @@ __global__ __launch_bounds__(TILE) void k_bi_v(SellView A, const double* __restr
   if constexpr (NC == 1) {
     if (i < ti.hi) v[i] = ay[0];
   } else {
-    __shared__ double lds[NC * TILE];
+    __shared__ double lds[NC * NT];
     store_rows_if<NC>(v, ti.lo, ti.hi, ay, act, lds);
   }
-  put_tile_partial<NC>(acc, part, T.ntile, ti.t);
+  put_partial<NC, NT, FINE>(acc, part, T.ntile, ti);
 }
 
 // alpha, s = r - alpha v, one thread per value of the tile's rows (as k_bi_dir)
-template <int NC, bool FIN>
-__global__ __launch_bounds__(TILE, FIN ? 8 : 4) void k_bi_s(Tiles T, int it, const double* __restrict__ r,
+template <int NC, bool FINE>
+__global__ __launch_bounds__(FINE ? QUARTER : TILE, FINE ? 1 : 8) void k_bi_s(Tiles T, int it, const double* __restrict__ r,
                                                const double* __restrict__ v, double* __restrict__ s,
                                                const double* __restrict__ part, BiState* sts, int nseg) {
-  const TileIdx ti = tile_idx(T);
+  constexpr int NT = FINE ? QUARTER : TILE;
+  const Span ti = span_of<FINE>(T);
   BiState* st = sts + (size_t)(it & 1) * nseg + ti.s;
   if (!st->any) return;
   const int e0 = NC * ti.lo, e1 = NC * ti.hi;
   double rv[NC], vv[NC];  // in flight with the partials
 #pragma unroll
   for (int q = 0; q < NC; ++q) {
-    const int e = min(e0 + q * TILE + (int)threadIdx.x, e1 - 1);
+    const int e = min(e0 + q * NT + (int)threadIdx.x, NC * ti.end - 1);
     rv[q] = r[e];
     vv[q] = v[e];
   }
   double tot[NC], alpha[NC];
   bool act[NC];
-  bi_totals<NC, FIN>(part, T, ti.s, tot);
+  bi_totals<NC, FINE>(part, T, ti.s, tot);
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
     act[c] = st->active[c] != 0;
     alpha[c] = st->rho[c] / tot[c];
   }
-  if (ti.t == seg_first(T, ti.s) && threadIdx.x == 0)
+  if (ti.t == seg_first(T, ti.s) && ti.j == 0 && threadIdx.x == 0)
 #pragma unroll
     for (int c = 0; c < NC; ++c)
       if (act[c]) st->alpha[c] = alpha[c];
 #pragma unroll
   for (int q = 0; q < NC; ++q) {
-    const int e = e0 + q * TILE + (int)threadIdx.x;
+    const int e = e0 + q * NT + (int)threadIdx.x;
     if (e >= e1) continue;
     const int c = e % NC;
-    if (pick(act, c)) s[e] = rv[q] - pick(alpha, c) * vv[q];
+    if (pick(act, c)) s[e] = __builtin_fma(-pick(alpha, c), vv[q], rv[q]);
   }
 }
 
 // t = A D^-1 s (s gathered from the pass above); partials t.s, t.t, s.s
-template <int NC>
-__global__ __launch_bounds__(TILE) void k_bi_t(SellView A, const double* __restrict__ colscaled, Tiles T, int it,
+template <int NC, bool FINE>
+__global__ __launch_bounds__(FINE ? QUARTER : TILE) void k_bi_t(SellView A, const double* __restrict__ colscaled, Tiles T, int it,
                                                const double* __restrict__ s, double* __restrict__ t,
                                                double* __restrict__ part, const BiState* sts, int nseg) {
-  const TileIdx ti = tile_idx(T);
+  constexpr int NT = FINE ? QUARTER : TILE;
+  const Span ti = span_of<FINE>(T);
   const BiState* st = sts + (size_t)(it & 1) * nseg + ti.s;
   if (!st->any) return;
   bool act[NC];
@@ -924,24 +1292,25 @@ __global__ __launch_bounds__(TILE) void k_bi_t(SellView A, const double* __restr
   if constexpr (NC == 1) {
     if (i < ti.hi) t[i] = az[0];
   } else {
-    __shared__ double lds[NC * TILE];
+    __shared__ double lds[NC * NT];
     store_rows_if<NC>(t, ti.lo, ti.hi, az, act, lds);
   }
-  put_tile_partial<3 * NC>(acc, part, T.ntile, ti.t);
+  put_partial<3 * NC, NT, FINE>(acc, part, T.ntile, ti);
 }
 
 // the test on s (the iteration ends with x += alpha D^-1 p if it passes) and omega;
 // x += alpha D^-1 p (+ omega D^-1 s); r = s - omega t; partials r.r, rhat.r
-template <int NC, bool FIN>
-__global__ __launch_bounds__(TILE, FIN ? 8 : 4) void k_bi_x(SellView A, Tiles T, int it, double* __restrict__ x,
+template <int NC, bool FINE>
+__global__ __launch_bounds__(FINE ? QUARTER : TILE, FINE ? 1 : 8) void k_bi_x(SellView A, Tiles T, int it, double* __restrict__ x,
                                                double* __restrict__ r, const double* __restrict__ rh,
                                                const double* __restrict__ p, const double* __restrict__ s,
                                                const double* __restrict__ t, const double* __restrict__ part_in,
                                                double* __restrict__ part, BiState* sts, int nseg) {
-  const TileIdx ti = tile_idx(T);
+  constexpr int NT = FINE ? QUARTER : TILE;
+  const Span ti = span_of<FINE>(T);
   BiState* st = sts + (size_t)(it & 1) * nseg + ti.s;
   if (!st->any) return;
-  const int i = ti.lo + (int)threadIdx.x, ii = min(i, ti.hi - 1);
+  const int i = ti.lo + (int)threadIdx.x, ii = min(i, ti.end - 1);
   double pv[NC], sv[NC], tv[NC], xv[NC], hv[NC];  // in flight with the partials
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
@@ -954,8 +1323,8 @@ __global__ __launch_bounds__(TILE, FIN ? 8 : 4) void k_bi_x(SellView A, Tiles T,
   }
   const double di = A.diag[ii];
   double tot[3 * NC];
-  bi_totals<3 * NC, FIN>(part_in, T, ti.s, tot);
-  const bool lead = ti.t == seg_first(T, ti.s) && threadIdx.x == 0;
+  bi_totals<3 * NC, FINE>(part_in, T, ti.s, tot);
+  const bool lead = ti.t == seg_first(T, ti.s) && ti.j == 0 && threadIdx.x == 0;
   bool keep_x[NC], keep_r[NC];
   double acc[2 * NC], rv[NC];
 #pragma unroll
@@ -971,8 +1340,8 @@ __global__ __launch_bounds__(TILE, FIN ? 8 : 4) void k_bi_x(SellView A, Tiles T,
       st->omega[c] = omega;
     }
     const double y = pv[c] / di, z = sv[c] / di;
-    xv[c] += keep_r[c] ? alpha * y + omega * z : alpha * y;
-    rv[c] = sv[c] - omega * tv[c];
+    xv[c] = __builtin_fma(alpha, y, keep_r[c] ? __builtin_fma(omega, z, xv[c]) : xv[c]);
+    rv[c] = __builtin_fma(-omega, tv[c], sv[c]);
     const bool in = keep_r[c] && i < ti.hi;
     acc[c] = in ? rv[c] * rv[c] : 0.0;
     acc[NC + c] = in ? hv[c] * rv[c] : 0.0;
@@ -981,11 +1350,11 @@ __global__ __launch_bounds__(TILE, FIN ? 8 : 4) void k_bi_x(SellView A, Tiles T,
     if (i < ti.hi && keep_x[0]) x[i] = xv[0];
     if (i < ti.hi && keep_r[0]) r[i] = rv[0];
   } else {
-    __shared__ double lds[NC * TILE];
+    __shared__ double lds[NC * NT];
     store_rows_if<NC>(x, ti.lo, ti.hi, xv, keep_x, lds);
     store_rows_if<NC>(r, ti.lo, ti.hi, rv, keep_r, lds);
   }
-  put_tile_partial<2 * NC>(acc, part, T.ntile, ti.t);
+  put_partial<2 * NC, NT, FINE>(acc, part, T.ntile, ti);
 }
 
 __global__ void k_bi_state_init(BiState* sts, int nseg, double tol, int maxit) {
@@ -1023,36 +1392,37 @@ SolveResult bicgstab_result(const difvm_mesh* m, int ncomp, const void* host_sta
   return R;
 }
 
-template <int NC, bool FIN>
+template <int NC, bool FINE>
 static SolveResult bicgstab_nc(difvm_mesh* m, SellMatrix A, const double* b, double* x, double tol, int maxit,
                                const QueueOnly* qo, int* hint) {
   KrylovWork* w = make_work(m);
   hipStream_t s = stream_of(m);
   SellView V = sview(m, A);
   Tiles T = tiles_of(m);
-  int G = T.ntile, nseg = m->d.nseg;
+  constexpr int NT = FINE ? QUARTER : TILE;
+  const int G = n_spans(m), nseg = m->d.nseg;
   k_bi_state_init<<<(nseg + 63) / 64, 64, 0, s>>>(w->bi, nseg, tol, maxit);
   double* partX = w->partials;
   double* partV = partX + 2 * NC * (size_t)G;
   double* partT = partV + NC * (size_t)G;
   double* tots = partX + 18 * (size_t)G;
   auto dir = [&](int it) {
-    if (FIN) k_bi_totals<2 * NC><<<nseg, TILE, 0, s>>>(partX, T, tots);
-    k_bi_dir<NC, FIN><<<G, TILE, 0, s>>>(T, it, w->r, w->p, w->v, x, FIN ? tots : partX, w->bi, nseg);
+    if (!FINE) k_bi_totals<2 * NC><<<nseg, TILE, 0, s>>>(partX, T, tots);
+    k_bi_dir<NC, FINE><<<G, NT, 0, s>>>(T, it, w->r, w->p, w->v, x, FINE ? partX : tots, w->bi, nseg);
   };
-  k_bi_init<NC><<<G, TILE, 0, s>>>(V, T, b, x, w->r, w->rh, w->colscaled, partX);
+  k_bi_init<NC, FINE><<<G, NT, 0, s>>>(V, T, b, x, w->r, w->rh, w->colscaled, partX);
   dir(1);
   DIFVM_HIP(hipGetLastError());
   int done = 0;  // iterations queued
   auto queue_iters = [&](int nb) {
     for (int n = 0; n < nb; ++n) {
       const int it = ++done;
-      k_bi_v<NC><<<G, TILE, 0, s>>>(V, w->colscaled, T, it, w->p, w->v, w->rh, partV, w->bi, nseg);
-      if (FIN) k_bi_totals<NC><<<nseg, TILE, 0, s>>>(partV, T, tots);
-      k_bi_s<NC, FIN><<<G, TILE, 0, s>>>(T, it, w->r, w->v, w->s, FIN ? tots : partV, w->bi, nseg);
-      k_bi_t<NC><<<G, TILE, 0, s>>>(V, w->colscaled, T, it, w->s, w->t, partT, w->bi, nseg);
-      if (FIN) k_bi_totals<3 * NC><<<nseg, TILE, 0, s>>>(partT, T, tots);
-      k_bi_x<NC, FIN><<<G, TILE, 0, s>>>(V, T, it, x, w->r, w->rh, w->p, w->s, w->t, FIN ? tots : partT, partX, w->bi,
+      k_bi_v<NC, FINE><<<G, NT, 0, s>>>(V, w->colscaled, T, it, w->p, w->v, w->rh, partV, w->bi, nseg);
+      if (!FINE) k_bi_totals<NC><<<nseg, TILE, 0, s>>>(partV, T, tots);
+      k_bi_s<NC, FINE><<<G, NT, 0, s>>>(T, it, w->r, w->v, w->s, FINE ? partV : tots, w->bi, nseg);
+      k_bi_t<NC, FINE><<<G, NT, 0, s>>>(V, w->colscaled, T, it, w->s, w->t, partT, w->bi, nseg);
+      if (!FINE) k_bi_totals<3 * NC><<<nseg, TILE, 0, s>>>(partT, T, tots);
+      k_bi_x<NC, FINE><<<G, NT, 0, s>>>(V, T, it, x, w->r, w->rh, w->p, w->s, w->t, FINE ? partT : tots, partX, w->bi,
                                          nseg);
       dir(it + 1);
     }
@@ -1089,9 +1459,9 @@ static SolveResult bicgstab_nc(difvm_mesh* m, SellMatrix A, const double* b, dou
 
 SolveResult bicgstab(difvm_mesh* m, int ncomp, SellMatrix A, const double* b, double* x, double tol, int maxit,
                      const QueueOnly* qo, int* hint) {
-  const bool fin = m->d.ntile > BI_FIN_TILES;
-  if (ncomp == 1) return (fin ? bicgstab_nc<1, true> : bicgstab_nc<1, false>)(m, A, b, x, tol, maxit, qo, hint);
-  return (fin ? bicgstab_nc<3, true> : bicgstab_nc<3, false>)(m, A, b, x, tol, maxit, qo, hint);
+  const bool fine = fine_spans(m);
+  if (ncomp == 1) return (fine ? bicgstab_nc<1, true> : bicgstab_nc<1, false>)(m, A, b, x, tol, maxit, qo, hint);
+  return (fine ? bicgstab_nc<3, true> : bicgstab_nc<3, false>)(m, A, b, x, tol, maxit, qo, hint);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1133,17 +1503,17 @@ double time_pcg_spmv(difvm_mesh* m, int grid, int reps, hipEvent_t e0, hipEvent_
     fill(diag, d.nc, 4.0);
     fill(w->z, d.nc, 1.0);
     fill(w->p, d.nc, 1.0);
-    fill(w->partials, (size_t)8 * w->ntile, 1.0);
+    fill(w->partials, (size_t)8 * n_spans(m), 1.0);
     k_tune_ctl<<<(d.nseg + 63) / 64, 64, 0, s>>>(ctl, d.nseg);
     DIFVM_HIP(hipGetLastError());
     int old = m->tune[DIFVM_TUNE_PCG_GRID];
     m->tune[DIFVM_TUNE_PCG_GRID] = grid;
-    int GS = pcg_spmv_grid(m);
+    int GS = pcg_spmv_launch_grid(m);
     m->tune[DIFVM_TUNE_PCG_GRID] = old;
     SellView V = sview(m, SellMatrix{diag, val});  // the same column form the solves read
     Tiles T = tiles_of(m);
     double* partA = w->partials;
-    double* partB = w->partials + 2 * (size_t)T.ntile;
+    double* partB = w->partials + 2 * (size_t)n_spans(m);
     launch_pcg_spmv(GS, s, V, T, 2, w->z, w->p, w->v, w->q, partB, partA, ctl);
     DIFVM_HIP(hipEventRecord(e0, s));
     for (int r = 0; r < reps; ++r)

@@ -86,168 +86,150 @@ __device__ __forceinline__ TileIdx tile_at(const Tiles& T, int t) {
   if (T.one_nc > 0) return {t, 0, t * TILE, min(t * TILE + TILE, T.one_nc)};
   return {t, T.seg[t], T.lo[t], T.hi[t]};
 }
-__device__ __forceinline__ TileIdx tile_idx(const Tiles& T) { return tile_at(T, xcd_tile(blockIdx.x, gridDim.x)); }
+// The cells of a block: a tile, or on meshes of at most FINE_TILES tiles a quarter of one.  A block of a
+// whole tile gathers its rows' neighbours through one compute unit, which takes about one cache line a
+// cycle: 8,192 of them (two vectors, four slots) are 3.4 us, and a mesh of 100 tiles leaves half the chip
+// idle meanwhile.  Quarters cost the kernels that sum the partials four loads per tile instead of one.
+constexpr int FINE_TILES = 384;
+constexpr int QUARTER = TILE / 4;
+struct Span {
+  int t, j, s, lo, hi, end;  // tile, quarter (0), segment, cells [lo, hi) (hi <= lo: none), end of the tile
+};
+template <bool FINE>
+__device__ __forceinline__ Span span_at(const Tiles& T, int b) {
+  const int t = FINE ? b >> 2 : b, j = FINE ? b & 3 : 0;
+  const TileIdx ti = tile_at(T, t);
+  if constexpr (FINE) return {t, j, ti.s, ti.lo + j * QUARTER, min(ti.hi, ti.lo + (j + 1) * QUARTER), ti.hi};
+  else return {t, 0, ti.s, ti.lo, ti.hi, ti.hi};
+}
+template <bool FINE>
+__device__ __forceinline__ Span span_of(const Tiles& T) {
+  return span_at<FINE>(T, xcd_tile(blockIdx.x, gridDim.x));
+}
+inline bool fine_spans(const difvm_mesh* m) { return m->d.ntile <= FINE_TILES; }
+inline int n_spans(const difvm_mesh* m) { return fine_spans(m) ? 4 * m->d.ntile : m->d.ntile; }
 __device__ __forceinline__ int seg_first(const Tiles& T, int s) { return T.one_nc > 0 ? 0 : T.first[s]; }
 __device__ __forceinline__ int seg_count(const Tiles& T, int s) { return T.one_nc > 0 ? T.ntile : T.count[s]; }
 
-// fixed-order sum of a segment's tile partials (NV arrays, value-major over all tiles, the segment's
-// n tiles from tile f) by a block of NT threads; every thread ends with the totals (sum_seg).  Each
-// thread adds the partials q = tid, tid + NT, ... in that order (seg_thread_sum); the loads of four
-// such steps (all NV arrays) are issued together, past the end at the clamped index n - 1 and not
-// added, so the chain is one load latency per 4 NT tiles.  A block reduction then gives the totals.
-template <int NV, int NT = BLOCK>
-__device__ __forceinline__ void seg_thread_sum(const double* __restrict__ part, int ntile, int f, int n,
-                                               double (&out)[NV]) {
-  constexpr int UN = 4;
-#pragma unroll
-  for (int k = 0; k < NV; ++k) out[k] = 0.0;
-  for (int q = threadIdx.x; q < n; q += UN * NT) {
-    double v[UN][NV];
-#pragma unroll
-    for (int u = 0; u < UN; ++u) {
-      int at = f + min(q + u * NT, n - 1);
-#pragma unroll
-      for (int k = 0; k < NV; ++k) v[u][k] = part[(size_t)k * ntile + at];
-    }
-#pragma unroll
-    for (int u = 0; u < UN; ++u)
-      if (q + u * NT < n)
-#pragma unroll
-        for (int k = 0; k < NV; ++k) out[k] += v[u][k];
-  }
-}
-template <int NV, int NT = BLOCK>
-__device__ __forceinline__ void sum_seg(const double* __restrict__ part, const Tiles& T, int s, double (&out)[NV]) {
-  __shared__ double lds[NV][NT / 64];
-  seg_thread_sum<NV, NT>(part, T.ntile, T.first[s], T.count[s], out);
-  block_sum<NV, NT>(out, lds);
-}
-
-template <int NV, int NT = BLOCK>
-__device__ __forceinline__ void put_partial(double (&v)[NV], double* __restrict__ part, int ntile, int t) {
-  __shared__ double lds[NV][NT / 64];
-  block_sum<NV, NT>(v, lds);
-  if (threadIdx.x == 0)
-#pragma unroll
-    for (int k = 0; k < NV; ++k) part[(size_t)k * ntile + t] = v[k];
-}
-
 // ---------------------------------------------------------------------------------------------
-// Reductions of a block of TILE threads with one cell each.  Summing several values over a wave by one
-// butterfly per value costs 6 exchanges each, all through the LDS pipe; halving the set of values at each
-// of the first steps instead (a lane keeps the half its lane bit names and sends the other) leaves one
-// value per group of lanes after log2 P steps: 10 exchanges for 8 values instead of 48.
+// Reductions.  Their order is the same whatever the shape of the launch: a tile's sum is the tree (row_sum)
+// over its 16 groups of 64 consecutive cells, each the sum of the group's wave; a segment's total adds its
+// tiles q in four chains (q / 64) mod 4, lane q mod 64 of each adding its own tiles in order, then a wave
+// sum per chain and the four in order.  So a kernel may give a block a tile or a quarter of one, a thread
+// one cell or several, or hold a whole segment in one block, with the same bits.
+//
+// Several values are summed over a wave by halving the set at each of the first steps (a lane keeps the
+// half its lane bit names and gives away the other), which leaves one value per group of lanes after
+// log2 P steps: 10 exchanges for 8 values instead of 48, each value with wave_sum's pairing and so its bits.
 // ---------------------------------------------------------------------------------------------
 constexpr int TILE_WAVES = TILE / 64;
 
-// v[0..P) summed over the wave (P a power of two): value k ends in v[0] of the lanes k 64/P .. (k+1) 64/P - 1
+// v[0..P) summed over the wave (P = 1, 2, 4, 8): value k ends in v[0] of the lanes k 64/P .. (k+1) 64/P - 1
 template <int P>
 __device__ __forceinline__ void wave_sum_split(double (&v)[P]) {
-  const int lane = threadIdx.x & 63;
-  int off = 32;
+#pragma clang fp contract(off)
+  static_assert(P <= 8, "at most eight values");
+  constexpr int M32 = P > 1 ? P / 2 : 1, M16 = P > 2 ? P / 4 : 1;
 #pragma unroll
-  for (int m = P / 2; m >= 1; m /= 2, off /= 2) {
-    const bool up = lane & off;
+  for (int k = 0; k < M32; ++k) v[k] = swap_add32(v[k], v[P > 1 ? k + M32 : k]);
 #pragma unroll
-    for (int k = 0; k < m; ++k) {
-      const double mine = up ? v[k + m] : v[k], send = up ? v[k] : v[k + m];
-      v[k] = mine + __shfl_xor(send, off, 64);
-    }
+  for (int k = 0; k < M16; ++k) v[k] = swap_add16(v[k], v[P > 2 ? k + M16 : k]);
+  if constexpr (P == 8) {
+    const bool up = threadIdx.x & 8;
+    const double mine = up ? v[1] : v[0], send = up ? v[0] : v[1];
+    v[0] = mine + dpp_mov<DPP_ROR8>(send);
+  } else {
+    v[0] += dpp_mov<DPP_ROR8>(v[0]);
   }
-#pragma unroll
-  for (; off > 0; off /= 2) v[0] += __shfl_xor(v[0], off, 64);
+  v[0] = lanes_sum<8>(v[0]);
 }
 
-// the tile's sums of NV values per thread into part[k ntile + t]: wave sums, then the waves in order
-template <int NV>
-__device__ __forceinline__ void put_tile_partial(const double (&v)[NV], double* __restrict__ part, int ntile, int t) {
-  __shared__ double lds[NV][TILE_WAVES + 1];
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  constexpr int P = NV > 4 ? 8 : NV > 2 ? 4 : NV;  // values of the first group (padded with zeros)
-  static_assert(NV <= 9, "two groups: up to 8 values, then one");
+// wave sums of v(0..M-1) stored as out(k, sum); groups of 8 values, then what is left
+template <int M, int K0 = 0, class V, class F>
+__device__ __forceinline__ void wave_sums(V&& v, F&& out) {
+  constexpr int N = M - K0, P = N > 4 ? 8 : N > 2 ? 4 : N;
+  const int lane = threadIdx.x & 63;
   double a[P];
 #pragma unroll
-  for (int k = 0; k < P; ++k) a[k] = k < NV ? v[k] : 0.0;
+  for (int k = 0; k < P; ++k) a[k] = k < N ? v(K0 + (k < N ? k : 0)) : 0.0;
   wave_sum_split<P>(a);
-  if (const int k = lane / (64 / P); lane % (64 / P) == 0 && k < NV) lds[k][wid] = a[0];
-  if constexpr (NV > P) {
-    double b[1] = {v[NV - 1]};
-    wave_sum_split<1>(b);
-    if (lane == 0) lds[NV - 1][wid] = b[0];
+  if (const int k = lane / (64 / P); lane % (64 / P) == 0 && k < N) out(K0 + k, a[0]);
+  if constexpr (N > P) wave_sums<M, K0 + P>(v, out);
+}
+
+// the sums of NV values per cell over a block's span, by a block of NT threads with C cells each (thread tid
+// holds cells tid + c NT of the span, value k of cell c in v[k C + c]): a tile's into part[k ntile + t], a
+// quarter's (FINE, C = 1) into part[k 4 ntile + 4 t + j]
+template <int NV, int NT, bool FINE>
+__device__ __forceinline__ void put_partial(const double (&v)[NV * (FINE ? 1 : TILE / NT)], double* __restrict__ part,
+                                            int ntile, const Span& sp) {
+  constexpr int C = FINE ? 1 : TILE / NT, GROUPS = NT * C / 64, LANES = (NV * GROUPS + 63) / 64 * 64;
+  static_assert(LANES <= NT && (FINE ? GROUPS == 4 : GROUPS == 16), "one lane per group sum");
+  __shared__ double lds[LANES];
+  const int wid = threadIdx.x >> 6;
+  __syncthreads();  // a previous tile's sums are out of lds
+  wave_sums<NV * C>([&](int e) { return v[e]; },
+                    [&](int e, double sum) { lds[e / C * GROUPS + e % C * (NT / 64) + wid] = sum; });
+  __syncthreads();
+  if (threadIdx.x < LANES) {  // whole waves; lanes past the values sum what the array holds, unused
+    const double s = FINE ? quad_sum(lds[threadIdx.x]) : row_sum(lds[threadIdx.x]);
+    const int k = threadIdx.x / GROUPS;
+    if (threadIdx.x % GROUPS == 0 && k < NV)
+      part[FINE ? (size_t)k * 4 * ntile + 4 * sp.t + sp.j : (size_t)k * ntile + sp.t] = s;
+  }
+}
+
+// the segment's totals of NV partials (n tiles from tile f, by tile or by quarter) for every thread of a
+// block of NT threads; waves 4g .. 4g+3 take the four chains of the values g, g + NT / 256, ...; several
+// loads of a lane in flight
+template <int NV, int NT, bool FINE>
+__device__ __forceinline__ void seg_totals(const double* __restrict__ part, int ntile, int f, int n,
+                                           double (&tot)[NV]) {
+#pragma clang fp contract(off)
+  constexpr int G = NT / 256, K = (NV + G - 1) / G, UN = K > 2 ? 1 : K > 1 ? 2 : 4;
+  __shared__ double sh[NV][4];
+  const int lane = threadIdx.x & 63, chain = (threadIdx.x >> 6) & 3, g = threadIdx.x >> 8;
+  double s[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) s[k] = 0.0;
+  for (int q = 64 * chain + lane; q < n; q += UN * 256) {
+    double w[UN][K];
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+#pragma unroll
+      for (int k = 0; k < K; ++k) {  // past the end (tiles or values) the last one, not added
+        const size_t at = (size_t)min(g + k * G, NV - 1) * ntile + f + min(q + u * 256, n - 1);
+        if constexpr (FINE) {
+          const double2 *h = reinterpret_cast<const double2*>(part) + 2 * at, a = h[0], b = h[1];
+          w[u][k] = (a.x + a.y) + (b.x + b.y);
+        } else {
+          w[u][k] = part[at];
+        }
+      }
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        if (q + u * 256 < n) s[k] += w[u][k];
+  }
+  __syncthreads();  // a previous call's totals have been read
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    s[k] = wave_sum(s[k]);
+    if (lane == 0 && g + k * G < NV) sh[g + k * G][chain] = s[k];
   }
   __syncthreads();
-  if (threadIdx.x < NV) {
-    double s = 0.0;
 #pragma unroll
-    for (int q = 0; q < TILE_WAVES; ++q) s += lds[threadIdx.x][q];
-    part[(size_t)threadIdx.x * ntile + t] = s;
-  }
+  for (int k = 0; k < NV; ++k) tot[k] = ((sh[k][0] + sh[k][1]) + sh[k][2]) + sh[k][3];
 }
-
-// the segment's totals of NV tile partials (n tiles from tile f) for every thread of a block of TILE
-// threads, in a fixed order: wave k sums value k, its lanes the tiles lane, lane + 64, ... (eight loads
-// in flight), then a butterfly
-template <int NV>
-__device__ __forceinline__ void tile_seg_totals(const double* __restrict__ part, int ntile, int f, int n,
-                                                double (&tot)[NV]) {
-  static_assert(NV <= TILE_WAVES, "one wave per value");
-  __shared__ double sh[NV];
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  if (wid < NV) {
-    constexpr int UN = 8;
-    double s = 0.0;
-    for (int q = lane; q < n; q += UN * 64) {
-      double w[UN];
-#pragma unroll
-      for (int u = 0; u < UN; ++u) w[u] = part[(size_t)wid * ntile + f + min(q + u * 64, n - 1)];
-#pragma unroll
-      for (int u = 0; u < UN; ++u)
-        if (q + u * 64 < n) s += w[u];
-    }
-    s = wave_sum(s);
-    if (lane == 0) sh[wid] = s;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < NV; ++k) tot[k] = sh[k];
-}
-
-// one read of a flag per block, shared through LDS, so every wave of the block takes the same branch
-// even while the segment's first tile of the same launch may be writing it
-__device__ __forceinline__ bool block_flag(const int* flag) {
-  __shared__ int f;
-  __syncthreads();  // a previous call's readers are done with f
-  if (threadIdx.x == 0) f = *flag;
-  __syncthreads();
-  return f != 0;
-}
-
-// thread 0's copy of a flag the block has already loaded, shared through LDS (as block_flag), so
-// that the flag's load can be in flight together with others
-__device__ __forceinline__ bool block_share(int v) {
-  __shared__ int f;
-  __syncthreads();  // a previous call's readers are done with f
-  if (threadIdx.x == 0) f = v;
-  __syncthreads();
-  return f != 0;
-}
-
-#define FOR_TILE_CELLS(I) \
-  _Pragma("unroll") for (int c_ = 0; c_ < CPT; ++c_) if (int I = ti.lo + c_ * BLOCK + threadIdx.x; I < ti.hi)
-
-// The same cells in rounds of BLOCK consecutive cells [BASE, BASE + BLOCK), every thread of the block
-// in every round whether or not its cell I < ti.hi exists: for kernels that stage their stores
-// through LDS (store_rows synchronises the block).  Each thread still visits its cells in the same
-// order as FOR_TILE_CELLS.
-#define FOR_TILE_ROUNDS(BASE, I) \
-  _Pragma("unroll") for (int c_ = 0; c_ < CPT; ++c_) \
-    if (const int BASE = ti.lo + c_ * BLOCK, I = BASE + (int)threadIdx.x; BASE < ti.hi)
 
 // per-segment PCG state (device)
 struct PcgCtl {
   double tol, bn, res;
   double rho[2];  // rho_k at index k & 1
+  double rr;      // r.r between two launches of a solve in one block
   int maxit, done, iters, status;
+  int next, pad;  // iterations made by those launches so far
 };
 
 }  // namespace difvm
