@@ -95,18 +95,51 @@ DevCsr upload_csr(AmgDev* a, const AmgCsr& M, bool with_diag, hipStream_t s, int
 
 // ---- kernels ------------------------------------------------------------------------------------
 // Every segment's CG stopped: the V-cycle of an iteration queued past the stop has nothing to do.
-// The flags are written only by the CG kernels queued before the V-cycle on the same stream, so they
-// do not change while a V-cycle kernel runs: every wave reads them itself, one segment per lane, and
-// votes (no barrier), and whole blocks return together.  Called first thing, with every lane active.
+// The flags are written by the CG kernels queued before the V-cycle on the same stream and by the test
+// blocks of its first kernel (below): every wave reads them itself, one segment per lane, and votes (no
+// barrier).  A wave of the first kernel may see them either way; the others see what was written before
+// them.  LATE (meshes of few tiles, where a kernel's time is its chain of dependent loads): the vote is
+// taken when a value is stored, so that no load waits for the flags; the kernels of an iteration queued past
+// the stop then read what they would, which there costs less.  Otherwise it is taken first and the wave returns.
 struct StopFlags {
   const PcgCtl* ctl;  // nullptr: never stopped
   int nseg;
 };
-__device__ __forceinline__ bool stopped(const StopFlags& st) {
-  if (!st.ctl) return false;
-  int all = 1;
-  for (int g = threadIdx.x & 63; g < st.nseg; g += 64) all &= st.ctl[g].done;
-  return __all(all) != 0;
+__device__ __forceinline__ int load_stops(const StopFlags& st) {  // 1 if this lane saw only stopped segments
+  if (!st.ctl) return 0;
+  const int lane = threadIdx.x & 63;
+  int all = st.ctl[min(lane, st.nseg - 1)].done;  // (no loop around the first load, which would wait for it)
+  for (int g = lane + 64; g < st.nseg; g += 64) all &= st.ctl[g].done;
+  return all;
+}
+__device__ __forceinline__ bool stopped(int flags) { return __all(flags) != 0; }
+
+// The stopping test of CG iterate k (its r.r partials rr), which the product of iteration k + 1 would make:
+// the cycle's first kernel makes it in blocks of their own, one segment after another, so that after the
+// last iteration the rest of the cycle returns at once.
+struct CycleTest {
+  PcgCtl* ctl;
+  const double* rr;
+  int k, nseg;
+  int blocks;  // the launch's first blocks (a multiple of 8, so that the others keep their XCDs)
+};
+template <bool FINE>
+__device__ __forceinline__ void test_iterate(const CycleTest& t, const Tiles& T) {
+  for (int s = blockIdx.x; s < t.nseg; s += t.blocks) {
+    PcgCtl* ctl = t.ctl + s;
+    const int done = ctl->done, maxit = ctl->maxit;  // uniform over the block: only this block writes them
+    const double tol = ctl->tol, bn = ctl->bn;
+    double rr[1];
+    seg_totals<1, BLOCK, FINE>(t.rr, T.ntile, seg_first(T, s), seg_count(T, s), rr);
+    const double rn = sqrt(rr[0]);
+    const bool conv = rn <= tol * bn;
+    if (threadIdx.x == 0 && !done && (conv || t.k >= maxit)) {
+      ctl->done = 1;
+      ctl->iters = t.k;
+      ctl->res = rn / bn;
+      ctl->status = conv ? 0 : DIFVM_WARN_NOT_CONVERGED;
+    }
+  }
 }
 
 // Sum of val[q] x(col[q]) over q = lo, lo + SW, lo + 2 SW, ... < hi (one lane's share of a CSR row),
@@ -208,46 +241,56 @@ Cheb cheb_coefficients(double lo, double hi) {
   return {theta, 1.0 / theta, rho1 * rho0, 2.0 * rho1 / delta};
 }
 
+// Row range of cell I of a finest-level pass, loaded at a clamped index, without a branch around the load, so
+// that it is in flight together with the flag reads.  Threads past the last cell take that cell's row and
+// store nothing: every lane stays active for the vote.
+#define DIFVM_AMG_CELL(I)                                 \
+  const int flags = load_stops(ctl);                      \
+  const bool in = I < K.nc;                               \
+  I = min(I, K.nc - 1);                                   \
+  SlotRange R = slots_of(K, I);                           \
+  if (!LATE && (stopped(flags) || !in)) return
+
 // level 0, down, first pass (x = 0, b = r): xs = d0 + d1, with d0 = D^-1 r / theta
-template <bool OFF16>
-__global__ __launch_bounds__(BLOCK) void k_amg_cheb_pre1(SellView K, const double* __restrict__ r,
-                                                         double* __restrict__ xs, Cheb c, StopFlags ctl) {
-  int i = xcd_tile(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x;
-  // row range loaded at a clamped index, without a branch around the load, so that it is in flight
-  // together with the flag reads
-  SlotRange R = slots_of(K, min(i, K.nc - 1));
-  if (stopped(ctl) || i >= K.nc) return;
+template <bool OFF16, bool LATE>
+__global__ __launch_bounds__(BLOCK) void k_amg_cheb_pre1(SellView K, Tiles T, CycleTest test,
+                                                         const double* __restrict__ r, double* __restrict__ xs, Cheb c,
+                                                         StopFlags ctl) {
+  if ((int)blockIdx.x < test.blocks) {
+    test_iterate<LATE>(test, T);  // LATE and quarter-tile partials go together (fine_spans)
+    return;
+  }
+  int i = xcd_tile(blockIdx.x - test.blocks, gridDim.x - test.blocks) * BLOCK + threadIdx.x;
+  DIFVM_AMG_CELL(i);
   double di = K.diag[i], rh0 = r[i] / di;
   double d0 = rh0 * c.inv_theta;
   double kd0 = di * d0 + sell_offdiag<OFF16>(K, i, R, [&](int j) { return r[j] / K.diag[j] * c.inv_theta; });
   double rh1 = rh0 - kd0 / di;
-  xs[i] = d0 + (c.c_d * d0 + c.c_r * rh1);
+  if (!LATE || (!stopped(flags) && in)) xs[i] = d0 + (c.c_d * d0 + c.c_r * rh1);
 }
 
 // level 0, down, second pass: res = r - K xs
-template <bool OFF16>
+template <bool OFF16, bool LATE>
 __global__ __launch_bounds__(BLOCK) void k_amg_cheb_pre2(SellView K, const double* __restrict__ r,
                                                          const double* __restrict__ xs, double* __restrict__ res,
                                                          StopFlags ctl) {
   int i = xcd_tile(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x;
-  SlotRange R = slots_of(K, min(i, K.nc - 1));
-  if (stopped(ctl) || i >= K.nc) return;
+  DIFVM_AMG_CELL(i);
   const double ri = r[i];
   double kx = K.diag[i] * xs[i] + sell_offdiag<OFF16>(K, i, R, [&](int j) { return xs[j]; });
-  res[i] = ri - kx;
+  if (!LATE || (!stopped(flags) && in)) res[i] = ri - kx;
 }
 
 // level 0, up, first pass (x = t): d0 = D^-1 (r - K t) / theta
-template <bool OFF16>
+template <bool OFF16, bool LATE>
 __global__ __launch_bounds__(BLOCK) void k_amg_cheb_post1(SellView K, const double* __restrict__ r,
                                                           const double* __restrict__ t, double* __restrict__ d0,
                                                           Cheb c, StopFlags ctl) {
   int i = xcd_tile(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x;
-  SlotRange R = slots_of(K, min(i, K.nc - 1));
-  if (stopped(ctl) || i >= K.nc) return;
+  DIFVM_AMG_CELL(i);
   const double di = K.diag[i], ri = r[i];
   double kt = di * t[i] + sell_offdiag<OFF16>(K, i, R, [&](int j) { return t[j]; });
-  d0[i] = (ri - kt) / di * c.inv_theta;
+  if (!LATE || (!stopped(flags) && in)) d0[i] = (ri - kt) / di * c.inv_theta;
 }
 
 // level 0, up, second pass: z = t + d0 + d1 with rh1 = theta d0 - D^-1 K d0, and per-tile partials
@@ -259,17 +302,21 @@ __global__ __launch_bounds__(FINE ? QUARTER : TILE) void k_amg_cheb_post2(SellVi
                                                              double* __restrict__ z, double* __restrict__ part, Cheb c,
                                                              StopFlags ctl) {
   const Span sp = span_of<FINE>(T);
-  if (stopped(ctl)) return;
+  const int flags = load_stops(ctl);
+  if (!FINE && stopped(flags)) return;
   double v[1] = {0.0};
-  if (const int i = sp.lo + (int)threadIdx.x; i < sp.hi) {
+  double zi = 0.0;
+  const int i = sp.lo + (int)threadIdx.x;
+  if (i < sp.hi) {
     SlotRange R = slots_of(K, i);
     const double di = K.diag[i], d0i = d0[i], ti = t[i], ri = r[i];
     double kd0 = di * d0i + sell_offdiag<OFF16>(K, i, R, [&](int j) { return d0[j]; });
     double rh1 = c.theta * d0i - kd0 / di;
-    double zi = ti + d0i + (c.c_d * d0i + c.c_r * rh1);
-    z[i] = zi;
+    zi = ti + d0i + (c.c_d * d0i + c.c_r * rh1);
     v[0] = ri * zi;
   }
+  if (FINE && stopped(flags)) return;  // every wave of the block alike: written before this launch
+  if (i < sp.hi) z[i] = zi;
   if (part) put_partial<1, FINE ? QUARTER : TILE, FINE>(v, part, T.ntile, sp);
 }
 
@@ -286,12 +333,13 @@ __global__ __launch_bounds__(FINE ? QUARTER : TILE) void k_amg_cheb_post2(SellVi
   int row = g / SW, lane = g % SW;                             \
   const int rr = min(row, n - 1);                              \
   int p0 = ptr[rr], p1 = ptr[rr + 1];                          \
-  if (stopped(ctl)) return;                                    \
+  const int flags = load_stops(ctl);                           \
+  if (!LATE && stopped(flags)) return;                         \
   int lo = p0 + lane, hi = row < n ? p1 : 0
 
 // out = R x (rows of the coarser level); with diag, also outd = out / diag (what the coarser level's
 // pre-smoothing gathers)
-template <int SW>
+template <int SW, bool LATE>
 __global__ __launch_bounds__(BLOCK) void k_amg_restrict(int n, const int32_t* __restrict__ ptr,
                                                         const int32_t* __restrict__ col, const double* __restrict__ val,
                                                         const double* __restrict__ xin, const double* __restrict__ diag,
@@ -301,14 +349,14 @@ __global__ __launch_bounds__(BLOCK) void k_amg_restrict(int n, const int32_t* __
   const double dg = diag ? diag[rr] : 1.0;
   double s = csr_lane_dot<SW>(lo, hi, col, val, [&](int j) { return xin[j]; });
   s = lanes_sum<SW>(s);
-  if (row < n && lane == 0) {
+  if ((!LATE || !stopped(flags)) && row < n && lane == 0) {
     out[row] = s;
     if (diag) outd[row] = s / dg;
   }
 }
 
 // coarse level, down, first pass (x = 0): xs = d0 + d1 with d0 = bd / theta (bd = D^-1 b)
-template <int SW>
+template <int SW, bool LATE>
 __global__ __launch_bounds__(BLOCK) void k_amg_cpre1(int n, const int32_t* __restrict__ ptr,
                                                      const int32_t* __restrict__ col, const double* __restrict__ val,
                                                      const double* __restrict__ diag, const double* __restrict__ bd,
@@ -317,7 +365,7 @@ __global__ __launch_bounds__(BLOCK) void k_amg_cpre1(int n, const int32_t* __res
   const double di = diag[rr], rh0 = bd[rr];
   double s = csr_lane_dot<SW>(lo, hi, col, val, [&](int j) { return bd[j]; });
   s = lanes_sum<SW>(s);
-  if (row < n && lane == 0) {
+  if ((!LATE || !stopped(flags)) && row < n && lane == 0) {
     double d0 = rh0 * c.inv_theta;
     double kd0 = di * d0 + s * c.inv_theta;
     double rh1 = rh0 - kd0 / di;
@@ -326,7 +374,7 @@ __global__ __launch_bounds__(BLOCK) void k_amg_cpre1(int n, const int32_t* __res
 }
 
 // coarse level, down, second pass: res = b - A xs
-template <int SW>
+template <int SW, bool LATE>
 __global__ __launch_bounds__(BLOCK) void k_amg_cpre2(int n, const int32_t* __restrict__ ptr,
                                                      const int32_t* __restrict__ col, const double* __restrict__ val,
                                                      const double* __restrict__ diag, const double* __restrict__ b,
@@ -336,12 +384,12 @@ __global__ __launch_bounds__(BLOCK) void k_amg_cpre2(int n, const int32_t* __res
   const double bi = b[rr], di = diag[rr], xi = xs[rr];
   double s = csr_lane_dot<SW>(lo, hi, col, val, [&](int j) { return xs[j]; });
   s = lanes_sum<SW>(s);
-  if (row < n && lane == 0) res[row] = bi - di * xi - s;
+  if ((!LATE || !stopped(flags)) && row < n && lane == 0) res[row] = bi - di * xi - s;
 }
 
 // coarse level, up, first pass: t = xs + P xc and, since b - A t = res - (A P) xc,
 // d0 = D^-1 (res - (A P) xc) / theta; one pass over the pattern of A P
-template <int SW>
+template <int SW, bool LATE>
 __global__ __launch_bounds__(BLOCK) void k_amg_cup1(int n, const int32_t* __restrict__ ptr,
                                                     const int32_t* __restrict__ col, const double* __restrict__ ap,
                                                     const double* __restrict__ pv, const double* __restrict__ diag,
@@ -354,14 +402,14 @@ __global__ __launch_bounds__(BLOCK) void k_amg_cup1(int n, const int32_t* __rest
   csr_lane_dot2<SW>(lo, hi, col, pv, ap, [&](int j) { return xc[j]; }, sp, sq);
   sp = lanes_sum<SW>(sp);
   sq = lanes_sum<SW>(sq);
-  if (row < n && lane == 0) {
+  if ((!LATE || !stopped(flags)) && row < n && lane == 0) {
     t[row] = xi + sp;
     d0[row] = (ri - sq) / di * c.inv_theta;
   }
 }
 
 // coarse level, up, second pass: x = t + d0 + d1 with rh1 = theta d0 - D^-1 A d0
-template <int SW>
+template <int SW, bool LATE>
 __global__ __launch_bounds__(BLOCK) void k_amg_cup2(int n, const int32_t* __restrict__ ptr,
                                                     const int32_t* __restrict__ col, const double* __restrict__ val,
                                                     const double* __restrict__ diag, const double* __restrict__ t,
@@ -371,7 +419,7 @@ __global__ __launch_bounds__(BLOCK) void k_amg_cup2(int n, const int32_t* __rest
   const double di = diag[rr], d0i = d0[rr], ti = t[rr];
   double s = csr_lane_dot<SW>(lo, hi, col, val, [&](int j) { return d0[j]; });
   s = lanes_sum<SW>(s);
-  if (row < n && lane == 0) {
+  if ((!LATE || !stopped(flags)) && row < n && lane == 0) {
     double rh1 = c.theta * d0i - (di * d0i + s) / di;
     x[row] = ti + d0i + (c.c_d * d0i + c.c_r * rh1);
   }
@@ -379,26 +427,31 @@ __global__ __launch_bounds__(BLOCK) void k_amg_cup2(int n, const int32_t* __rest
 
 // level 0, up: t = xs + P xc (one thread per row; almost every row of the finest prolongator has at
 // most four entries, so four in flight)
+template <bool LATE>
 __global__ __launch_bounds__(BLOCK) void k_amg_prolong(int n, const int32_t* __restrict__ ptr,
                                                        const int32_t* __restrict__ col, const double* __restrict__ val,
                                                        const double* __restrict__ xs, const double* __restrict__ xc,
                                                        double* __restrict__ t, StopFlags ctl) {
   int i = xcd_tile(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x;
-  int lo = ptr[min(i, n - 1)], hi = ptr[min(i, n - 1) + 1];
-  if (stopped(ctl) || i >= n) return;
-  const double xi = xs[i];
+  const int ii = min(i, n - 1);
+  int lo = ptr[ii], hi = ptr[ii + 1];
+  const int flags = load_stops(ctl);
+  if (!LATE && (stopped(flags) || i >= n)) return;
+  const double xi = xs[ii];
   double s = csr_lane_dot<1, 4>(lo, hi, col, val, [&](int j) { return xc[j]; });
-  t[i] = xi + s;
+  if (!LATE || (!stopped(flags) && i < n)) t[i] = xi + s;
 }
 
 // coarsest: x = A_L^-1 b with the dense inverse (row-major, n <= 2048): one block per row, threads
 // over the columns (every load of a thread in flight at once: n / BLOCK <= 8), per-wave shuffle trees
 // and the four wave sums added in order; b is read through L2
 constexpr int MAX_DENSE = 2048;
+template <bool LATE>
 __global__ __launch_bounds__(BLOCK) void k_amg_coarsest(int n, const double* __restrict__ inv,
                                                         const double* __restrict__ b, double* __restrict__ x,
                                                         StopFlags ctl) {
-  if (stopped(ctl)) return;
+  const int flags = load_stops(ctl);
+  if (!LATE && stopped(flags)) return;
   __shared__ double ws[BLOCK / 64];
   const double* row = inv + (size_t)blockIdx.x * n;
   constexpr int U = MAX_DENSE / BLOCK;
@@ -416,7 +469,8 @@ __global__ __launch_bounds__(BLOCK) void k_amg_coarsest(int n, const double* __r
   s = lanes_sum<64>(s);
   if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = s;
   __syncthreads();
-  if (threadIdx.x == 0) {
+  const bool go = !LATE || !stopped(flags);
+  if (threadIdx.x == 0 && go) {
     double t = 0.0;
 #pragma unroll
     for (int w = 0; w < BLOCK / 64; ++w) t += ws[w];
@@ -491,7 +545,7 @@ void dense_inverse_spd(const Ctx& c, int n, double* M, hipStream_t s) {
 }
 
 #define DIFVM_AMG_LAUNCH(KERNEL, SW, N, S, ...)                                                           \
-  KERNEL<SW><<<(int)(((size_t)(N) * (SW) + BLOCK - 1) / BLOCK), BLOCK, 0, S>>>(__VA_ARGS__)
+  KERNEL<SW, LATE><<<(int)(((size_t)(N) * (SW) + BLOCK - 1) / BLOCK), BLOCK, 0, S>>>(__VA_ARGS__)
 
 #define DIFVM_AMG_DISPATCH(KERNEL, sw, N, S, ...)               \
   switch (sw) {                                                 \
@@ -648,21 +702,21 @@ double amg_vcycle_bytes(const AmgDev* a) {
   return b;
 }
 
+template <bool LATE>
 static void launch_vcycle(const AmgDev* a, hipStream_t s, SellMatrix Km, const double* r, double* z, double* part,
-                          StopFlags ctl) {
+                          StopFlags ctl, CycleTest test) {
   difvm_mesh* m = a->mesh;
   SellView K = sview(m, Km);
   const int L = a->L, nc = m->d.nc;
   std::vector<Cheb> c(L);
   for (int l = 0; l < L; ++l) c[l] = cheb_coefficients(0.1 * a->hi[l], a->hi[l]);
+  const Tiles T = tiles_of(m);
+  const int G = grid_for(nc);
   // down
-  if (K.off16) {
-    k_amg_cheb_pre1<true><<<grid_for(nc), BLOCK, 0, s>>>(K, r, a->xs[0], c[0], ctl);
-    k_amg_cheb_pre2<true><<<grid_for(nc), BLOCK, 0, s>>>(K, r, a->xs[0], a->res[0], ctl);
-  } else {
-    k_amg_cheb_pre1<false><<<grid_for(nc), BLOCK, 0, s>>>(K, r, a->xs[0], c[0], ctl);
-    k_amg_cheb_pre2<false><<<grid_for(nc), BLOCK, 0, s>>>(K, r, a->xs[0], a->res[0], ctl);
-  }
+  (K.off16 ? k_amg_cheb_pre1<true, LATE> : k_amg_cheb_pre1<false, LATE>)<<<G + test.blocks, BLOCK, 0, s>>>(
+      K, T, test, r, a->xs[0], c[0], ctl);
+  (K.off16 ? k_amg_cheb_pre2<true, LATE> : k_amg_cheb_pre2<false, LATE>)<<<G, BLOCK, 0, s>>>(K, r, a->xs[0], a->res[0],
+                                                                                             ctl);
   for (int l = 0; l < L; ++l) {
     if (l > 0) {
       const DevCsr& A = a->A[l];
@@ -675,7 +729,7 @@ static void launch_vcycle(const AmgDev* a, hipStream_t s, SellMatrix Km, const d
     DIFVM_AMG_DISPATCH(k_amg_restrict, R.sw, R.n, s, R.n, R.ptr, R.col, R.val, a->res[l], dc, a->b[l + 1],
                        a->bd[l + 1], ctl);
   }
-  k_amg_coarsest<<<a->rows[L], BLOCK, 0, s>>>(a->rows[L], a->cinv, a->b[L], a->x[L], ctl);
+  k_amg_coarsest<LATE><<<a->rows[L], BLOCK, 0, s>>>(a->rows[L], a->cinv, a->b[L], a->x[L], ctl);
   // up
   for (int l = L - 1; l >= 1; --l) {
     const DevCsr& Q = a->AP[l];
@@ -687,25 +741,25 @@ static void launch_vcycle(const AmgDev* a, hipStream_t s, SellMatrix Km, const d
   }
   {
     const DevCsr& P = a->P0;
-    k_amg_prolong<<<grid_for(P.n), BLOCK, 0, s>>>(P.n, P.ptr, P.col, P.val, a->xs[0], a->x[1], a->t[0], ctl);
+    k_amg_prolong<LATE><<<grid_for(P.n), BLOCK, 0, s>>>(P.n, P.ptr, P.col, P.val, a->xs[0], a->x[1], a->t[0], ctl);
   }
-  Tiles T = tiles_of(m);
-  const bool fine = fine_spans(m);
-  (K.off16 ? k_amg_cheb_post1<true> : k_amg_cheb_post1<false>)<<<grid_for(nc), BLOCK, 0, s>>>(K, r, a->t[0], a->d0[0],
+  (K.off16 ? k_amg_cheb_post1<true, LATE> : k_amg_cheb_post1<false, LATE>)<<<G, BLOCK, 0, s>>>(K, r, a->t[0], a->d0[0],
                                                                                                c[0], ctl);
-  (K.off16 ? fine ? k_amg_cheb_post2<true, true> : k_amg_cheb_post2<true, false>
-           : fine ? k_amg_cheb_post2<false, true> : k_amg_cheb_post2<false, false>)<<<n_spans(m), fine ? QUARTER : TILE, 0,
-                                                                                       s>>>(K, T, r, a->t[0], a->d0[0], z,
-                                                                                            part, c[0], ctl);
+  (K.off16 ? k_amg_cheb_post2<true, LATE> : k_amg_cheb_post2<false, LATE>)<<<n_spans(m), LATE ? QUARTER : TILE, 0, s>>>(
+      K, T, r, a->t[0], a->d0[0], z, part, c[0], ctl);
   DIFVM_HIP(hipGetLastError());
 }
 
-void amg_vcycle(const AmgDev* a, SellMatrix Km, const double* r, double* z, double* part, const PcgCtl* ctls) {
+void amg_vcycle(const AmgDev* a, SellMatrix Km, const double* r, double* z, double* part, PcgCtl* ctls,
+                const double* rr, int k) {
   difvm_mesh* m = a->mesh;
+  const int nseg = m->d.nseg;
+  const CycleTest test{ctls, rr, k, nseg, rr ? std::min(64, (nseg + 7) & ~7) : 0};
   // queued kernel by kernel on the solve's stream (inside a captured step they join that graph): the
   // host queues a cycle in well under one iteration's GPU time, and a replayed graph of the cycle
   // cost about 9 us of idle GPU between its end and the next kernel on the stream
-  launch_vcycle(a, ctx_of(m).stream, Km, r, z, part, StopFlags{ctls, m->d.nseg});
+  (fine_spans(m) ? launch_vcycle<true> : launch_vcycle<false>)(a, ctx_of(m).stream, Km, r, z, part, StopFlags{ctls, nseg},
+                                                               test);
 }
 
 }  // namespace difvm

@@ -19,8 +19,11 @@ void amg_free(AmgDev* a);
 // each coarse correction, a dense solve on the coarsest; the finest level uses K, the coarser ones
 // the stored Galerkin operators), queued on the mesh's stream.  part != nullptr: the last kernel stores per-tile partials of r.z at part[t].
 // ctl != nullptr (the per-segment CG states): every kernel returns at once when all segments have
-// stopped (iterations queued after the stop).
-void amg_vcycle(const AmgDev* a, SellMatrix K, const double* r, double* z, double* part, const PcgCtl* ctl);
+// stopped (iterations queued after the stop).  rr != nullptr: the first kernel also makes the stopping test
+// of CG iterate k, whose r.r partials these are (as the product of iteration k + 1 does), so that the
+// cycle after the last iteration ends there.
+void amg_vcycle(const AmgDev* a, SellMatrix K, const double* r, double* z, double* part, PcgCtl* ctl,
+                const double* rr = nullptr, int k = 0);
 // rows per level (finest first) into rows[0..cap); returns the number of levels
 int amg_levels(const AmgDev* a, int* rows, int cap);
 // Algorithmic bytes of one V-cycle: every kernel's distinct inputs read once and outputs written

@@ -845,10 +845,14 @@ SolveResult pcg(difvm_mesh* m, SellMatrix A, const double* b, double* x, double 
   // the r.z partials)
   // (the V-cycle's kernels skip their work once every segment has stopped; while some segment runs
   // on they compute for all, which changes nothing a stopped segment reads)
+  // the cycle's first kernel makes iterate kk's stopping test, so that the last cycle ends with it; while every
+  // launch is being timed the product makes it and every timed cycle is a whole one
+  const Profiler& prof = ctx_of(m).prof;
+  const bool cycle_test = !(prof.on && prof.stride == 1);
   auto precondition = [&](int kk) {
     if (!amg) return;
-    ProfScope ps(m, "pcg_amg_vcycle", kk);
-    amg_vcycle(amg, A, r, z, partB + NP, w->pcg);
+    ProfScope ps(m, "pcg_amg_vcycle", cycle_test ? kk + 1 : kk);  // a whole cycle if iteration kk + 1 runs
+    amg_vcycle(amg, A, r, z, partB + NP, w->pcg, cycle_test && kk > 0 ? partB : nullptr, kk);
   };
   (fine ? k_pcg_init1<true> : k_pcg_init1<false>)<<<NP, NTB, 0, s>>>(V, T, b, x, r, part0);
   (amg ? fine ? k_pcg_init2<false, true> : k_pcg_init2<false, false>
@@ -868,7 +872,8 @@ SolveResult pcg(difvm_mesh* m, SellMatrix A, const double* b, double* x, double 
   if (qo) {
     // queue-only: iterations 1..K and the stopping test of iterate K, no read-back
     int K = std::min(qo->budget, maxit);
-    for (int kk = 1; kk <= K + 1; ++kk) {
+    const int last = amg && cycle_test && K > 0 ? K : K + 1;  // the launch that tests iterate K
+    for (int kk = 1; kk <= last; ++kk) {
       {
         ProfScope ps(m, "pcg_spmv_dot", kk);
         launch_pcg_spmv(GS, s, V, T, kk, z, Pk[(kk - 1) & 1], Pk[kk & 1], q, partB, partA, w->pcg);
@@ -913,7 +918,8 @@ SolveResult pcg(difvm_mesh* m, SellMatrix A, const double* b, double* x, double 
     slot ^= 1;
   }
   SolveResult R = pcg_result(m, hs, nullptr);
-  // iteration k's kernels ran while some segment had not stopped, i.e. for k <= the largest count
+  // iteration k's kernels ran while some segment had not stopped, i.e. for k <= the largest count (and the
+  // cycle after the last one ended with its first kernel)
   prof_idle_after(ctx_of(m), prof_mark, R.iters[0]);  // iters[0]: the largest over the segments
   if (hint) *hint = R.iters[0];
   return R;
