@@ -31,6 +31,27 @@ struct AmgLevel {
   double hi = 0.0;
 };
 
+// The degree-2 Chebyshev sweep in D^-1 A over [lo, hi]: theta = (hi + lo) / 2, delta = (hi - lo) / 2,
+// sigma = theta / delta, rho0 = 1 / sigma, rho1 = 1 / (2 sigma - rho0), c_d = rho1 rho0, c_r = 2 rho1 / delta.
+struct Cheb {
+  double theta, inv_theta, c_d, c_r;
+};
+Cheb cheb_coefficients(double lo, double hi);
+
+// A level between the finest and the coarsest as two passes instead of six.  The sweep from zero is a fixed
+// polynomial of D^-1 A, xs = q(b) = (alpha - beta D^-1 A) D^-1 b with alpha = (1 + c_d) / theta + c_r and
+// beta = c_r / theta, so with bd = D^-1 b:
+//   down:  xs = q(b);  res = b - A xs = S bd,  S = D - alpha A + beta A D^-1 A;  b_2 = R res = (R S) bd
+//   up:    x = xs + P x_2 + q(res - A P x_2) = xs + q(res) + G x_2,  G = P - alpha D^-1 (A P) + beta D^-1 A D^-1 (A P)
+// and with the coarsest level's inverse, G x_2 = (G A_2^-1) b_2.
+struct AmgFused {
+  double alpha = 0.0, beta = 0.0;
+  AmgCsr S, RS, G;  // every entry in CSR (the diagonal too)
+};
+struct AmgHierarchy;
+// those of level 1 of a hierarchy of three levels
+AmgFused amg_fuse(const AmgHierarchy& H);
+
 struct AmgOptions {
   double theta = 0.0;        // strength-of-connection threshold on coarse levels (0: every coupling)
   double theta_fine = 0.08;  // ... and on the finest

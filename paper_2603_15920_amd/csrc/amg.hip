@@ -49,6 +49,10 @@ struct AmgDev {
                                        // post-smoothing step
   std::vector<double> hi;        // levels 0..L-1: upper end of the Chebyshev interval
   double* cinv = nullptr;        // dense inverse of A_L, row-major
+  // level 1 of three as two passes (AmgFused; S.n = 0: not built): H = G A_2^-1, dense rows(1) x rows(2)
+  DevCsr S, RS;
+  double* H = nullptr;
+  double alpha = 0.0, beta = 0.0;
   std::vector<int> rows;
   std::vector<void*> allocs;
 };
@@ -229,18 +233,7 @@ __device__ __forceinline__ double sell_offdiag(const SellView& K, int i, SlotRan
 
 // The degree-2 Chebyshev sweep in D^-1 A over [lo, hi] (hi bounds the spectrum of D^-1 A), the same
 // before and after the coarse correction.  From x with residual rh0 = D^-1 (b - A x):  d0 = rh0 / theta,  rh1 = rh0 - D^-1 K d0,  d1 = c_d d0 + c_r rh1,
-// x <- x + d0 + d1,  with theta = (hi + lo) / 2, delta = (hi - lo) / 2, sigma = theta / delta,
-// rho0 = 1 / sigma, rho1 = 1 / (2 sigma - rho0), c_d = rho1 rho0, c_r = 2 rho1 / delta.
-struct Cheb {
-  double theta, inv_theta, c_d, c_r;
-};
-
-Cheb cheb_coefficients(double lo, double hi) {
-  double theta = 0.5 * (hi + lo), delta = 0.5 * (hi - lo);
-  double sigma = theta / delta, rho0 = 1.0 / sigma, rho1 = 1.0 / (2.0 * sigma - rho0);
-  return {theta, 1.0 / theta, rho1 * rho0, 2.0 * rho1 / delta};
-}
-
+// x <- x + d0 + d1 (coefficients: Cheb, amg.h).
 // Row range of cell I of a finest-level pass, loaded at a clamped index, without a branch around the load, so
 // that it is in flight together with the flag reads.  Threads past the last cell take that cell's row and
 // store nothing: every lane stays active for the vote.
@@ -425,6 +418,93 @@ __global__ __launch_bounds__(BLOCK) void k_amg_cup2(int n, const int32_t* __rest
   }
 }
 
+// Level 1 of three, the whole way down (AmgFused): rows of level 1 (SW lanes each) in the first blocks,
+//   xs = alpha bd - beta D^-1 A bd,  resd = D^-1 S bd
+// and rows of level 2 (a wave each) in the others, b2 = (R S) bd.  With the pass below it stands for the
+// six of the level and the dense solve: on meshes of few tiles a cycle's time is its number of launches
+// (each some 3 us on the device and 2.5 to 5 for the host), while the 4.5 times as many entries of S stay
+// in the caches.  A CG iteration's 14 launches become 10: 48,000 cells 58 to 42 us, 93,750 61 to 47,
+// 162,000 67 to 52 (31, 38 and 45 us where the host is fast enough for the device to be the limit).  Eight
+// or 32 lanes per row measured the same or slower, 64 slower (38 to 42 us at 93,750 cells).
+template <int SW, bool LATE>
+__global__ __launch_bounds__(BLOCK) void k_amg_down1(int n, const int32_t* __restrict__ aptr,
+                                                     const int32_t* __restrict__ acol, const double* __restrict__ aval,
+                                                     const double* __restrict__ diag, const int32_t* __restrict__ sptr,
+                                                     const int32_t* __restrict__ scol, const double* __restrict__ sval,
+                                                     int n2, const int32_t* __restrict__ rptr,
+                                                     const int32_t* __restrict__ rcol, const double* __restrict__ rval,
+                                                     double alpha, double beta, const double* __restrict__ bd,
+                                                     double* __restrict__ xs, double* __restrict__ resd,
+                                                     double* __restrict__ b2, StopFlags ctl) {
+  const int flags = load_stops(ctl);
+  if (!LATE && stopped(flags)) return;
+  const int blocks1 = (n * SW + BLOCK - 1) / BLOCK;
+  auto x = [&](int j) { return bd[j]; };
+  if ((int)blockIdx.x < blocks1) {
+    const int g = blockIdx.x * BLOCK + threadIdx.x, row = g / SW, lane = g % SW, rr = min(row, n - 1);
+    const int a0 = aptr[rr], a1 = aptr[rr + 1], s0 = sptr[rr], s1 = sptr[rr + 1];
+    const double di = diag[rr], bi = bd[rr];
+    double s = csr_lane_dot<SW>(s0 + lane, row < n ? s1 : 0, scol, sval, x);
+    double a = csr_lane_dot<SW, 4>(a0 + lane, row < n ? a1 : 0, acol, aval, x);
+    s = lanes_sum<SW>(s);
+    a = lanes_sum<SW>(a);
+    if ((!LATE || !stopped(flags)) && row < n && lane == 0) {
+      resd[row] = s / di;
+      xs[row] = alpha * bi - beta / di * (di * bi + a);
+    }
+  } else {
+    const int row = ((int)blockIdx.x - blocks1) * (BLOCK / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int rr = min(row, n2 - 1);
+    const int p0 = rptr[rr], p1 = rptr[rr + 1];
+    double s = lanes_sum<64>(csr_lane_dot<64>(p0 + lane, row < n2 ? p1 : 0, rcol, rval, x));
+    if ((!LATE || !stopped(flags)) && row < n2 && lane == 0) b2[row] = s;
+  }
+}
+
+// and up: x = xs + q(res) + H b2, the dense row of H by SW lanes, four loads in flight
+template <int SW, bool LATE>
+__global__ __launch_bounds__(BLOCK) void k_amg_up1(int n, const int32_t* __restrict__ ptr,
+                                                   const int32_t* __restrict__ col, const double* __restrict__ val,
+                                                   const double* __restrict__ diag, int n2,
+                                                   const double* __restrict__ H, double alpha, double beta,
+                                                   const double* __restrict__ xs, const double* __restrict__ resd,
+                                                   const double* __restrict__ b2, double* __restrict__ x,
+                                                   StopFlags ctl) {
+  DIFVM_AMG_ROW(ptr, n);
+  const double di = diag[rr], rd = resd[rr], xi = xs[rr];
+  const double* h = H + (size_t)rr * n2;
+  double a = csr_lane_dot<SW, 4>(lo, hi, col, val, [&](int j) { return resd[j]; });
+  double s = 0.0;
+  constexpr int UN = 8;
+  for (int q = lane; q < n2; q += UN * SW) {
+    double v[UN], w[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int k = min(q + u * SW, n2 - 1);
+      v[u] = h[k];
+      w[u] = b2[k];
+    }
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+      if (q + u * SW < n2) s += v[u] * w[u];
+  }
+  a = lanes_sum<SW>(a);
+  s = lanes_sum<SW>(s);
+  if ((!LATE || !stopped(flags)) && row < n && lane == 0) x[row] = xi + (alpha * rd - beta / di * (di * rd + a)) + s;
+}
+
+// setup: H = G A_2^-1, one block per row of G
+__global__ __launch_bounds__(BLOCK) void k_amg_h(int n2, const int32_t* __restrict__ ptr, const int32_t* __restrict__ col,
+                                                 const double* __restrict__ val, const double* __restrict__ inv,
+                                                 double* __restrict__ H) {
+  const int p0 = ptr[blockIdx.x], p1 = ptr[blockIdx.x + 1];
+  for (int c = threadIdx.x; c < n2; c += BLOCK) {
+    double s = 0.0;
+    for (int q = p0; q < p1; ++q) s += val[q] * inv[(size_t)col[q] * n2 + c];
+    H[(size_t)blockIdx.x * n2 + c] = s;
+  }
+}
+
 // level 0, up: t = xs + P xc (one thread per row; almost every row of the finest prolongator has at
 // most four entries, so four in flight)
 template <bool LATE>
@@ -544,6 +624,11 @@ void dense_inverse_spd(const Ctx& c, int n, double* M, hipStream_t s) {
   DIFVM_CHECK(!hbad, DIFVM_ERR_UNSUPPORTED, "AMG setup: coarsest matrix is not positive definite");
 }
 
+// largest rows(1) x rows(2) of the fused passes' dense matrix (32 MB: it is read in every cycle; 162,000
+// cells have 22 MB, 384,000 would have 110)
+constexpr size_t FUSE_MAX_DENSE = size_t(4) << 20;
+constexpr int FUSE_LANES = 16;  // per row of level 1: its S row has some 90 entries, H's some hundreds
+
 #define DIFVM_AMG_LAUNCH(KERNEL, SW, N, S, ...)                                                           \
   KERNEL<SW, LATE><<<(int)(((size_t)(N) * (SW) + BLOCK - 1) / BLOCK), BLOCK, 0, S>>>(__VA_ARGS__)
 
@@ -650,6 +735,18 @@ AmgDev* amg_create(difvm_mesh* m, SellMatrix K, const AmgOptions& opt) {
     DIFVM_CHECK(H.n_coarsest <= MAX_DENSE, DIFVM_ERR_UNSUPPORTED, "coarsest AMG level too large");
     a->cinv = up(a, H.coarsest_dense, s);
     dense_inverse_spd(ctx_of(m), H.n_coarsest, a->cinv, s);
+    AmgFused F;  // kept until the synchronisation below
+    if (L_ == 2 && fine_spans(m) && (size_t)a->rows[1] * a->rows[2] <= FUSE_MAX_DENSE) {
+      F = amg_fuse(H);
+      a->alpha = F.alpha;
+      a->beta = F.beta;
+      a->S = upload_csr(a, F.S, false, s);
+      a->RS = upload_csr(a, F.RS, false, s);
+      const DevCsr G = upload_csr(a, F.G, false, s);
+      a->H = work(a, (size_t)a->rows[1] * a->rows[2]);
+      k_amg_h<<<a->rows[1], BLOCK, 0, s>>>(a->rows[2], G.ptr, G.col, G.val, a->cinv, a->H);
+      DIFVM_HIP(hipGetLastError());
+    }
     DIFVM_HIP(hipStreamSynchronize(s));
   } catch (...) {
     amg_free(a);
@@ -683,18 +780,24 @@ double amg_vcycle_bytes(const AmgDev* a) {
   double b = 0.0;
   b += K + 16.0 * n0;  // first pre-smoothing pass: r -> xs
   b += K + 24.0 * n0;  // second: r, xs -> res
-  for (int l = 0; l < L; ++l) {
-    if (l > 0) {
-      b += csr(a->A[l], true, 1) + 16.0 * rows(l);  // bd -> xs
-      b += csr(a->A[l], true, 1) + 24.0 * rows(l);  // b, xs -> res
+  if (a->S.n) {
+    b += csr(a->R[0], false, 1) + 8.0 * n0 + 24.0 * rows(1);  // res -> b, D^-1 b
+    b += csr(a->A[1], true, 1) + csr(a->S, false, 1) + csr(a->RS, false, 1) + 24.0 * rows(1) + 8.0 * rows(2);
+    b += csr(a->A[1], true, 1) + 8.0 * rows(1) * rows(2) + 24.0 * rows(1) + 8.0 * rows(2);  // xs, resd, b_2 -> x
+  } else {
+    for (int l = 0; l < L; ++l) {
+      if (l > 0) {
+        b += csr(a->A[l], true, 1) + 16.0 * rows(l);  // bd -> xs
+        b += csr(a->A[l], true, 1) + 24.0 * rows(l);  // b, xs -> res
+      }
+      bool coarsest = l + 1 == L;
+      b += csr(a->R[l], false, 1) + 8.0 * rows(l) + (coarsest ? 8.0 : 24.0) * rows(l + 1);  // res -> b (, D^-1 b)
     }
-    bool coarsest = l + 1 == L;
-    b += csr(a->R[l], false, 1) + 8.0 * rows(l) + (coarsest ? 8.0 : 24.0) * rows(l + 1);  // res -> b (, D^-1 b)
-  }
-  b += 8.0 * rows(L) * rows(L) + 16.0 * rows(L);  // dense solve
-  for (int l = L - 1; l >= 1; --l) {
-    b += csr(a->AP[l], true, 2) + 32.0 * rows(l) + 8.0 * rows(l + 1);  // xs, res, x_c -> t, d0
-    b += csr(a->A[l], true, 1) + 24.0 * rows(l);                       // t, d0 -> x
+    b += 8.0 * rows(L) * rows(L) + 16.0 * rows(L);  // dense solve
+    for (int l = L - 1; l >= 1; --l) {
+      b += csr(a->AP[l], true, 2) + 32.0 * rows(l) + 8.0 * rows(l + 1);  // xs, res, x_c -> t, d0
+      b += csr(a->A[l], true, 1) + 24.0 * rows(l);                       // t, d0 -> x
+    }
   }
   b += csr(a->P0, false, 1) + 16.0 * n0 + 8.0 * rows(1);  // xs, x_1 -> t
   b += K + 24.0 * n0;                                     // r, t -> d0
@@ -717,27 +820,39 @@ static void launch_vcycle(const AmgDev* a, hipStream_t s, SellMatrix Km, const d
       K, T, test, r, a->xs[0], c[0], ctl);
   (K.off16 ? k_amg_cheb_pre2<true, LATE> : k_amg_cheb_pre2<false, LATE>)<<<G, BLOCK, 0, s>>>(K, r, a->xs[0], a->res[0],
                                                                                              ctl);
-  for (int l = 0; l < L; ++l) {
-    if (l > 0) {
+  if (a->S.n) {
+    // level 1 and the coarsest in two passes
+    const DevCsr &R = a->R[0], &A = a->A[1], &S = a->S, &Q = a->RS;
+    DIFVM_AMG_DISPATCH(k_amg_restrict, R.sw, R.n, s, R.n, R.ptr, R.col, R.val, a->res[0], A.diag, a->b[1], a->bd[1], ctl);
+    const int blocks = (S.n * FUSE_LANES + BLOCK - 1) / BLOCK + (Q.n + BLOCK / 64 - 1) / (BLOCK / 64);
+    k_amg_down1<FUSE_LANES, LATE><<<blocks, BLOCK, 0, s>>>(A.n, A.ptr, A.col, A.val, A.diag, S.ptr, S.col, S.val, Q.n,
+                                                           Q.ptr, Q.col, Q.val, a->alpha, a->beta, a->bd[1], a->xs[1],
+                                                           a->res[1], a->b[2], ctl);
+    k_amg_up1<FUSE_LANES, LATE><<<(A.n * FUSE_LANES + BLOCK - 1) / BLOCK, BLOCK, 0, s>>>(
+        A.n, A.ptr, A.col, A.val, A.diag, Q.n, a->H, a->alpha, a->beta, a->xs[1], a->res[1], a->b[2], a->x[1], ctl);
+  } else {
+    for (int l = 0; l < L; ++l) {
+      if (l > 0) {
+        const DevCsr& A = a->A[l];
+        DIFVM_AMG_DISPATCH(k_amg_cpre1, A.sw, A.n, s, A.n, A.ptr, A.col, A.val, A.diag, a->bd[l], a->xs[l], c[l], ctl);
+        DIFVM_AMG_DISPATCH(k_amg_cpre2, A.sw, A.n, s, A.n, A.ptr, A.col, A.val, A.diag, a->b[l], a->xs[l], a->res[l],
+                           ctl);
+      }
+      const DevCsr& R = a->R[l];
+      const double* dc = l + 1 < L ? a->A[l + 1].diag : nullptr;  // the coarsest level needs no D^-1 b
+      DIFVM_AMG_DISPATCH(k_amg_restrict, R.sw, R.n, s, R.n, R.ptr, R.col, R.val, a->res[l], dc, a->b[l + 1],
+                         a->bd[l + 1], ctl);
+    }
+    k_amg_coarsest<LATE><<<a->rows[L], BLOCK, 0, s>>>(a->rows[L], a->cinv, a->b[L], a->x[L], ctl);
+    // up
+    for (int l = L - 1; l >= 1; --l) {
+      const DevCsr& Q = a->AP[l];
       const DevCsr& A = a->A[l];
-      DIFVM_AMG_DISPATCH(k_amg_cpre1, A.sw, A.n, s, A.n, A.ptr, A.col, A.val, A.diag, a->bd[l], a->xs[l], c[l], ctl);
-      DIFVM_AMG_DISPATCH(k_amg_cpre2, A.sw, A.n, s, A.n, A.ptr, A.col, A.val, A.diag, a->b[l], a->xs[l], a->res[l],
+      DIFVM_AMG_DISPATCH(k_amg_cup1, Q.sw, Q.n, s, Q.n, Q.ptr, Q.col, Q.val, Q.val2, A.diag, a->xs[l], a->res[l],
+                         a->x[l + 1], a->t[l], a->d0[l], c[l], ctl);
+      DIFVM_AMG_DISPATCH(k_amg_cup2, A.sw, A.n, s, A.n, A.ptr, A.col, A.val, A.diag, a->t[l], a->d0[l], a->x[l], c[l],
                          ctl);
     }
-    const DevCsr& R = a->R[l];
-    const double* dc = l + 1 < L ? a->A[l + 1].diag : nullptr;  // the coarsest level needs no D^-1 b
-    DIFVM_AMG_DISPATCH(k_amg_restrict, R.sw, R.n, s, R.n, R.ptr, R.col, R.val, a->res[l], dc, a->b[l + 1],
-                       a->bd[l + 1], ctl);
-  }
-  k_amg_coarsest<LATE><<<a->rows[L], BLOCK, 0, s>>>(a->rows[L], a->cinv, a->b[L], a->x[L], ctl);
-  // up
-  for (int l = L - 1; l >= 1; --l) {
-    const DevCsr& Q = a->AP[l];
-    const DevCsr& A = a->A[l];
-    DIFVM_AMG_DISPATCH(k_amg_cup1, Q.sw, Q.n, s, Q.n, Q.ptr, Q.col, Q.val, Q.val2, A.diag, a->xs[l], a->res[l],
-                       a->x[l + 1], a->t[l], a->d0[l], c[l], ctl);
-    DIFVM_AMG_DISPATCH(k_amg_cup2, A.sw, A.n, s, A.n, A.ptr, A.col, A.val, A.diag, a->t[l], a->d0[l], a->x[l], c[l],
-                       ctl);
   }
   {
     const DevCsr& P = a->P0;

@@ -332,4 +332,77 @@ void amg_build(const AmgCsr& A0, const AmgOptions& opt, AmgHierarchy& H) {
   }
 }
 
+Cheb cheb_coefficients(double lo, double hi) {
+  double theta = 0.5 * (hi + lo), delta = 0.5 * (hi - lo);
+  double sigma = theta / delta, rho0 = 1.0 / sigma, rho1 = 1.0 / (2.0 * sigma - rho0);
+  return {theta, 1.0 / theta, rho1 * rho0, 2.0 * rho1 / delta};
+}
+
+// C = X + s Y diag(d)^-1 Z for CSR matrices of whole rows (nothing apart), n_cols columns
+static AmgCsr add_product(const AmgCsr& X, double s, const AmgCsr& Y, const std::vector<double>* d, const AmgCsr& Z,
+                          int n_cols) {
+  AmgCsr C;
+  C.n = Y.n;
+  C.ptr.assign(1, 0);
+  C.col.reserve(X.col.size());
+  C.val.reserve(X.col.size());
+  std::vector<double> acc(n_cols, 0.0);
+  std::vector<int32_t> mark(n_cols, -1);
+  for (int i = 0; i < Y.n; ++i) {
+    const size_t first = C.col.size();
+    auto add = [&](int c, double v) {
+      if (mark[c] != i) {
+        mark[c] = i;
+        acc[c] = 0.0;
+        C.col.push_back(c);
+      }
+      acc[c] += v;
+    };
+    if (X.n)
+      for (int q = X.ptr[i]; q < X.ptr[i + 1]; ++q) add(X.col[q], X.val[q]);
+    for (int q = Y.ptr[i]; q < Y.ptr[i + 1]; ++q) {
+      const int j = Y.col[q];
+      const double y = s * Y.val[q] / (d ? (*d)[j] : 1.0);
+      for (int r = Z.ptr[j]; r < Z.ptr[j + 1]; ++r) add(Z.col[r], y * Z.val[r]);
+    }
+    for (size_t k = first; k < C.col.size(); ++k) C.val.push_back(acc[C.col[k]]);
+    C.ptr.push_back((int32_t)C.col.size());
+  }
+  return C;
+}
+
+AmgFused amg_fuse(const AmgHierarchy& H) {
+  const AmgLevel& L = H.levels[1];
+  const AmgCsr& A = H.coarse[0];
+  const int n = A.n, n2 = H.n_coarsest;
+  AmgFused F;
+  const Cheb c = cheb_coefficients(0.1 * L.hi, L.hi);
+  F.alpha = (1.0 + c.c_d) * c.inv_theta + c.c_r;
+  F.beta = c.c_r * c.inv_theta;
+  AmgCsr W, X;  // A with its diagonal in the rows; D - alpha A
+  W.n = X.n = n;
+  W.ptr.assign(1, 0);
+  for (int i = 0; i < n; ++i) {
+    W.col.push_back(i);
+    W.val.push_back(A.diag[i]);
+    for (int q = A.ptr[i]; q < A.ptr[i + 1]; ++q) {
+      W.col.push_back(A.col[q]);
+      W.val.push_back(A.val[q]);
+    }
+    W.ptr.push_back((int32_t)W.col.size());
+  }
+  X = W;
+  for (size_t q = 0; q < X.val.size(); ++q) X.val[q] *= -F.alpha;
+  for (int i = 0; i < n; ++i) X.val[X.ptr[i]] += A.diag[i];
+  F.S = add_product(X, F.beta, W, &A.diag, W, n);
+  F.RS = add_product(AmgCsr{}, 1.0, L.R, nullptr, F.S, n);
+  X = L.AP;  // D (P - alpha D^-1 A P) on the pattern of A P, then D G
+  for (int i = 0; i < n; ++i)
+    for (int q = X.ptr[i]; q < X.ptr[i + 1]; ++q) X.val[q] = A.diag[i] * L.P_on_AP[q] - F.alpha * L.AP.val[q];
+  F.G = add_product(X, F.beta, W, &A.diag, L.AP, n2);
+  for (int i = 0; i < n; ++i)
+    for (int q = F.G.ptr[i]; q < F.G.ptr[i + 1]; ++q) F.G.val[q] /= A.diag[i];
+  return F;
+}
+
 }  // namespace difvm

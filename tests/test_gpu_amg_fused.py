@@ -1,0 +1,47 @@
+"""The V-cycle's passes over the level between the finest and the coarsest: two fused ones on meshes of at
+most 384 tiles whose dense product with the coarsest inverse has at most 2^22 entries, six otherwise.  The
+cycle stays symmetric positive definite in either form, and CG with it reaches the Jacobi solution; the
+meshes lie on both sides of each limit."""
+import numpy as np
+import pytest
+
+from paper_2603_15920_amd import binding as B
+from paper_2603_15920_amd import meshgen as mg
+from gpu_util import ctx, dev, empty, host, note
+
+pytestmark = pytest.mark.gpu
+
+# cells: 52,272 and 162,000 (fused), 235,824 (dense product too large), 407,208 (more than 384 tiles)
+BOXES = {"22x22x18": (22, 22, 18), "30x30x30": (30, 30, 30), "34x34x34": (34, 34, 34), "38x38x47": (38, 38, 47)}
+
+
+@pytest.mark.parametrize("name", BOXES)
+def test_cycle_symmetric_and_solves(name):
+    m = mg.kuhn_cube(1, jitter=0.15, patches="walls", seed=21, nxyz=BOXES[name])
+    M = B.Mesh(ctx(), m)
+    A = B.ldu(empty(m.n_cells), empty(m.n_internal_faces))
+    rhs = empty(m.n_cells)
+    B.difvm_ldu_assemble_laplace(M.h, B.BC_ALL_FIXED, None, dev(np.zeros(m.n_boundary_faces)), A, rhs)
+    amg = B.difvm_amg_create(M.h, A)
+    levels = B.difvm_amg_levels(amg)
+    note("cycle", name, levels)
+    assert len(levels) == 3
+    fused = -(-m.n_cells // 1024) <= 384 and levels[1] * levels[2] <= 1 << 22
+    assert fused == (name in ("22x22x18", "30x30x30"))
+    rng = np.random.default_rng(7)
+    x, y = rng.standard_normal((2, m.n_cells))
+    z = []
+    for v in (x, y):
+        out = empty(m.n_cells)
+        B.difvm_amg_apply(amg, dev(v), out)
+        z.append(host(out))
+    assert z[0] @ x > 0 and z[1] @ y > 0
+    assert abs(z[0] @ y - z[1] @ x) <= 1e-12 * np.linalg.norm(z[0]) * np.linalg.norm(y)
+    b = dev(rng.standard_normal(m.n_cells))
+    xa, xj = empty(m.n_cells).zero_(), empty(m.n_cells).zero_()
+    sa, ia, _ = B.difvm_solve_pcg_amg(amg, A, b, xa, 1e-12, 200)
+    sj, ij, _ = B.difvm_solve_pcg(M.h, A, b, xj, 1e-12, 20000)
+    note("iterations", ia, ij)
+    assert sa == 0 and sj == 0 and 4 * ia <= ij
+    assert np.abs(host(xa) - host(xj)).max() <= 1e-9 * np.abs(host(xj)).max()
+    B.difvm_amg_destroy(amg)
