@@ -24,6 +24,7 @@
 #include <cstring>
 
 #include "amg_dev.h"
+#include "host_rows.h"
 #include "krylov_util.h"
 
 namespace difvm {
@@ -645,6 +646,9 @@ constexpr int FUSE_LANES = 16;  // per row of level 1: its S row has some 90 ent
 
 }  // namespace
 
+// cells per thread of the copy of K to CSR (a cell takes about 50 ns, starting a thread 20 us)
+constexpr int CSR_ROWS = 8192;
+
 AmgDev* amg_create(difvm_mesh* m, SellMatrix K, const AmgOptions& opt) {
   const DMesh& d = m->d;
   const HostLayout& L = m->host;
@@ -658,24 +662,34 @@ AmgDev* amg_create(difvm_mesh* m, SellMatrix K, const AmgOptions& opt) {
   A0.n = d.nc;
   A0.ptr.assign(d.nc + 1, 0);
   A0.diag = diag;
-  std::vector<std::pair<int32_t, double>> row;
-  for (int i = 0; i < d.nc; ++i) {
+  auto each_slot = [&](int i, auto&& f) {
     int sl = i >> 6, base = L.slice_start[sl] + (i & (SLICE - 1));
     int width = (L.slice_start[sl + 1] - L.slice_start[sl]) >> 6;
-    row.clear();
     for (int k = 0; k < width; ++k) {
       int at = base + k * SLICE;
       int sf = L.slot_face[at];
-      if (sf == SLOT_PAD || sf >= d.nfi) continue;
-      row.push_back({L.slot_col[at], val[at]});
+      if (sf != SLOT_PAD && sf < d.nfi) f(at);
     }
-    std::sort(row.begin(), row.end());
-    for (auto& e : row) {
-      A0.col.push_back(e.first);
-      A0.val.push_back(e.second);
+  };
+  parallel_rows(d.nc, CSR_ROWS, [&](int, int a, int b) {
+    for (int i = a; i < b; ++i) each_slot(i, [&](int) { ++A0.ptr[i + 1]; });
+  });
+  for (int i = 0; i < d.nc; ++i) A0.ptr[i + 1] += A0.ptr[i];
+  A0.col.resize(A0.ptr[d.nc]);
+  A0.val.resize(A0.ptr[d.nc]);
+  parallel_rows(d.nc, CSR_ROWS, [&](int, int a, int b) {
+    std::vector<std::pair<int32_t, double>> row;
+    for (int i = a; i < b; ++i) {
+      row.clear();
+      each_slot(i, [&](int at) { row.push_back({L.slot_col[at], val[at]}); });
+      std::sort(row.begin(), row.end());
+      int q = A0.ptr[i];
+      for (auto& e : row) {
+        A0.col[q] = e.first;
+        A0.val[q++] = e.second;
+      }
     }
-    A0.ptr[i + 1] = (int32_t)A0.col.size();
-  }
+  });
   for (int i = 0; i < d.nc; ++i)
     DIFVM_CHECK(diag[i] > 0.0, DIFVM_ERR_INVALID_ARG, "AMG needs a matrix with a positive diagonal");
   AmgHierarchy H;

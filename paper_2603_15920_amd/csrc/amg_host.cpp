@@ -8,6 +8,7 @@
 // each V-cycle uses the current matrix, the coarser levels the stored Galerkin operators, so the
 // preconditioner stays symmetric positive definite for every solve.
 #include "amg.h"
+#include "host_rows.h"
 
 #include <algorithm>
 #include <cmath>
@@ -18,6 +19,69 @@
 namespace difvm {
 
 namespace {
+
+// Sparse accumulator for one row at a time: values summed per column, columns listed in ascending
+// order when the row is flushed (or as they came).
+struct SparseAcc {
+  std::vector<double> acc;
+  std::vector<int32_t> mark, touched;
+  int32_t stamp = 0;
+  explicit SparseAcc(int n) : acc(n, 0.0), mark(n, -1) {}
+  void add(int I, double v) {
+    if (mark[I] != stamp) {
+      mark[I] = stamp;
+      acc[I] = 0.0;
+      touched.push_back(I);
+    }
+    acc[I] += v;
+  }
+  template <class F>
+  void flush(F&& out, bool sorted = true) {
+    if (sorted) std::sort(touched.begin(), touched.end());
+    for (int I : touched) out(I, acc[I]);
+    touched.clear();
+    ++stamp;
+  }
+};
+
+// CSR rows 0..n-1 (ptr, col, val) over n_cols columns: row(i, acc) adds row i's entries, keep(i, column,
+// value) says whether an entry is stored
+constexpr int ROWS_PER_THREAD = 1024;
+template <class Row, class Keep>
+void build_rows(int n, int n_cols, AmgCsr& C, bool sorted, Row&& row, Keep&& keep) {
+  struct Part {
+    std::vector<int32_t> col;
+    std::vector<double> val;
+  };
+  std::vector<Part> part(n_chunks(n, ROWS_PER_THREAD));
+  C.n = n;
+  C.ptr.assign(n + 1, 0);
+  parallel_rows(n, ROWS_PER_THREAD, [&](int t, int a, int b) {
+    SparseAcc sa(n_cols);
+    Part& P = part[t];
+    for (int i = a; i < b; ++i) {
+      row(i, sa);
+      const size_t before = P.col.size();
+      sa.flush(
+          [&](int I, double v) {
+            if (!keep(i, I, v)) return;
+            P.col.push_back(I);
+            P.val.push_back(v);
+          },
+          sorted);
+      C.ptr[i + 1] = (int32_t)(P.col.size() - before);
+    }
+  });
+  for (int i = 0; i < n; ++i) C.ptr[i + 1] += C.ptr[i];
+  C.col.resize(C.ptr[n]);
+  C.val.resize(C.ptr[n]);
+  size_t at = 0;
+  for (const Part& P : part) {
+    std::copy(P.col.begin(), P.col.end(), C.col.begin() + at);
+    std::copy(P.val.begin(), P.val.end(), C.val.begin() + at);
+    at += P.col.size();
+  }
+}
 
 // strong couplings of row i: |a_ij| >= theta sqrt(d_i d_j)
 inline bool strong(double aij, double di, double dj, double theta) {
@@ -90,19 +154,27 @@ AmgCsr strong_square(const AmgCsr& A, double theta) {
   G.n = n;
   G.ptr.assign(n + 1, 0);
   G.diag.assign(n, 1.0);
-  std::vector<int32_t> mark(n, -1);
-  for (int i = 0; i < n; ++i) {
-    mark[i] = i;
-    for (int q = sp[i]; q < sp[i + 1]; ++q) {
-      int j = sc[q];
-      if (mark[j] != i) { mark[j] = i; G.col.push_back(j); }
-      for (int r = sp[j]; r < sp[j + 1]; ++r) {
-        int k = sc[r];
-        if (mark[k] != i) { mark[k] = i; G.col.push_back(k); }
+  std::vector<std::vector<int32_t>> part(n_chunks(n, ROWS_PER_THREAD));
+  parallel_rows(n, ROWS_PER_THREAD, [&](int t, int a, int b) {
+    std::vector<int32_t> mark(n, -1);
+    std::vector<int32_t>& out = part[t];
+    for (int i = a; i < b; ++i) {
+      const size_t before = out.size();
+      mark[i] = i;
+      for (int q = sp[i]; q < sp[i + 1]; ++q) {
+        int j = sc[q];
+        if (mark[j] != i) { mark[j] = i; out.push_back(j); }
+        for (int r = sp[j]; r < sp[j + 1]; ++r) {
+          int k = sc[r];
+          if (mark[k] != i) { mark[k] = i; out.push_back(k); }
+        }
       }
+      G.ptr[i + 1] = (int32_t)(out.size() - before);
     }
-    G.ptr[i + 1] = (int32_t)G.col.size();
-  }
+  });
+  for (int i = 0; i < n; ++i) G.ptr[i + 1] += G.ptr[i];
+  G.col.reserve(G.ptr[n]);
+  for (const auto& c : part) G.col.insert(G.col.end(), c.begin(), c.end());
   G.val.assign(G.col.size(), 1.0);
   return G;
 }
@@ -118,20 +190,25 @@ double spectral_radius_dinv_a(const AmgCsr& A, int iters) {
   const int n = A.n;
   std::vector<double> v(n), w(n);
   for (int i = 0; i < n; ++i) v[i] = 1.0 + 0.5 * std::sin(0.7 * i + 0.3);  // deterministic, not constant
-  double lam = 0.0;
+  double lam = 0.0, nv = 0.0;
+  for (int i = 0; i < n; ++i) nv += v[i] * v[i];
   for (int it = 0; it < iters; ++it) {
-    double nv = 0.0;
-    for (int i = 0; i < n; ++i) nv += v[i] * v[i];
     nv = std::sqrt(nv);
     if (nv == 0.0) return 1.0;
     for (int i = 0; i < n; ++i) v[i] /= nv;
-    for (int i = 0; i < n; ++i) {
-      double s = A.diag[i] * v[i];
-      for (int q = A.ptr[i]; q < A.ptr[i + 1]; ++q) s += A.val[q] * v[A.col[q]];
-      w[i] = s / A.diag[i];
-    }
+    parallel_rows(n, 16384, [&](int, int a, int b) {
+      for (int i = a; i < b; ++i) {
+        double s = A.diag[i] * v[i];
+        for (int q = A.ptr[i]; q < A.ptr[i + 1]; ++q) s += A.val[q] * v[A.col[q]];
+        w[i] = s / A.diag[i];
+      }
+    });
     double num = 0.0;
-    for (int i = 0; i < n; ++i) num += v[i] * w[i];
+    nv = 0.0;  // of the next iteration
+    for (int i = 0; i < n; ++i) {
+      num += v[i] * w[i];
+      nv += w[i] * w[i];
+    }
     lam = num;
     v.swap(w);
   }
@@ -157,30 +234,6 @@ AmgCsr transpose(const AmgCsr& P, int m) {
     }
   return R;
 }
-
-// Sparse accumulator for one row at a time: values summed per column, columns listed in ascending
-// order when the row is flushed.
-struct SparseAcc {
-  std::vector<double> acc;
-  std::vector<int32_t> mark, touched;
-  int32_t stamp = 0;
-  explicit SparseAcc(int n) : acc(n, 0.0), mark(n, -1) {}
-  void add(int I, double v) {
-    if (mark[I] != stamp) {
-      mark[I] = stamp;
-      acc[I] = 0.0;
-      touched.push_back(I);
-    }
-    acc[I] += v;
-  }
-  template <class F>
-  void flush(F&& out) {
-    std::sort(touched.begin(), touched.end());
-    for (int I : touched) out(I, acc[I]);
-    touched.clear();
-    ++stamp;
-  }
-};
 
 }  // namespace
 
@@ -212,76 +265,57 @@ static bool coarsen(const AmgCsr& A, const std::vector<double>& B, double theta,
     }
     L.hi = std::min(g, 1.1 * std::max(1.0, spectral_radius_dinv_a(A, 50)));
   }
+  auto all = [](int, int, double) { return true; };
   AmgCsr& P = L.P;
-  P.n = n;
-  P.ptr.assign(n + 1, 0);
-  P.col.clear();
-  P.val.clear();
-  SparseAcc sa(na);
-  for (int i = 0; i < n; ++i) {
-    double s = w / A.diag[i];
-    sa.add(agg[i], tent[i] - s * A.diag[i] * tent[i]);
-    for (int q = A.ptr[i]; q < A.ptr[i + 1]; ++q) {
-      int j = A.col[q];
-      sa.add(agg[j], -s * A.val[q] * tent[j]);
-    }
-    sa.flush([&](int I, double v) {
-      P.col.push_back(I);
-      P.val.push_back(v);
-    });
-    P.ptr[i + 1] = (int32_t)P.col.size();
-  }
+  build_rows(
+      n, na, P, true,
+      [&](int i, SparseAcc& sa) {
+        double s = w / A.diag[i];
+        sa.add(agg[i], tent[i] - s * A.diag[i] * tent[i]);
+        for (int q = A.ptr[i]; q < A.ptr[i + 1]; ++q) {
+          int j = A.col[q];
+          sa.add(agg[j], -s * A.val[q] * tent[j]);
+        }
+      },
+      all);
   L.R = transpose(P, na);
   // A P by fine rows (A = diag + off-diagonals)
-  std::vector<int32_t> ap_ptr(n + 1, 0), ap_col;
-  std::vector<double> ap_val;
-  for (int i = 0; i < n; ++i) {
-    for (int q = P.ptr[i]; q < P.ptr[i + 1]; ++q) sa.add(P.col[q], A.diag[i] * P.val[q]);
-    for (int q = A.ptr[i]; q < A.ptr[i + 1]; ++q) {
-      int j = A.col[q];
-      for (int r = P.ptr[j]; r < P.ptr[j + 1]; ++r) sa.add(P.col[r], A.val[q] * P.val[r]);
-    }
-    sa.flush([&](int I, double v) {
-      ap_col.push_back(I);
-      ap_val.push_back(v);
-    });
-    ap_ptr[i + 1] = (int32_t)ap_col.size();
-  }
-  if (with_ap) {
-    L.AP.n = n;
-    L.AP.ptr = ap_ptr;
-    L.AP.col = ap_col;
-    L.AP.val = ap_val;
-    L.P_on_AP.assign(ap_val.size(), 0.0);
-    for (int i = 0; i < n; ++i) {
-      int q = P.ptr[i];
-      for (int k = ap_ptr[i]; k < ap_ptr[i + 1] && q < P.ptr[i + 1]; ++k)
-        if (P.col[q] == ap_col[k]) L.P_on_AP[k] = P.val[q++];
-      if (q != P.ptr[i + 1]) throw AmgError{"prolongator pattern not inside that of A P"};
-    }
-  }
+  AmgCsr AP;
+  build_rows(
+      n, na, AP, true,
+      [&](int i, SparseAcc& sa) {
+        for (int q = P.ptr[i]; q < P.ptr[i + 1]; ++q) sa.add(P.col[q], A.diag[i] * P.val[q]);
+        for (int q = A.ptr[i]; q < A.ptr[i + 1]; ++q) {
+          int j = A.col[q];
+          for (int r = P.ptr[j]; r < P.ptr[j + 1]; ++r) sa.add(P.col[r], A.val[q] * P.val[r]);
+        }
+      },
+      all);
   // A_c = R (A P) by coarse rows
-  Ac.n = na;
-  Ac.ptr.assign(na + 1, 0);
-  Ac.col.clear();
-  Ac.val.clear();
   Ac.diag.assign(na, 0.0);
   const AmgCsr& R = L.R;
-  for (int I = 0; I < na; ++I) {
-    for (int q = R.ptr[I]; q < R.ptr[I + 1]; ++q) {
-      int i = R.col[q];
-      double r = R.val[q];
-      for (int s2 = ap_ptr[i]; s2 < ap_ptr[i + 1]; ++s2) sa.add(ap_col[s2], r * ap_val[s2]);
+  build_rows(
+      na, na, Ac, true,
+      [&](int I, SparseAcc& sa) {
+        for (int q = R.ptr[I]; q < R.ptr[I + 1]; ++q) {
+          int i = R.col[q];
+          double r = R.val[q];
+          for (int s2 = AP.ptr[i]; s2 < AP.ptr[i + 1]; ++s2) sa.add(AP.col[s2], r * AP.val[s2]);
+        }
+      },
+      [&](int I, int J, double v) {
+        if (J == I) Ac.diag[I] = v;
+        return J != I;
+      });
+  if (with_ap) {
+    L.P_on_AP.assign(AP.val.size(), 0.0);
+    for (int i = 0; i < n; ++i) {
+      int q = P.ptr[i];
+      for (int k = AP.ptr[i]; k < AP.ptr[i + 1] && q < P.ptr[i + 1]; ++k)
+        if (P.col[q] == AP.col[k]) L.P_on_AP[k] = P.val[q++];
+      if (q != P.ptr[i + 1]) throw AmgError{"prolongator pattern not inside that of A P"};
     }
-    sa.flush([&](int J, double v) {
-      if (J == I) {
-        Ac.diag[I] = v;
-      } else {
-        Ac.col.push_back(J);
-        Ac.val.push_back(v);
-      }
-    });
-    Ac.ptr[I + 1] = (int32_t)Ac.col.size();
+    L.AP = std::move(AP);
   }
   // exact symmetry: a_IJ and a_JI replaced by their mean (rounding made them differ in the last bits)
   AmgCsr T = transpose(Ac, na);
@@ -342,32 +376,18 @@ Cheb cheb_coefficients(double lo, double hi) {
 static AmgCsr add_product(const AmgCsr& X, double s, const AmgCsr& Y, const std::vector<double>* d, const AmgCsr& Z,
                           int n_cols) {
   AmgCsr C;
-  C.n = Y.n;
-  C.ptr.assign(1, 0);
-  C.col.reserve(X.col.size());
-  C.val.reserve(X.col.size());
-  std::vector<double> acc(n_cols, 0.0);
-  std::vector<int32_t> mark(n_cols, -1);
-  for (int i = 0; i < Y.n; ++i) {
-    const size_t first = C.col.size();
-    auto add = [&](int c, double v) {
-      if (mark[c] != i) {
-        mark[c] = i;
-        acc[c] = 0.0;
-        C.col.push_back(c);
-      }
-      acc[c] += v;
-    };
-    if (X.n)
-      for (int q = X.ptr[i]; q < X.ptr[i + 1]; ++q) add(X.col[q], X.val[q]);
-    for (int q = Y.ptr[i]; q < Y.ptr[i + 1]; ++q) {
-      const int j = Y.col[q];
-      const double y = s * Y.val[q] / (d ? (*d)[j] : 1.0);
-      for (int r = Z.ptr[j]; r < Z.ptr[j + 1]; ++r) add(Z.col[r], y * Z.val[r]);
-    }
-    for (size_t k = first; k < C.col.size(); ++k) C.val.push_back(acc[C.col[k]]);
-    C.ptr.push_back((int32_t)C.col.size());
-  }
+  build_rows(
+      Y.n, n_cols, C, false,
+      [&](int i, SparseAcc& sa) {
+        if (X.n)
+          for (int q = X.ptr[i]; q < X.ptr[i + 1]; ++q) sa.add(X.col[q], X.val[q]);
+        for (int q = Y.ptr[i]; q < Y.ptr[i + 1]; ++q) {
+          const int j = Y.col[q];
+          const double y = s * Y.val[q] / (d ? (*d)[j] : 1.0);
+          for (int r = Z.ptr[j]; r < Z.ptr[j + 1]; ++r) sa.add(Z.col[r], y * Z.val[r]);
+        }
+      },
+      [](int, int, double) { return true; });
   return C;
 }
 

@@ -1,0 +1,48 @@
+// Row-independent host loops on a few threads.
+#pragma once
+
+#include <algorithm>
+#include <exception>
+#include <system_error>
+#include <thread>
+#include <vector>
+
+namespace difvm {
+
+// f(chunk, first, last) over consecutive chunks of n rows, at least per_thread rows each, on at most eight
+// threads (the caller's among them).  Rows are independent, so what a row computes does not depend on
+// the chunks.  The first exception of any chunk is rethrown here; where no thread can be started its chunk
+// runs on the caller's.
+constexpr int MAX_CHUNKS = 8;
+inline int n_chunks(int n, int per_thread) {
+  int hw = (int)std::thread::hardware_concurrency();
+  return std::max(1, std::min({n / per_thread, MAX_CHUNKS, hw > 0 ? hw : 1}));
+}
+template <class F>
+void parallel_rows(int n, int per_thread, F&& f) {
+  const int T = n_chunks(n, per_thread);
+  std::exception_ptr err[MAX_CHUNKS];
+  auto run = [&](int t) {
+    try {
+      f(t, (int)((long long)n * t / T), (int)((long long)n * (t + 1) / T));
+    } catch (...) {
+      err[t] = std::current_exception();
+    }
+  };
+  std::vector<std::thread> th;
+  th.reserve(T);
+  std::vector<int> here = {0};
+  for (int t = 1; t < T; ++t) {
+    try {
+      th.emplace_back(run, t);
+    } catch (const std::system_error&) {
+      here.push_back(t);
+    }
+  }
+  for (int t : here) run(t);
+  for (auto& x : th) x.join();
+  for (int t = 0; t < T; ++t)
+    if (err[t]) std::rethrow_exception(err[t]);
+}
+
+}  // namespace difvm
