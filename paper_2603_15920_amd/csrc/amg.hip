@@ -124,7 +124,7 @@ __device__ __forceinline__ bool stopped(int flags) { return __all(flags) != 0; }
 // last iteration the rest of the cycle returns at once.
 struct CycleTest {
   PcgCtl* ctl;
-  const double* rr;
+  double* rr;
   int k, nseg;
   int blocks;  // the launch's first blocks (a multiple of 8, so that the others keep their XCDs)
 };
@@ -245,15 +245,19 @@ __device__ __forceinline__ double sell_offdiag(const SellView& K, int i, SlotRan
   SlotRange R = slots_of(K, I);                           \
   if (!LATE && (stopped(flags) || !in)) return
 
+// the stopping test in the kernel's first blocks (LATE and quarter-tile partials go together: fine_spans)
+#define DIFVM_AMG_TEST                 \
+  if ((int)blockIdx.x < test.blocks) { \
+    test_iterate<LATE>(test, T);       \
+    return;                            \
+  }
+
 // level 0, down, first pass (x = 0, b = r): xs = d0 + d1, with d0 = D^-1 r / theta
 template <bool OFF16, bool LATE>
 __global__ __launch_bounds__(BLOCK) void k_amg_cheb_pre1(SellView K, Tiles T, CycleTest test,
                                                          const double* __restrict__ r, double* __restrict__ xs, Cheb c,
                                                          StopFlags ctl) {
-  if ((int)blockIdx.x < test.blocks) {
-    test_iterate<LATE>(test, T);  // LATE and quarter-tile partials go together (fine_spans)
-    return;
-  }
+  DIFVM_AMG_TEST;
   int i = xcd_tile(blockIdx.x - test.blocks, gridDim.x - test.blocks) * BLOCK + threadIdx.x;
   DIFVM_AMG_CELL(i);
   double di = K.diag[i], rh0 = r[i] / di;
@@ -263,12 +267,71 @@ __global__ __launch_bounds__(BLOCK) void k_amg_cheb_pre1(SellView K, Tiles T, Cy
   if (!LATE || (!stopped(flags) && in)) xs[i] = d0 + (c.c_d * d0 + c.c_r * rh1);
 }
 
+// The same on meshes of few tiles (fine_spans), joined with the update of the CG iteration before it: x and r, the
+// partials of r.r, xs.  Each cell makes its neighbours' new residuals again from the old ones (the same
+// operations, so the same bits) instead of waiting for a kernel that stores them, which is why r goes to a
+// second array.  12 gathers per cell instead of 8, and a launch less: there an iteration's time is its launches
+// and each kernel's chain of loads.  A segment that has stopped hands its r on.
+// Per CG iteration, separate kernels -> joint: 48,000 cells 41.6 -> 38.9 us, 93,750 47.7 -> 44.4, 384,000 77.0 -> 75.0.
+template <bool OFF16>
+__global__ __launch_bounds__(QUARTER) void k_amg_step_pre1(SellView K, Tiles T, CgStep st, double* __restrict__ xs,
+                                                           double* __restrict__ rr, int k, Cheb c, PcgCtl* ctls) {
+  constexpr int W = 4;
+  const Span ti = span_of<true>(T);
+  PcgCtl* ctl = ctls + ti.s;
+  const bool done = ctl->done != 0;
+  const double rho = ctl->rho[(k - 1) & 1];
+  const int i0 = ti.lo + (int)threadIdx.x, i = min(i0, ti.end - 1);
+  const SlotRange R = slots_of(K, i);
+  const double xi = st.x[i], pi = st.p[i], r_i = st.r[i], q_i = st.q[i], di = K.diag[i];
+  double a[W], rj[W], qj[W], dj[W];
+  const int n0 = min(R.width, W);
+  if (n0 > 0) {
+    int j[W];
+#pragma unroll
+    for (int s = 0; s < W; ++s) {
+      const int at = R.base + (s < n0 ? s : 0) * SLICE;  // past n0 the first slot again, not added
+      a[s] = K.val[at];
+      j[s] = slot_col_of<OFF16>(K, i, at);
+    }
+#pragma unroll
+    for (int s = 0; s < W; ++s) {
+      rj[s] = st.r[j[s]];
+      qj[s] = st.q[j[s]];
+      dj[s] = K.diag[j[s]];
+    }
+  }
+  double pq[1];
+  seg_totals<1, QUARTER, true>(st.pq, T.ntile, seg_first(T, ti.s), seg_count(T, ti.s), pq);
+  const double alpha = rho / pq[0];
+  auto residual = [&](double ro, double qo) { return done ? ro : __builtin_fma(-alpha, qo, ro); };
+  const double ri = residual(r_i, q_i);
+  double acc = 0.0;
+#pragma unroll
+  for (int s = 0; s < W; ++s)
+    if (s < n0) acc += a[s] * (residual(rj[s], qj[s]) / dj[s] * c.inv_theta);
+  for (int s = W; s < R.width; ++s) {
+    const int at = R.base + s * SLICE, j = slot_col_of<OFF16>(K, i, at);
+    acc += K.val[at] * (residual(st.r[j], st.q[j]) / K.diag[j] * c.inv_theta);
+  }
+  double v[1] = {0.0};
+  if (i0 < ti.hi) {
+    const double rh0 = ri / di, d0 = rh0 * c.inv_theta, rh1 = rh0 - (di * d0 + acc) / di;
+    if (!done) st.x[i] = __builtin_fma(alpha, pi, xi);
+    st.r_new[i] = ri;
+    xs[i] = d0 + (c.c_d * d0 + c.c_r * rh1);
+    v[0] = ri * ri;
+  }
+  put_partial<1, QUARTER, true>(v, rr, T.ntile, ti);
+}
+
 // level 0, down, second pass: res = r - K xs
 template <bool OFF16, bool LATE>
-__global__ __launch_bounds__(BLOCK) void k_amg_cheb_pre2(SellView K, const double* __restrict__ r,
+__global__ __launch_bounds__(BLOCK) void k_amg_cheb_pre2(SellView K, Tiles T, CycleTest test, const double* __restrict__ r,
                                                          const double* __restrict__ xs, double* __restrict__ res,
                                                          StopFlags ctl) {
-  int i = xcd_tile(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x;
+  DIFVM_AMG_TEST;
+  int i = xcd_tile(blockIdx.x - test.blocks, gridDim.x - test.blocks) * BLOCK + threadIdx.x;
   DIFVM_AMG_CELL(i);
   const double ri = r[i];
   double kx = K.diag[i] * xs[i] + sell_offdiag<OFF16>(K, i, R, [&](int j) { return xs[j]; });
@@ -821,7 +884,7 @@ double amg_vcycle_bytes(const AmgDev* a) {
 
 template <bool LATE>
 static void launch_vcycle(const AmgDev* a, hipStream_t s, SellMatrix Km, const double* r, double* z, double* part,
-                          StopFlags ctl, CycleTest test) {
+                          StopFlags ctl, CycleTest test, const CgStep* step) {
   difvm_mesh* m = a->mesh;
   SellView K = sview(m, Km);
   const int L = a->L, nc = m->d.nc;
@@ -830,10 +893,17 @@ static void launch_vcycle(const AmgDev* a, hipStream_t s, SellMatrix Km, const d
   const Tiles T = tiles_of(m);
   const int G = grid_for(nc);
   // down
-  (K.off16 ? k_amg_cheb_pre1<true, LATE> : k_amg_cheb_pre1<false, LATE>)<<<G + test.blocks, BLOCK, 0, s>>>(
-      K, T, test, r, a->xs[0], c[0], ctl);
-  (K.off16 ? k_amg_cheb_pre2<true, LATE> : k_amg_cheb_pre2<false, LATE>)<<<G, BLOCK, 0, s>>>(K, r, a->xs[0], a->res[0],
-                                                                                             ctl);
+  const CycleTest none{};
+  if (step)
+    (K.off16 ? k_amg_step_pre1<true> : k_amg_step_pre1<false>)<<<n_spans(m), QUARTER, 0, s>>>(
+        K, T, *step, a->xs[0], test.rr, test.k, c[0], test.ctl);
+  else
+    (K.off16 ? k_amg_cheb_pre1<true, LATE> : k_amg_cheb_pre1<false, LATE>)<<<G + test.blocks, BLOCK, 0, s>>>(
+        K, T, test, r, a->xs[0], c[0], ctl);
+  // after the joint kernel the test is here: it needs every block's partials of r.r
+  const CycleTest& t2 = step ? test : none;
+  (K.off16 ? k_amg_cheb_pre2<true, LATE> : k_amg_cheb_pre2<false, LATE>)<<<G + t2.blocks, BLOCK, 0, s>>>(
+      K, T, t2, r, a->xs[0], a->res[0], ctl);
   if (a->S.n) {
     // level 1 and the coarsest in two passes
     const DevCsr &R = a->R[0], &A = a->A[1], &S = a->S, &Q = a->RS;
@@ -880,7 +950,7 @@ static void launch_vcycle(const AmgDev* a, hipStream_t s, SellMatrix Km, const d
 }
 
 void amg_vcycle(const AmgDev* a, SellMatrix Km, const double* r, double* z, double* part, PcgCtl* ctls,
-                const double* rr, int k) {
+                double* rr, int k, const CgStep* step) {
   difvm_mesh* m = a->mesh;
   const int nseg = m->d.nseg;
   const CycleTest test{ctls, rr, k, nseg, rr ? std::min(64, (nseg + 7) & ~7) : 0};
@@ -888,7 +958,7 @@ void amg_vcycle(const AmgDev* a, SellMatrix Km, const double* r, double* z, doub
   // host queues a cycle in well under one iteration's GPU time, and a replayed graph of the cycle
   // cost about 9 us of idle GPU between its end and the next kernel on the stream
   (fine_spans(m) ? launch_vcycle<true> : launch_vcycle<false>)(a, ctx_of(m).stream, Km, r, z, part, StopFlags{ctls, nseg},
-                                                               test);
+                                                               test, step);
 }
 
 }  // namespace difvm

@@ -10,6 +10,14 @@ namespace difvm {
 struct PcgCtl;
 struct AmgDev;
 
+// The update of a CG iteration, made by the first kernel of the cycle after it: with alpha from the segment's
+// p.q partials (pq), x += alpha p and r_new = r - alpha q.
+struct CgStep {
+  double* x;
+  const double *p, *r, *q, *pq;
+  double* r_new;
+};
+
 // Builds the hierarchy from the symmetric cell-slot matrix K (copied to the host; synchronises) and
 // uploads it.  No face joins two segments, so no aggregate does either and every level stays
 // block-diagonal over the segments.  Throws Error.
@@ -21,9 +29,10 @@ void amg_free(AmgDev* a);
 // ctl != nullptr (the per-segment CG states): every kernel returns at once when all segments have
 // stopped (iterations queued after the stop).  rr != nullptr: the first kernel also makes the stopping test
 // of CG iterate k, whose r.r partials these are (as the product of iteration k + 1 does), so that the
-// cycle after the last iteration ends there.
+// cycle after the last iteration ends there.  step != nullptr (with rr, on meshes of fine_spans): the first kernel
+// also makes iteration k's update, storing r (= step->r_new) and the partials rr, and the second makes the test.
 void amg_vcycle(const AmgDev* a, SellMatrix K, const double* r, double* z, double* part, PcgCtl* ctl,
-                const double* rr = nullptr, int k = 0);
+                double* rr = nullptr, int k = 0, const CgStep* step = nullptr);
 // rows per level (finest first) into rows[0..cap); returns the number of levels
 int amg_levels(const AmgDev* a, int* rows, int cap);
 // Algorithmic bytes of one V-cycle: every kernel's distinct inputs read once and outputs written

@@ -834,6 +834,7 @@ SolveResult pcg(difvm_mesh* m, SellMatrix A, const double* b, double* x, double 
   const int GS = pcg_spmv_launch_grid(m);
   const bool fine = fine_spans(m);
   const int NP = n_spans(m), NTB = fine ? QUARTER : TILE;  // partials of one value; threads of the init kernels
+  double* Rk[2] = {w->r, w->rh};  // r_k at parity k & 1 (joint), else r
   double* r = w->r;
   double* q = w->q;
   double* z = w->z;
@@ -849,10 +850,10 @@ SolveResult pcg(difvm_mesh* m, SellMatrix A, const double* b, double* x, double 
   // launch is being timed the product makes it and every timed cycle is a whole one
   const Profiler& prof = ctx_of(m).prof;
   const bool cycle_test = !(prof.on && prof.stride == 1);
-  auto precondition = [&](int kk) {
+  auto precondition = [&](int kk, const CgStep* step = nullptr) {
     if (!amg) return;
     ProfScope ps(m, "pcg_amg_vcycle", cycle_test ? kk + 1 : kk);  // a whole cycle if iteration kk + 1 runs
-    amg_vcycle(amg, A, r, z, partB + NP, w->pcg, cycle_test && kk > 0 ? partB : nullptr, kk);
+    amg_vcycle(amg, A, step ? step->r_new : r, z, partB + NP, w->pcg, cycle_test && kk > 0 ? partB : nullptr, kk, step);
   };
   (fine ? k_pcg_init1<true> : k_pcg_init1<false>)<<<NP, NTB, 0, s>>>(V, T, b, x, r, part0);
   (amg ? fine ? k_pcg_init2<false, true> : k_pcg_init2<false, false>
@@ -860,7 +861,15 @@ SolveResult pcg(difvm_mesh* m, SellMatrix A, const double* b, double* x, double 
                                                                                         w->pcg);
   DIFVM_HIP(hipGetLastError());
   precondition(0);
+  // on meshes of few tiles the update is made by the cycle's first kernel (while kernels are being timed by
+  // name, by its own: the same results)
+  const bool joint = amg && fine && !prof.on;
   auto update = [&](int kk) {
+    if (joint) {
+      const CgStep step{x, Pk[kk & 1], Rk[(kk - 1) & 1], q, partA, Rk[kk & 1]};
+      precondition(kk, &step);
+      return;
+    }
     {
       ProfScope ps(m, "pcg_update_dot", kk);
       auto kernel = fine ? (amg ? k_pcg_update<false, true> : k_pcg_update<true, true>)

@@ -45,3 +45,42 @@ def test_cycle_symmetric_and_solves(name):
     assert sa == 0 and sj == 0 and 4 * ia <= ij
     assert np.abs(host(xa) - host(xj)).max() <= 1e-9 * np.abs(host(xj)).max()
     B.difvm_amg_destroy(amg)
+
+
+# one tile and five; members that stop at different iterations, one before the first; the largest mesh of quarter-tile blocks
+# (384 tiles) and the next one; hexahedra (rows of six slots); iteration caps
+@pytest.mark.parametrize("name", ["kuhn5", "kuhn9", "members", "hex", "384 tiles", "385 tiles"])
+@pytest.mark.parametrize("maxit", [1, 4, 200])
+def test_joint_update_matches_separate(name, maxit):
+    """the CG update inside the cycle's first kernel and as a kernel of its own (taken while kernels are timed
+    by name): equal iterations and status, iterates equal up to rounding carried through the iterations"""
+    lap = lambda n: mg.kuhn_cube(n, jitter=0.1, patches="walls", seed=5)
+    m = {"kuhn5": lambda: lap(5), "kuhn9": lambda: lap(9), "hex": lambda: mg.hex_box(14, 13, 12),
+         "members": lambda: mg.pack([lap(8), lap(5), lap(9)]),
+         "384 tiles": lambda: mg.kuhn_cube(1, patches="walls", nxyz=(32, 32, 64)),
+         "385 tiles": lambda: mg.kuhn_cube(1, patches="walls", nxyz=(27, 27, 90))}[name]()
+    m, starts = m if name == "members" else (m, None)
+    cx = ctx()
+    M = B.Mesh(cx, m, seg_cell_start=starts)
+    A = B.ldu(empty(m.n_cells), empty(m.n_internal_faces))
+    B.difvm_ldu_assemble_laplace(M.h, B.BC_ALL_FIXED, None, dev(np.zeros(m.n_boundary_faces)), A, empty(m.n_cells))
+    amg = B.difvm_amg_create(M.h, A)
+    rng = np.random.default_rng(3)
+    bh = rng.standard_normal(m.n_cells)
+    x0 = 0.1 * rng.standard_normal(m.n_cells)
+    if starts is not None:
+        bh[starts[1]:starts[2]] = 0.0  # stops before the first iteration
+    out = []
+    for timed in (0, 7):
+        x = dev(x0)
+        B.difvm_ctx_profile(cx.h, timed)
+        st, it, res = B.difvm_solve_pcg_amg(amg, A, dev(bh), x, 1e-10, maxit)
+        B.difvm_ctx_profile_read(cx.h)
+        B.difvm_ctx_profile(cx.h, 0)
+        out.append((st, it, res, host(x)))
+    (sa, ia, ra, xa), (sb, ib, rb, xb) = out
+    note("joint", name, maxit, ia, ra, rb)
+    assert (sa, ia) == (sb, ib)
+    assert abs(ra - rb) <= 1e-6 * rb
+    assert np.abs(xa - xb).max() <= 1e-11 * np.abs(xb).max()
+    B.difvm_amg_destroy(amg)
