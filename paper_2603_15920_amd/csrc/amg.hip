@@ -37,6 +37,24 @@ struct DevCsr {
   double *val = nullptr, *diag = nullptr;
   double* val2 = nullptr;  // A P: P's values on its pattern
 };
+// Transfers laid out for a solve in one block (k_amg_pcg_block).
+constexpr int BLOCK_COARSE = 384, BLOCK_NT = 512, BLOCK_R_LANES = 2, BLOCK_R_FOURS = 4;
+constexpr int BLOCK_R_ROWS = BLOCK_NT / BLOCK_R_LANES, BLOCK_R_PASSES = (BLOCK_COARSE + BLOCK_R_ROWS - 1) / BLOCK_R_ROWS;
+// P: the first four entries of row i as columns pcol[i] and values pval[i], pval[4 TILE + i] (rows past the last:
+// zeros).  R: pass r takes the rows r BLOCK_R_ROWS ..., thread t its row t / BLOCK_R_LANES,
+// every BLOCK_R_LANES-th four entries from t % BLOCK_R_LANES; fours e of thread t: columns at (first[r] + e) BLOCK_NT + t,
+// values there with twice the first index (padded with zeros).  inv: leading dimension ld, padded.
+struct AmgBlock {
+  int n2 = 0;  // coarsest rows (0: not built)
+  int ld = 0;
+  ushort4 *pcol = nullptr, *rcol = nullptr;
+  double2 *pval = nullptr, *rval = nullptr, *inv = nullptr;
+  int nlong = 0;  // rows of P with more than four entries: row, then CSR of the others
+  int32_t *lrow = nullptr, *lptr = nullptr, *lcol = nullptr;
+  double* lval = nullptr;
+  int first[BLOCK_R_PASSES + 1] = {};
+  Cheb c{};
+};
 }  // namespace
 
 struct AmgDev {
@@ -54,6 +72,7 @@ struct AmgDev {
   DevCsr S, RS;
   double* H = nullptr;
   double alpha = 0.0, beta = 0.0;
+  AmgBlock block;
   std::vector<int> rows;
   std::vector<void*> allocs;
 };
@@ -622,6 +641,296 @@ __global__ __launch_bounds__(BLOCK) void k_amg_coarsest(int n, const double* __r
   }
 }
 
+// ---------------------------------------------------------------------------------------------
+// AMG-CG of a small mesh (one segment of at most four tiles, uniform rows of three or four slots, two levels, at
+// most BLOCK_COARSE coarse rows), the whole solve in one block and launch, as k_pcg_segment does for Jacobi-CG: K's
+// rows, the diagonal, r and p in registers (thread tid holds cells tid + c BLOCK_NT), x in LDS, the vector that a
+// product gathers in LDS too, in two arrays by turns so that one barrier parts two passes.  An iteration is
+// twelve barriers and three reductions instead of eight kernels.  What does not fit is read from L2 in every cycle,
+// R and the coarse inverse (with more than four cells per thread P too): one compute unit gets 55 bytes a cycle
+// by loads of 16 bytes per lane (30 by loads of 8) and 600 ns pass between a load and its use, so all of
+// it is laid out again for whole 1 KB loads (AmgBlock) and taken several loads at a time.  The inverse grows with
+// the square of its rows and bounds the largest of these meshes (8.9k of 39k cycles at 222 rows, 16.6k at 336).
+// Per iteration in us, eight launches -> this: 968 prisms 33 -> 6.3, 2,048 prisms 34 -> 8.0, 3,872 prisms (336 coarse
+// rows) 34 -> 17, 1,296 tets 33 -> 7.9, 3,888 tets 34 -> 16.  Replayed from a graph, ten PISO steps of
+// 968 / 1,922 / 2,178 / 4,050 prisms 7.4 / 7.9 / 7.9 / 8.6 -> 3.0 / 3.6 / 4.6 / 6.9 ms.  With rows of any length (hexahedra),
+// read from L2 in each of the five products, it took 24 us at 1,728 cells and 47 at 4,096 against 35: they take
+// the eight launches, and so do more coarse rows (at 512 their reads alone are 16 us).
+// A launch makes at most `chunk` iterations; what a further launch needs is stored when it ends unconverged.
+// ---------------------------------------------------------------------------------------------
+// acc + the four products of values a, b and entries j of f
+__device__ __forceinline__ double four(double2 a, double2 b, ushort4 j, const double* f, double acc) {
+  acc = __builtin_fma(a.x, f[j.x], acc);
+  acc = __builtin_fma(a.y, f[j.y], acc);
+  acc = __builtin_fma(b.x, f[j.z], acc);
+  return __builtin_fma(b.y, f[j.w], acc);
+}
+
+// barrier that orders LDS alone: loads from memory stay in flight over it (what the waves share between two barriers
+// is in LDS)
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+template <int C, int W>
+__global__ __launch_bounds__(BLOCK_NT) void k_amg_pcg_block(SellView K, int nt, AmgBlock M, const double* __restrict__ b,
+                                                      double* __restrict__ x, double* __restrict__ rbuf,
+                                                      double* __restrict__ pbuf, int chunk, PcgCtl* ctl) {
+  constexpr int NT = BLOCK_NT, NTILE = NT * C / TILE, WAVES = NT / 64;
+  static_assert(NTILE <= 4, "the tiles' sums fill one wave");
+  __shared__ double va[C * NT], vb[C * NT], xs[C * NT], bc[BLOCK_COARSE], xc[BLOCK_COARSE], gs[2][64];
+  __shared__ double2 xp[NT];
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, n = K.nc;
+  if (ctl->done) return;
+  const double tol = ctl->tol;
+  const int maxit = ctl->maxit, k0 = ctl->next;
+  double r[C], p[C], d[C], di[C];  // di: 1 / d
+  // totals of NV values per cell (in the order of k_pcg_segment's); gs may be written again after the next barrier
+  auto totals = [&](auto&& v, auto& tot) {
+    constexpr int NV = sizeof(tot) / sizeof(double);
+    wave_sums<NV * C>([&](int e) { return e % C * NT + tid < n ? v(e / C, e % C) : 0.0; },
+                      [&](int e, double sum) { gs[e / C][e % C * WAVES + wid] = sum; });
+    lds_barrier();
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      double t = row_sum(gs[k][lane]);
+      if (lane / TILE_WAVES >= nt) t = 0.0;
+      t = swap_add16(t, t);
+      tot[k] = wave_first(NTILE > 2 ? swap_add32(t, t) : t);
+    }
+  };
+  double av[C][W];
+  int jv[C][W];
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    // cells past the last: an empty row, so that no branch is needed for them
+    const int i = c * NT + tid;
+    const bool in = i < n;
+    const int ii = in ? i : 0, base = (ii >> 6) * (SLICE * W) + (ii & (SLICE - 1));  // uniform rows
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+      const double a = K.val[base + k * SLICE];
+      const int j = K.off16[base + k * SLICE];
+      av[c][k] = in ? a : 0.0;
+      jv[c][k] = i + (in ? j : 0);
+    }
+    xs[i] = in ? x[i] : 0.0;  // only this thread's entries are read
+    d[c] = in ? K.diag[i] : 1.0;
+    di[c] = 1.0 / d[c];
+    r[c] = in && k0 > 0 ? rbuf[i] : 0.0;
+    p[c] = in && k0 > 0 ? pbuf[i] : 0.0;
+  }
+  // out(c, off-diagonal part of row c applied to the vector f in LDS) for this thread's cells
+  auto rows = [&](const double* f, auto&& out) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      double acc = 0.0;
+#pragma unroll
+      for (int k = 0; k < W; ++k) acc = __builtin_fma(av[c][k], f[jv[c][k]], acc);
+      out(c, acc);
+    }
+  };
+  const Cheb ch = M.c;
+  double z[C], rho, rho_old = 0.0, bn, one[1], two[2];
+  // What of the transfers and the inverse is in flight at once.  With four cells per thread there are registers
+  // to load the first of each before the pass in front of its own; an offset that is zero, which the
+  // compiler does not know, keeps it from holding all of it in scratch memory from before the loop.
+  constexpr bool AHEAD = C <= 4;
+  constexpr int UR = BLOCK_R_FOURS, UD = 8, CB = 4;  // fours of R, columns of the inverse, cells of P
+  const int h = M.ld / 2, G = NT / h, g = tid / h;
+  ushort4 rj[UR], pj[CB];
+  double2 rv[UR][2], dv[UD], pv[CB][2];
+  int again = 0;
+  auto load_r = [&](int e) {
+#pragma unroll
+    for (int u = 0; u < UR; ++u) {
+      const int f = e + u;
+      rj[u] = M.rcol[f * NT + tid + again];
+      rv[u][0] = M.rval[2 * f * NT + tid + again];
+      rv[u][1] = M.rval[(2 * f + 1) * NT + tid + again];
+    }
+  };
+  // thread t takes the pair of rows t % h of the inverse and every G-th column from t / h, so that a load of the block
+  // is one run of the array
+  auto load_d = [&](int q) {
+#pragma unroll
+    for (int u = 0; u < UD; ++u) dv[u] = M.inv[min(min(q + u * G, M.n2 - 1) * h + tid - g * h, M.n2 * h - 1) + again];
+  };
+  auto load_p = [&](int c0) {
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+      const int i = (c0 + c) * NT + tid + again;
+      pj[c] = M.pcol[i];
+      pv[c][0] = M.pval[i];
+      pv[c][1] = M.pval[4 * TILE + i];
+    }
+  };
+  if constexpr (AHEAD) load_p(0);  // kept
+  // z = M^-1 r and rho = r.z; vb and gs are free at the start (every read is behind a barrier)
+  auto cycle = [&]() {
+    asm volatile("" : "+s"(again));
+#pragma unroll
+    for (int c = 0; c < C; ++c) vb[c * NT + tid] = r[c] * di[c] * ch.inv_theta;
+    if constexpr (AHEAD) load_r(0);
+    lds_barrier();
+    rows(vb, [&](int c, double s) {  // rh1 = D^-1 (r - K d0), s without K's diagonal
+      const double d0 = vb[c * NT + tid], rh1 = (r[c] - s) * di[c] - d0;
+      va[c * NT + tid] = d0 + (ch.c_d * d0 + ch.c_r * rh1);
+    });
+    if constexpr (AHEAD) load_d(g);
+    lds_barrier();
+    rows(va, [&](int c, double s) { vb[c * NT + tid] = r[c] - __builtin_fma(d[c], va[c * NT + tid], s); });
+    lds_barrier();
+    for (int ps = 0; ps * BLOCK_R_ROWS < M.n2; ++ps) {  // b = R res
+      const int e1 = M.first[ps + 1];
+      double s = 0.0;
+      for (int e = M.first[ps]; e < e1; e += UR) {
+        if (!AHEAD || e > 0) load_r(e);
+#pragma unroll
+        for (int u = 0; u < UR; ++u) s = four(rv[u][0], rv[u][1], rj[u], vb, s);
+      }
+      s = lanes_sum<BLOCK_R_LANES>(s);
+      if (const int row = ps * BLOCK_R_ROWS + tid / BLOCK_R_LANES; lane % BLOCK_R_LANES == 0 && row < M.n2) bc[row] = s;
+    }
+    lds_barrier();
+    {  // x_2 = A_2^-1 b; past the last column zeros
+      double s0 = 0.0, s1 = 0.0;
+      for (int q = g; q < M.n2; q += UD * G) {
+        if (!AHEAD || q > g) load_d(q);
+        double bq[UD];
+#pragma unroll
+        for (int u = 0; u < UD; ++u) bq[u] = bc[min(q + u * G, M.n2 - 1)];
+#pragma unroll
+        for (int u = 0; u < UD; ++u) {
+          if (q + u * G >= M.n2) bq[u] = 0.0;
+          s0 = __builtin_fma(dv[u].x, bq[u], s0);
+          s1 = __builtin_fma(dv[u].y, bq[u], s1);
+        }
+      }
+      xp[tid] = {s0, s1};  // threads from G h on: not read
+    }
+    lds_barrier();
+    for (int row = tid; row < M.n2; row += NT) {
+      double s = 0.0;
+      for (int k = 0; k < G; ++k) s += reinterpret_cast<const double*>(xp)[k * M.ld + row];
+      xc[row] = s;
+    }
+    lds_barrier();
+    // t = xs + P x_2, each thread's own entries of va, which no pass since the last barriers but one reads
+#pragma unroll
+    for (int c0 = 0; c0 < C; c0 += CB) {
+      if (!AHEAD) load_p(c0);
+#pragma unroll
+      for (int c = 0; c < CB; ++c) va[(c0 + c) * NT + tid] = four(pv[c][0], pv[c][1], pj[c], xc, va[(c0 + c) * NT + tid]);
+    }
+    if (M.nlong) {
+      lds_barrier();
+      for (int k = tid; k < M.nlong; k += NT) {
+        double s = va[M.lrow[k]];
+        for (int q = M.lptr[k]; q < M.lptr[k + 1]; ++q) s = __builtin_fma(M.lval[q], xc[M.lcol[q]], s);
+        va[M.lrow[k]] = s;
+      }
+    }
+    lds_barrier();
+    rows(va, [&](int c, double s) {
+      vb[c * NT + tid] = (r[c] - __builtin_fma(d[c], va[c * NT + tid], s)) * di[c] * ch.inv_theta;
+    });
+    lds_barrier();
+    rows(vb, [&](int c, double s) {
+      const double d0 = vb[c * NT + tid], rh1 = ch.theta * d0 - (d0 + s * di[c]);
+      z[c] = va[c * NT + tid] + d0 + (ch.c_d * d0 + ch.c_r * rh1);
+    });
+    totals([&](int, int c) { return r[c] * z[c]; }, one);
+    rho = one[0];
+  };
+  if (k0 == 0) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) va[c * NT + tid] = xs[c * NT + tid];
+    lds_barrier();
+    double bv[C];
+    rows(va, [&](int c, double s) {
+      const int i = c * NT + tid;
+      bv[c] = i < n ? b[i] : 0.0;
+      r[c] = bv[c] - __builtin_fma(d[c], xs[i], s);
+    });
+    totals([&](int k, int c) { return k == 0 ? bv[c] * bv[c] : r[c] * r[c]; }, two);
+    bn = sqrt(two[0]);
+    const double rn = sqrt(two[1]);
+    const bool zero_b = bn == 0.0, stop = zero_b || rn <= tol * bn, capped = !stop && maxit <= 0;
+    if (tid == 0) {
+      ctl->bn = bn;
+      ctl->res = zero_b ? 0.0 : rn / bn;
+      ctl->done = stop || capped ? 1 : 0;
+      if (capped) ctl->status = DIFVM_WARN_NOT_CONVERGED;
+    }
+    if (zero_b)
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+        if (c * NT + tid < n) x[c * NT + tid] = 0.0;
+    if (stop || capped) return;
+    lds_barrier();  // gs is read
+  } else {
+    bn = ctl->bn;
+    rho_old = ctl->rho[0];
+  }
+  int k = k0 + 1;
+  bool done = false;
+  for (; k - k0 <= chunk; ++k) {
+    cycle();
+    const double beta = k >= 2 ? rho / rho_old : 0.0;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {  // the last reads of va are behind the barrier of rho's sum
+      p[c] = __builtin_fma(beta, p[c], z[c]);
+      va[c * NT + tid] = p[c];
+    }
+    lds_barrier();
+    rows(va, [&](int c, double s) { z[c] = __builtin_fma(d[c], p[c], s); });  // z holds q
+    totals([&](int, int c) { return p[c] * z[c]; }, one);
+    const double alpha = rho / one[0];
+    lds_barrier();  // gs is read
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      xs[c * NT + tid] = __builtin_fma(alpha, p[c], xs[c * NT + tid]);
+      r[c] = __builtin_fma(-alpha, z[c], r[c]);
+    }
+    totals([&](int, int c) { return r[c] * r[c]; }, one);
+    const double rn = sqrt(one[0]);
+    const bool conv = rn <= tol * bn;
+    if (conv || k >= maxit) {
+      done = true;
+      if (tid == 0) {
+        ctl->done = 1;
+        ctl->iters = k;
+        ctl->res = rn / bn;
+        ctl->status = conv ? 0 : DIFVM_WARN_NOT_CONVERGED;
+      }
+      break;
+    }
+    rho_old = rho;
+  }
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+    if (const int i = c * NT + tid; i < n) {
+      x[i] = xs[i];
+      if (!done) {
+        rbuf[i] = r[c];
+        pbuf[i] = p[c];
+      }
+    }
+  if (!done && tid == 0) {
+    ctl->next = k - 1;
+    ctl->rho[0] = rho_old;
+  }
+}
+
+// setup: row blockIdx.x of the n x n matrix M copied with leading dimension ld, zeros past its end
+__global__ __launch_bounds__(BLOCK) void k_amg_pad(int n, int ld, const double* __restrict__ M, double* __restrict__ out) {
+  for (int j = threadIdx.x; j < ld; j += BLOCK)
+    out[(size_t)blockIdx.x * ld + j] = j < n ? M[(size_t)blockIdx.x * n + j] : 0.0;
+}
+
 // Setup: in-place Gauss-Jordan inversion of the dense SPD coarsest matrix M (row-major), one pivot k
 // per pair of launches.  Without pivoting: the pivots of an SPD matrix are Schur-complement diagonals,
 // all positive; a pivot that is not sets *bad.
@@ -708,6 +1017,68 @@ constexpr int FUSE_LANES = 16;  // per row of level 1: its S row has some 90 ent
   }
 
 }  // namespace
+
+// the transfers of a two-level hierarchy of a small mesh as k_amg_pcg_block reads them
+static AmgBlock amg_block(AmgDev* a, const AmgHierarchy& H, hipStream_t s) {
+  const difvm_mesh* m = a->mesh;
+  const int uw = m->d.uw, n = m->d.nc, n2 = a->rows[1];
+  AmgBlock B;
+  if (m->d.nseg != 1 || m->d.ntile > SEG_TILES || !m->d.slot_off16 || (uw != 3 && uw != 4) || n2 > BLOCK_COARSE) return B;
+  const AmgCsr &P = H.levels[0].P, &R = H.levels[0].R;
+  constexpr int ROWS = SEG_TILES * TILE;
+  std::vector<ushort4> pcol(ROWS, ushort4{0, 0, 0, 0}), rcol;
+  std::vector<double2> pval(2 * ROWS, double2{0.0, 0.0}), rval;
+  auto put = [](ushort4& col, double2& v0, double2& v1, int k, int c, double v) {
+    (k == 0 ? col.x : k == 1 ? col.y : k == 2 ? col.z : col.w) = (uint16_t)c;
+    (k == 0 ? v0.x : k == 1 ? v0.y : k == 2 ? v1.x : v1.y) = v;
+  };
+  std::vector<int32_t> lrow, lptr = {0}, lcol;
+  std::vector<double> lval;
+  for (int i = 0; i < n; ++i) {
+    const int q4 = std::min(P.ptr[i + 1], P.ptr[i] + 4);
+    for (int q = P.ptr[i]; q < q4; ++q) put(pcol[i], pval[i], pval[ROWS + i], q - P.ptr[i], P.col[q], P.val[q]);
+    if (q4 == P.ptr[i + 1]) continue;
+    lrow.push_back(i);
+    lcol.insert(lcol.end(), P.col.begin() + q4, P.col.begin() + P.ptr[i + 1]);
+    lval.insert(lval.end(), P.val.begin() + q4, P.val.begin() + P.ptr[i + 1]);
+    lptr.push_back((int32_t)lcol.size());
+  }
+  B.nlong = (int)lrow.size();
+  if (B.nlong) {
+    B.lrow = up(a, lrow, s);
+    B.lptr = up(a, lptr, s);
+    B.lcol = up(a, lcol, s);
+    B.lval = up(a, lval, s);
+  }
+  constexpr int PER = 4 * BLOCK_R_LANES;
+  for (int ps = 0; ps < BLOCK_R_PASSES; ++ps) {
+    int most = 0;
+    for (int I = ps * BLOCK_R_ROWS; I < std::min((ps + 1) * BLOCK_R_ROWS, n2); ++I)
+      most = std::max(most, (R.ptr[I + 1] - R.ptr[I] + PER - 1) / PER);
+    B.first[ps + 1] = B.first[ps] + (most + BLOCK_R_FOURS - 1) / BLOCK_R_FOURS * BLOCK_R_FOURS;
+  }
+  rcol.assign((size_t)B.first[BLOCK_R_PASSES] * BLOCK_NT, ushort4{0, 0, 0, 0});
+  rval.assign(2 * rcol.size(), double2{0.0, 0.0});
+  for (int I = 0; I < n2; ++I)
+    for (int q = R.ptr[I]; q < R.ptr[I + 1]; ++q) {
+      const int k = q - R.ptr[I], t = I % BLOCK_R_ROWS * BLOCK_R_LANES + k / 4 % BLOCK_R_LANES;
+      const size_t e = B.first[I / BLOCK_R_ROWS] + k / PER;
+      put(rcol[e * BLOCK_NT + t], rval[2 * e * BLOCK_NT + t], rval[(2 * e + 1) * BLOCK_NT + t], k % 4, R.col[q], R.val[q]);
+    }
+  B.pcol = up(a, pcol, s);
+  B.pval = up(a, pval, s);
+  B.rcol = up(a, rcol, s);
+  B.rval = up(a, rval, s);
+  B.ld = (n2 + 15) & ~15;
+  double* inv = work(a, (size_t)n2 * B.ld);
+  k_amg_pad<<<n2, BLOCK, 0, s>>>(n2, B.ld, a->cinv, inv);
+  DIFVM_HIP(hipGetLastError());
+  B.inv = reinterpret_cast<double2*>(inv);
+  DIFVM_HIP(hipStreamSynchronize(s));  // the host arrays end here
+  B.c = cheb_coefficients(0.1 * a->hi[0], a->hi[0]);
+  B.n2 = n2;
+  return B;
+}
 
 // cells per thread of the copy of K to CSR (a cell takes about 50 ns, starting a thread 20 us)
 constexpr int CSR_ROWS = 8192;
@@ -812,6 +1183,7 @@ AmgDev* amg_create(difvm_mesh* m, SellMatrix K, const AmgOptions& opt) {
     DIFVM_CHECK(H.n_coarsest <= MAX_DENSE, DIFVM_ERR_UNSUPPORTED, "coarsest AMG level too large");
     a->cinv = up(a, H.coarsest_dense, s);
     dense_inverse_spd(ctx_of(m), H.n_coarsest, a->cinv, s);
+    if (L_ == 1) a->block = amg_block(a, H, s);
     AmgFused F;  // kept until the synchronisation below
     if (L_ == 2 && fine_spans(m) && (size_t)a->rows[1] * a->rows[2] <= FUSE_MAX_DENSE) {
       F = amg_fuse(H);
@@ -946,6 +1318,19 @@ static void launch_vcycle(const AmgDev* a, hipStream_t s, SellMatrix Km, const d
                                                                                                c[0], ctl);
   (K.off16 ? k_amg_cheb_post2<true, LATE> : k_amg_cheb_post2<false, LATE>)<<<n_spans(m), LATE ? QUARTER : TILE, 0, s>>>(
       K, T, r, a->t[0], a->d0[0], z, part, c[0], ctl);
+  DIFVM_HIP(hipGetLastError());
+}
+
+bool amg_pcg_in_block(const AmgDev* a) { return a->block.n2 > 0; }
+
+void amg_pcg_block(const AmgDev* a, SellMatrix Km, const double* b, double* x, double* r, double* p, int chunk,
+                   PcgCtl* ctl) {
+  const difvm_mesh* m = a->mesh;
+  const SellView K = sview(m, Km);
+  const bool half = m->d.ntile <= 2;
+  auto kernel = K.uw == 4 ? half ? k_amg_pcg_block<4, 4> : k_amg_pcg_block<8, 4>
+                          : half ? k_amg_pcg_block<4, 3> : k_amg_pcg_block<8, 3>;
+  kernel<<<1, BLOCK_NT, 0, stream_of(m)>>>(K, m->d.ntile, a->block, b, x, r, p, chunk, ctl);
   DIFVM_HIP(hipGetLastError());
 }
 

@@ -33,6 +33,12 @@ void amg_free(AmgDev* a);
 // also makes iteration k's update, storing r (= step->r_new) and the partials rr, and the second makes the test.
 void amg_vcycle(const AmgDev* a, SellMatrix K, const double* r, double* z, double* part, PcgCtl* ctl,
                 double* rr = nullptr, int k = 0, const CgStep* step = nullptr);
+// Whether a whole CG solve with this preconditioner fits one block (a mesh of one segment and at most four
+// tiles, two levels), and that solve: at most `chunk` further iterations in one launch; r and p keep what the next
+// launch needs.
+bool amg_pcg_in_block(const AmgDev* a);
+void amg_pcg_block(const AmgDev* a, SellMatrix K, const double* b, double* x, double* r, double* p, int chunk,
+                   PcgCtl* ctl);
 // rows per level (finest first) into rows[0..cap); returns the number of levels
 int amg_levels(const AmgDev* a, int* rows, int cap);
 // Algorithmic bytes of one V-cycle: every kernel's distinct inputs read once and outputs written

@@ -477,7 +477,6 @@ __global__ __launch_bounds__(FINE ? QUARTER : BLOCK) void k_pcg_update(
 // to eight tiles and 16 at eleven against 7.1, so those segments take the two kernels.
 // A launch makes at most `chunk` iterations; what a further launch needs is stored when it ends unconverged.
 // ---------------------------------------------------------------------------------------------
-constexpr int SEG_TILES = 4;     // most tiles of a segment
 constexpr int SEG_CHUNK = 2048;  // most iterations per launch: a launch stays under some 12 ms
 
 // NT threads with C cells each; W: slots of every row, kept in registers (0: rows of any length, read in every
@@ -806,7 +805,8 @@ SolveResult pcg(difvm_mesh* m, SellMatrix A, const double* b, double* x, double 
   const int nseg = m->d.nseg;
   const size_t prof_mark = ctx_of(m).prof.pending.size();  // timed launches of this solve start here
   k_pcg_ctl_init<<<(nseg + 63) / 64, 64, 0, s>>>(w->pcg, nseg, tol, maxit);
-  if (const int nt = max_seg_tiles(m); !amg && nt <= SEG_TILES && !ctx_of(m).prof.on) {
+  const int seg_tiles = max_seg_tiles(m);
+  if ((amg ? amg_pcg_in_block(amg) : seg_tiles <= SEG_TILES) && !ctx_of(m).prof.on) {
     // one block per segment makes the whole solve (while the kernels of an iteration are being timed, it
     // is made by them: the same results)
     const int budget = qo ? std::min(qo->budget, maxit) : maxit;
@@ -814,7 +814,8 @@ SolveResult pcg(difvm_mesh* m, SellMatrix A, const double* b, double* x, double 
     int made = 0;
     do {
       const int chunk = std::min(SEG_CHUNK, budget - made);
-      launch_pcg_segment(m, nt, V, T, b, x, w, chunk);
+      if (amg) amg_pcg_block(amg, A, b, x, w->r, w->p, chunk, w->pcg);
+      else launch_pcg_segment(m, seg_tiles, V, T, b, x, w, chunk);
       made += chunk;
       if (qo) continue;
       post_poll(m, w, w->pcg, bytes, 0);

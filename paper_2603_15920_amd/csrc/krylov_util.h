@@ -223,6 +223,7 @@ __device__ __forceinline__ void seg_totals(const double* __restrict__ part, int 
   for (int k = 0; k < NV; ++k) tot[k] = ((sh[k][0] + sh[k][1]) + sh[k][2]) + sh[k][3];
 }
 
+constexpr int SEG_TILES = 4;  // most tiles of a segment whose whole solve one block makes
 // per-segment PCG state (device)
 struct PcgCtl {
   double tol, bn, res;
