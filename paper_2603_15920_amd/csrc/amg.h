@@ -38,19 +38,25 @@ struct Cheb {
 };
 Cheb cheb_coefficients(double lo, double hi);
 
-// A level between the finest and the coarsest as two passes instead of six.  The sweep from zero is a fixed
-// polynomial of D^-1 A, xs = q(b) = (alpha - beta D^-1 A) D^-1 b with alpha = (1 + c_d) / theta + c_r and
-// beta = c_r / theta, so with bd = D^-1 b:
-//   down:  xs = q(b);  res = b - A xs = S bd,  S = D - alpha A + beta A D^-1 A;  b_2 = R res = (R S) bd
-//   up:    x = xs + P x_2 + q(res - A P x_2) = xs + q(res) + G x_2,  G = P - alpha D^-1 (A P) + beta D^-1 A D^-1 (A P)
-// and with the coarsest level's inverse, G x_2 = (G A_2^-1) b_2.
+// The level above the coarsest as three passes instead of six.  The sweep from zero is a fixed polynomial of D^-1 A,
+// xs = q(b) = (alpha - beta D^-1 A) D^-1 b with alpha = (1 + c_d) / theta + c_r and beta = c_r / theta, so with the
+// residual res = b - A xs
+//   down:  b_c = R res = R (I - A q) b = G^T b
+//   up:    x = xs + P x_c + q(res - A P x_c) = xs + q(res) + G x_c,
+//   G = (I - q A) P = P - alpha D^-1 (A P) + beta D^-1 A D^-1 (A P)
+// and the coarsest level's right-hand side needs neither xs nor res.
+// Or in two passes, with bd = D^-1 b:
+//   down:  xs = q(b);  res = S bd,  S = D - alpha A + beta A D^-1 A;  b_c = (R S) bd
+//   up:    x = xs + q(res) + (G A_c^-1) b_c
 struct AmgFused {
   double alpha = 0.0, beta = 0.0;
-  AmgCsr S, RS, G;  // every entry in CSR (the diagonal too)
+  AmgCsr G;
+  AmgCsr GT;     // three passes
+  AmgCsr S, RS;  // two: every entry in CSR (the diagonal too)
 };
 struct AmgHierarchy;
-// those of level 1 of a hierarchy of three levels
-AmgFused amg_fuse(const AmgHierarchy& H);
+// those of the last level but one of a hierarchy of at least three levels
+AmgFused amg_fuse(const AmgHierarchy& H, bool two);
 
 struct AmgOptions {
   double theta = 0.0;        // strength-of-connection threshold on coarse levels (0: every coupling)

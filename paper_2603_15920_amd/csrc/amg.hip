@@ -62,14 +62,15 @@ struct AmgDev {
   int L = 0;                     // coarse levels 1..L (level L is the coarsest)
   std::vector<DevCsr> A;         // A[l], l = 1..L (A[0] unused: level 0 is K)
   DevCsr P0;                     // prolongation from level 1 to level 0
-  std::vector<DevCsr> R, AP;     // R[l]: rows of level l+1, columns of l; AP[l] (l >= 1): rows of l
+  std::vector<DevCsr> R, AP;     // R[l]: rows of level l+1, columns of l; AP[l] (l >= 1): rows of l; neither at
+                                 // level L-1 >= 1
   std::vector<double*> b, bd, res, x;  // per level (index 0: res only; bd: D^-1 b, levels 1..L-1)
   std::vector<double*> xs, t, d0;      // levels 0..L-1: pre-smoothed x, xs + P x_{l+1}, first
                                        // post-smoothing step
   std::vector<double> hi;        // levels 0..L-1: upper end of the Chebyshev interval
   double* cinv = nullptr;        // dense inverse of A_L, row-major
-  // level 1 of three as two passes (AmgFused; S.n = 0: not built): H = G A_2^-1, dense rows(1) x rows(2)
-  DevCsr S, RS;
+  // level L-1 >= 1 in three passes (AmgFused), or with L = 2 in two (S.n > 0): H = G A_2^-1, dense rows(1) x rows(2)
+  DevCsr G, GT, S, RS;
   double* H = nullptr;
   double alpha = 0.0, beta = 0.0;
   AmgBlock block;
@@ -131,6 +132,7 @@ struct StopFlags {
 };
 __device__ __forceinline__ int load_stops(const StopFlags& st) {  // 1 if this lane saw only stopped segments
   if (!st.ctl) return 0;
+  if (st.nseg == 1) return st.ctl->done;  // a scalar load
   const int lane = threadIdx.x & 63;
   int all = st.ctl[min(lane, st.nseg - 1)].done;  // (no loop around the first load, which would wait for it)
   for (int g = lane + 64; g < st.nseg; g += 64) all &= st.ctl[g].done;
@@ -191,6 +193,34 @@ __device__ __forceinline__ double csr_lane_dot(int lo, int hi, const int32_t* __
   }
   return s;
 }
+
+// The first UN entries of a lane's share, loaded, gathered and summed in three steps, so that a kernel can have two
+// matrices' in flight together; the rest after them.
+template <int SW, int UN>
+struct CsrBatch {
+  int c[UN];
+  double v[UN], xv[UN];
+  __device__ __forceinline__ void load(int lo, int hi, const int32_t* __restrict__ col, const double* __restrict__ val) {
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int k = max(min(lo + u * SW, hi - 1), 0);  // an empty row: the array's first entry, not added
+      c[u] = col[k];
+      v[u] = val[k];
+    }
+  }
+  __device__ __forceinline__ void gather(const double* __restrict__ x) {
+#pragma unroll
+    for (int u = 0; u < UN; ++u) xv[u] = x[c[u]];
+  }
+  __device__ __forceinline__ double sum(int lo, int hi, const int32_t* __restrict__ col, const double* __restrict__ val,
+                                        const double* __restrict__ x) const {
+    double s = 0.0;
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+      if (lo + u * SW < hi) s += v[u] * xv[u];
+    return s + csr_lane_dot<SW, UN>(lo + UN * SW, hi, col, val, [&](int j) { return x[j]; });
+  }
+};
 
 // The same for two value arrays on one pattern: sa = sum va[q] x(col[q]), sb = sum vb[q] x(col[q]).
 template <int SW, int UN = 4, class X>
@@ -501,7 +531,127 @@ __global__ __launch_bounds__(BLOCK) void k_amg_cup2(int n, const int32_t* __rest
   }
 }
 
-// Level 1 of three, the whole way down (AmgFused): rows of level 1 (SW lanes each) in the first blocks,
+// coarsest: x = A_L^-1 b with the dense inverse (row-major, n <= 2048): one block per row, threads
+// over the columns (every load of a thread in flight at once: n / BLOCK <= 8), per-wave shuffle trees
+// and the four wave sums added in order; b is read through L2
+constexpr int MAX_DENSE = 2048;
+template <bool LATE>
+__device__ __forceinline__ void dense_row(int i, int n, const double* __restrict__ inv, const double* __restrict__ b,
+                                          double* __restrict__ x, int flags) {
+  __shared__ double ws[BLOCK / 64];
+  const double* row = inv + (size_t)i * n;
+  constexpr int U = MAX_DENSE / BLOCK;
+  double v[U], w[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {  // columns past the end load column n-1 (no branch around a load)
+    int j = min((int)threadIdx.x + u * BLOCK, n - 1);
+    v[u] = row[j];
+    w[u] = b[j];
+  }
+  double s = 0.0;
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if ((int)threadIdx.x + u * BLOCK < n) s += v[u] * w[u];
+  s = lanes_sum<64>(s);
+  if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = s;
+  __syncthreads();
+  const bool go = !LATE || !stopped(flags);
+  if (threadIdx.x == 0 && go) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < BLOCK / 64; ++w) t += ws[w];
+    x[i] = t;
+  }
+}
+template <bool LATE>
+__global__ __launch_bounds__(BLOCK) void k_amg_coarsest(int n, const double* __restrict__ inv,
+                                                        const double* __restrict__ b, double* __restrict__ x,
+                                                        StopFlags ctl) {
+  const int flags = load_stops(ctl);
+  if (!LATE && stopped(flags)) return;
+  dense_row<LATE>(blockIdx.x, n, inv, b, x, flags);
+}
+
+// The level above the coarsest in three passes (AmgFused), each two kernels' work in one launch: rows of that level
+// (SW lanes each) in the first blocks, rows of the coarsest in the others.
+// A cycle has three launches less than with six passes and the coarsest solve, and gathers as much: what bounds it on
+// large meshes are those gathers, a cache line a cycle and compute unit.  Per CG iteration 384,000 cells 74 -> 66 us,
+// 1,053,696 140 -> 138.
+#define DIFVM_AMG_MID(ptr, n)                                                \
+  const int flags = load_stops(ctl);                                         \
+  if (!LATE && stopped(flags)) return;                                       \
+  const int blocks1 = ((n) * SW + BLOCK - 1) / BLOCK;                        \
+  const int g = xcd_tile(blockIdx.x, blocks1) * BLOCK + threadIdx.x;         \
+  const int row = g / SW, lane = g % SW, rr = min(row, (n) - 1)
+
+// xs = alpha bd - beta D^-1 A bd (bd = D^-1 b);  b2 = G^T b, a wave per row
+template <int SW, bool LATE>
+__global__ __launch_bounds__(BLOCK) void k_amg_mid1(int n, const int32_t* __restrict__ ptr,
+                                                    const int32_t* __restrict__ col, const double* __restrict__ val,
+                                                    const double* __restrict__ diag, const double* __restrict__ bd,
+                                                    double* __restrict__ xs, double alpha, double beta, int n2,
+                                                    const int32_t* __restrict__ tptr, const int32_t* __restrict__ tcol,
+                                                    const double* __restrict__ tval, const double* __restrict__ b,
+                                                    double* __restrict__ b2, StopFlags ctl) {
+  DIFVM_AMG_MID(ptr, n);
+  if ((int)blockIdx.x < blocks1) {
+    const int p0 = ptr[rr], p1 = ptr[rr + 1];
+    const double di = diag[rr], bi = bd[rr];
+    const double a = lanes_sum<SW>(
+        csr_lane_dot<SW>(p0 + lane, row < n ? p1 : 0, col, val, [&](int j) { return bd[j]; }));
+    if ((!LATE || !stopped(flags)) && row < n && lane == 0) xs[row] = alpha * bi - beta / di * (di * bi + a);
+  } else {
+    const int row2 = ((int)blockIdx.x - blocks1) * (BLOCK / 64) + (threadIdx.x >> 6), r2 = min(row2, n2 - 1);
+    const int p0 = tptr[r2], p1 = tptr[r2 + 1];
+    const double s = lanes_sum<64>(csr_lane_dot<64, 12>(p0 + (threadIdx.x & 63), row2 < n2 ? p1 : 0, tcol, tval,
+                                                    [&](int j) { return b[j]; }));
+    if ((!LATE || !stopped(flags)) && row2 < n2 && (threadIdx.x & 63) == 0) b2[row2] = s;
+  }
+}
+
+// resd = D^-1 (b - A xs);  x2 = A_2^-1 b2, a block per row
+template <int SW, bool LATE>
+__global__ __launch_bounds__(BLOCK) void k_amg_mid2(int n, const int32_t* __restrict__ ptr,
+                                                    const int32_t* __restrict__ col, const double* __restrict__ val,
+                                                    const double* __restrict__ diag, const double* __restrict__ b,
+                                                    const double* __restrict__ xs, double* __restrict__ resd, int n2,
+                                                    const double* __restrict__ inv, const double* __restrict__ b2,
+                                                    double* __restrict__ x2, StopFlags ctl) {
+  DIFVM_AMG_MID(ptr, n);
+  if ((int)blockIdx.x < blocks1) {
+    const int p0 = ptr[rr], p1 = ptr[rr + 1];
+    const double bi = b[rr], di = diag[rr], xi = xs[rr];
+    const double s = lanes_sum<SW>(
+        csr_lane_dot<SW>(p0 + lane, row < n ? p1 : 0, col, val, [&](int j) { return xs[j]; }));
+    if ((!LATE || !stopped(flags)) && row < n && lane == 0) resd[row] = (bi - di * xi - s) / di;
+  } else {
+    dense_row<LATE>((int)blockIdx.x - blocks1, n2, inv, b2, x2, flags);
+  }
+}
+
+// x = xs + q(res) + G x2
+template <int SW, bool LATE>
+__global__ __launch_bounds__(BLOCK) void k_amg_up(int n, const int32_t* __restrict__ ptr,
+                                                  const int32_t* __restrict__ col, const double* __restrict__ val,
+                                                  const double* __restrict__ diag, const int32_t* __restrict__ gptr,
+                                                  const int32_t* __restrict__ gcol, const double* __restrict__ gval,
+                                                  double alpha, double beta, const double* __restrict__ xs,
+                                                  const double* __restrict__ resd, const double* __restrict__ x2,
+                                                  double* __restrict__ x, StopFlags ctl) {
+  DIFVM_AMG_ROW(ptr, n);
+  const int glo = gptr[rr] + lane, ghi = row < n ? gptr[rr + 1] : 0;
+  const double di = diag[rr], rd = resd[rr], xi = xs[rr];
+  CsrBatch<SW, 4> ba;
+  CsrBatch<SW, 6> bg;
+  ba.load(lo, hi, col, val);
+  bg.load(glo, ghi, gcol, gval);
+  ba.gather(resd);
+  bg.gather(x2);
+  const double a = lanes_sum<SW>(ba.sum(lo, hi, col, val, resd)), s = lanes_sum<SW>(bg.sum(glo, ghi, gcol, gval, x2));
+  if ((!LATE || !stopped(flags)) && row < n && lane == 0) x[row] = xi + (alpha * rd - beta / di * (di * rd + a)) + s;
+}
+
+// The same of three levels on small meshes (amg_create) in two passes, the whole way down: rows of level 1 (SW lanes each) in the first blocks,
 //   xs = alpha bd - beta D^-1 A bd,  resd = D^-1 S bd
 // and rows of level 2 (a wave each) in the others, b2 = (R S) bd.  With the pass below it stands for the
 // six of the level and the dense solve: on meshes of few tiles a cycle's time is its number of launches
@@ -603,42 +753,6 @@ __global__ __launch_bounds__(BLOCK) void k_amg_prolong(int n, const int32_t* __r
   const double xi = xs[ii];
   double s = csr_lane_dot<1, 4>(lo, hi, col, val, [&](int j) { return xc[j]; });
   if (!LATE || (!stopped(flags) && i < n)) t[i] = xi + s;
-}
-
-// coarsest: x = A_L^-1 b with the dense inverse (row-major, n <= 2048): one block per row, threads
-// over the columns (every load of a thread in flight at once: n / BLOCK <= 8), per-wave shuffle trees
-// and the four wave sums added in order; b is read through L2
-constexpr int MAX_DENSE = 2048;
-template <bool LATE>
-__global__ __launch_bounds__(BLOCK) void k_amg_coarsest(int n, const double* __restrict__ inv,
-                                                        const double* __restrict__ b, double* __restrict__ x,
-                                                        StopFlags ctl) {
-  const int flags = load_stops(ctl);
-  if (!LATE && stopped(flags)) return;
-  __shared__ double ws[BLOCK / 64];
-  const double* row = inv + (size_t)blockIdx.x * n;
-  constexpr int U = MAX_DENSE / BLOCK;
-  double v[U], w[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) {  // columns past the end load column n-1 (no branch around a load)
-    int j = min((int)threadIdx.x + u * BLOCK, n - 1);
-    v[u] = row[j];
-    w[u] = b[j];
-  }
-  double s = 0.0;
-#pragma unroll
-  for (int u = 0; u < U; ++u)
-    if ((int)threadIdx.x + u * BLOCK < n) s += v[u] * w[u];
-  s = lanes_sum<64>(s);
-  if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = s;
-  __syncthreads();
-  const bool go = !LATE || !stopped(flags);
-  if (threadIdx.x == 0 && go) {
-    double t = 0.0;
-#pragma unroll
-    for (int w = 0; w < BLOCK / 64; ++w) t += ws[w];
-    x[blockIdx.x] = t;
-  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1005,6 +1119,18 @@ constexpr int FUSE_LANES = 16;  // per row of level 1: its S row has some 90 ent
 #define DIFVM_AMG_LAUNCH(KERNEL, SW, N, S, ...)                                                           \
   KERNEL<SW, LATE><<<(int)(((size_t)(N) * (SW) + BLOCK - 1) / BLOCK), BLOCK, 0, S>>>(__VA_ARGS__)
 
+#define DIFVM_AMG_MID_LAUNCH(KERNEL, SW, N, MORE, S, ...) \
+  KERNEL<SW, LATE><<<((N) * SW + BLOCK - 1) / BLOCK + (MORE), BLOCK, 0, S>>>(__VA_ARGS__)
+#define DIFVM_AMG_MID_DISPATCH(KERNEL, sw, N, MORE, S, ...)                     \
+  switch (sw) {                                                                 \
+    case 1: DIFVM_AMG_MID_LAUNCH(KERNEL, 1, N, MORE, S, __VA_ARGS__); break;    \
+    case 2: DIFVM_AMG_MID_LAUNCH(KERNEL, 2, N, MORE, S, __VA_ARGS__); break;    \
+    case 4: DIFVM_AMG_MID_LAUNCH(KERNEL, 4, N, MORE, S, __VA_ARGS__); break;    \
+    case 8: DIFVM_AMG_MID_LAUNCH(KERNEL, 8, N, MORE, S, __VA_ARGS__); break;    \
+    case 16: DIFVM_AMG_MID_LAUNCH(KERNEL, 16, N, MORE, S, __VA_ARGS__); break;  \
+    case 32: DIFVM_AMG_MID_LAUNCH(KERNEL, 32, N, MORE, S, __VA_ARGS__); break;  \
+    default: DIFVM_AMG_MID_LAUNCH(KERNEL, 64, N, MORE, S, __VA_ARGS__); break;  \
+  }
 #define DIFVM_AMG_DISPATCH(KERNEL, sw, N, S, ...)               \
   switch (sw) {                                                 \
     case 1: DIFVM_AMG_LAUNCH(KERNEL, 1, N, S, __VA_ARGS__); break;   \
@@ -1147,11 +1273,12 @@ AmgDev* amg_create(difvm_mesh* m, SellMatrix K, const AmgOptions& opt) {
     a->rows.push_back(d.nc);
     a->P0 = upload_csr(a, H.levels[0].P, false, s);
     for (int l = 0; l < L_; ++l) {
-      if (l > 0) {
+      const bool mid = l > 0 && l == L_ - 1;
+      if (l > 0 && !mid) {
         a->AP[l] = upload_csr(a, H.levels[l].AP, false, s, 1);
         a->AP[l].val2 = up(a, H.levels[l].P_on_AP, s);
       }
-      a->R[l] = upload_csr(a, H.levels[l].R, false, s);
+      if (!mid) a->R[l] = upload_csr(a, H.levels[l].R, false, s);
       a->A[l + 1] = upload_csr(a, H.coarse[l], true, s);
       a->rows.push_back(H.coarse[l].n);
     }
@@ -1185,16 +1312,22 @@ AmgDev* amg_create(difvm_mesh* m, SellMatrix K, const AmgOptions& opt) {
     dense_inverse_spd(ctx_of(m), H.n_coarsest, a->cinv, s);
     if (L_ == 1) a->block = amg_block(a, H, s);
     AmgFused F;  // kept until the synchronisation below
-    if (L_ == 2 && fine_spans(m) && (size_t)a->rows[1] * a->rows[2] <= FUSE_MAX_DENSE) {
-      F = amg_fuse(H);
+    if (L_ >= 2) {
+      const bool two = L_ == 2 && fine_spans(m) && (size_t)a->rows[1] * a->rows[2] <= FUSE_MAX_DENSE;
+      F = amg_fuse(H, two);
       a->alpha = F.alpha;
       a->beta = F.beta;
-      a->S = upload_csr(a, F.S, false, s);
-      a->RS = upload_csr(a, F.RS, false, s);
-      const DevCsr G = upload_csr(a, F.G, false, s);
-      a->H = work(a, (size_t)a->rows[1] * a->rows[2]);
-      k_amg_h<<<a->rows[1], BLOCK, 0, s>>>(a->rows[2], G.ptr, G.col, G.val, a->cinv, a->H);
-      DIFVM_HIP(hipGetLastError());
+      a->G = upload_csr(a, F.G, false, s);
+      a->G.sw = lanes_for(F.G.n, F.G.col.size() + H.coarse[L_ - 2].col.size(), 4);
+      if (two) {
+        a->S = upload_csr(a, F.S, false, s);
+        a->RS = upload_csr(a, F.RS, false, s);
+        a->H = work(a, (size_t)a->rows[1] * a->rows[2]);
+        k_amg_h<<<a->rows[1], BLOCK, 0, s>>>(a->rows[2], a->G.ptr, a->G.col, a->G.val, a->cinv, a->H);
+        DIFVM_HIP(hipGetLastError());
+      } else {
+        a->GT = upload_csr(a, F.GT, false, s);
+      }
     }
     DIFVM_HIP(hipStreamSynchronize(s));
   } catch (...) {
@@ -1229,24 +1362,29 @@ double amg_vcycle_bytes(const AmgDev* a) {
   double b = 0.0;
   b += K + 16.0 * n0;  // first pre-smoothing pass: r -> xs
   b += K + 24.0 * n0;  // second: r, xs -> res
-  if (a->S.n) {
-    b += csr(a->R[0], false, 1) + 8.0 * n0 + 24.0 * rows(1);  // res -> b, D^-1 b
-    b += csr(a->A[1], true, 1) + csr(a->S, false, 1) + csr(a->RS, false, 1) + 24.0 * rows(1) + 8.0 * rows(2);
-    b += csr(a->A[1], true, 1) + 8.0 * rows(1) * rows(2) + 24.0 * rows(1) + 8.0 * rows(2);  // xs, resd, b_2 -> x
-  } else {
-    for (int l = 0; l < L; ++l) {
-      if (l > 0) {
-        b += csr(a->A[l], true, 1) + 16.0 * rows(l);  // bd -> xs
-        b += csr(a->A[l], true, 1) + 24.0 * rows(l);  // b, xs -> res
-      }
+  for (int l = 0; l < L; ++l) {
+    if (l > 0 && a->S.n) {
+      b += csr(a->A[1], true, 1) + csr(a->S, false, 1) + csr(a->RS, false, 1) + 24.0 * rows(1) + 8.0 * rows(2);
+      b += csr(a->A[1], true, 1) + 8.0 * rows(1) * rows(2) + 24.0 * rows(1) + 8.0 * rows(2);  // xs, resd, b_2 -> x
+      break;
+    }
+    if (l > 0) {
+      b += csr(a->A[l], true, 1) + 16.0 * rows(l);  // bd -> xs
+      b += csr(a->A[l], true, 1) + 24.0 * rows(l);  // b, xs -> res
+    }
+    if (l > 0 && l == L - 1) {
+      b += csr(a->GT, false, 1) + 8.0 * rows(l) + 8.0 * rows(L);  // b -> b_L
+    } else {
       bool coarsest = l + 1 == L;
       b += csr(a->R[l], false, 1) + 8.0 * rows(l) + (coarsest ? 8.0 : 24.0) * rows(l + 1);  // res -> b (, D^-1 b)
     }
-    b += 8.0 * rows(L) * rows(L) + 16.0 * rows(L);  // dense solve
-    for (int l = L - 1; l >= 1; --l) {
-      b += csr(a->AP[l], true, 2) + 32.0 * rows(l) + 8.0 * rows(l + 1);  // xs, res, x_c -> t, d0
-      b += csr(a->A[l], true, 1) + 24.0 * rows(l);                       // t, d0 -> x
-    }
+  }
+  if (!a->S.n) b += 8.0 * rows(L) * rows(L) + 16.0 * rows(L);  // dense solve
+  if (L >= 2 && !a->S.n)
+    b += csr(a->A[L - 1], true, 1) + csr(a->G, false, 1) + 24.0 * rows(L - 1) + 8.0 * rows(L);  // xs, res, x_L -> x
+  for (int l = L - 2; l >= 1; --l) {
+    b += csr(a->AP[l], true, 2) + 32.0 * rows(l) + 8.0 * rows(l + 1);  // xs, res, x_c -> t, d0
+    b += csr(a->A[l], true, 1) + 24.0 * rows(l);                       // t, d0 -> x
   }
   b += csr(a->P0, false, 1) + 16.0 * n0 + 8.0 * rows(1);  // xs, x_1 -> t
   b += K + 24.0 * n0;                                     // r, t -> d0
@@ -1276,39 +1414,56 @@ static void launch_vcycle(const AmgDev* a, hipStream_t s, SellMatrix Km, const d
   const CycleTest& t2 = step ? test : none;
   (K.off16 ? k_amg_cheb_pre2<true, LATE> : k_amg_cheb_pre2<false, LATE>)<<<G + t2.blocks, BLOCK, 0, s>>>(
       K, T, t2, r, a->xs[0], a->res[0], ctl);
-  if (a->S.n) {
-    // level 1 and the coarsest in two passes
-    const DevCsr &R = a->R[0], &A = a->A[1], &S = a->S, &Q = a->RS;
-    DIFVM_AMG_DISPATCH(k_amg_restrict, R.sw, R.n, s, R.n, R.ptr, R.col, R.val, a->res[0], A.diag, a->b[1], a->bd[1], ctl);
-    const int blocks = (S.n * FUSE_LANES + BLOCK - 1) / BLOCK + (Q.n + BLOCK / 64 - 1) / (BLOCK / 64);
-    k_amg_down1<FUSE_LANES, LATE><<<blocks, BLOCK, 0, s>>>(A.n, A.ptr, A.col, A.val, A.diag, S.ptr, S.col, S.val, Q.n,
-                                                           Q.ptr, Q.col, Q.val, a->alpha, a->beta, a->bd[1], a->xs[1],
-                                                           a->res[1], a->b[2], ctl);
-    k_amg_up1<FUSE_LANES, LATE><<<(A.n * FUSE_LANES + BLOCK - 1) / BLOCK, BLOCK, 0, s>>>(
-        A.n, A.ptr, A.col, A.val, A.diag, Q.n, a->H, a->alpha, a->beta, a->xs[1], a->res[1], a->b[2], a->x[1], ctl);
-  } else {
-    for (int l = 0; l < L; ++l) {
-      if (l > 0) {
-        const DevCsr& A = a->A[l];
-        DIFVM_AMG_DISPATCH(k_amg_cpre1, A.sw, A.n, s, A.n, A.ptr, A.col, A.val, A.diag, a->bd[l], a->xs[l], c[l], ctl);
-        DIFVM_AMG_DISPATCH(k_amg_cpre2, A.sw, A.n, s, A.n, A.ptr, A.col, A.val, A.diag, a->b[l], a->xs[l], a->res[l],
-                           ctl);
-      }
-      const DevCsr& R = a->R[l];
-      const double* dc = l + 1 < L ? a->A[l + 1].diag : nullptr;  // the coarsest level needs no D^-1 b
-      DIFVM_AMG_DISPATCH(k_amg_restrict, R.sw, R.n, s, R.n, R.ptr, R.col, R.val, a->res[l], dc, a->b[l + 1],
-                         a->bd[l + 1], ctl);
-    }
-    k_amg_coarsest<LATE><<<a->rows[L], BLOCK, 0, s>>>(a->rows[L], a->cinv, a->b[L], a->x[L], ctl);
-    // up
-    for (int l = L - 1; l >= 1; --l) {
-      const DevCsr& Q = a->AP[l];
+  for (int l = 0; l < L; ++l) {
+    if (l > 0) {
       const DevCsr& A = a->A[l];
-      DIFVM_AMG_DISPATCH(k_amg_cup1, Q.sw, Q.n, s, Q.n, Q.ptr, Q.col, Q.val, Q.val2, A.diag, a->xs[l], a->res[l],
-                         a->x[l + 1], a->t[l], a->d0[l], c[l], ctl);
-      DIFVM_AMG_DISPATCH(k_amg_cup2, A.sw, A.n, s, A.n, A.ptr, A.col, A.val, A.diag, a->t[l], a->d0[l], a->x[l], c[l],
+      if (a->S.n) {  // and the coarsest
+        const DevCsr &S = a->S, &Q = a->RS;
+        const int blocks = (S.n * FUSE_LANES + BLOCK - 1) / BLOCK + (Q.n + BLOCK / 64 - 1) / (BLOCK / 64);
+        k_amg_down1<FUSE_LANES, LATE><<<blocks, BLOCK, 0, s>>>(A.n, A.ptr, A.col, A.val, A.diag, S.ptr, S.col, S.val, Q.n,
+                                                               Q.ptr, Q.col, Q.val, a->alpha, a->beta, a->bd[1],
+                                                               a->xs[1], a->res[1], a->b[2], ctl);
+        break;
+      }
+      if (l == L - 1) {  // and the coarsest
+        const DevCsr& GT = a->GT;
+        const int n2 = GT.n;
+        DIFVM_AMG_MID_DISPATCH(k_amg_mid1, A.sw, A.n, (n2 + BLOCK / 64 - 1) / (BLOCK / 64), s, A.n, A.ptr, A.col, A.val,
+                               A.diag, a->bd[l], a->xs[l], a->alpha, a->beta, n2, GT.ptr, GT.col, GT.val, a->b[l],
+                               a->b[L], ctl);
+        DIFVM_AMG_MID_DISPATCH(k_amg_mid2, A.sw, A.n, n2, s, A.n, A.ptr, A.col, A.val, A.diag, a->b[l], a->xs[l],
+                               a->res[l], n2, a->cinv, a->b[L], a->x[L], ctl);
+        break;
+      }
+      DIFVM_AMG_DISPATCH(k_amg_cpre1, A.sw, A.n, s, A.n, A.ptr, A.col, A.val, A.diag, a->bd[l], a->xs[l], c[l], ctl);
+      DIFVM_AMG_DISPATCH(k_amg_cpre2, A.sw, A.n, s, A.n, A.ptr, A.col, A.val, A.diag, a->b[l], a->xs[l], a->res[l],
                          ctl);
     }
+    const DevCsr& R = a->R[l];
+    const double* dc = l + 1 < L ? a->A[l + 1].diag : nullptr;  // the coarsest level needs no D^-1 b
+    DIFVM_AMG_DISPATCH(k_amg_restrict, R.sw, R.n, s, R.n, R.ptr, R.col, R.val, a->res[l], dc, a->b[l + 1],
+                       a->bd[l + 1], ctl);
+  }
+  // up
+  if (L == 1) {
+    k_amg_coarsest<LATE><<<a->rows[L], BLOCK, 0, s>>>(a->rows[L], a->cinv, a->b[L], a->x[L], ctl);
+  } else if (a->S.n) {
+    const DevCsr& A = a->A[1];
+    k_amg_up1<FUSE_LANES, LATE><<<(A.n * FUSE_LANES + BLOCK - 1) / BLOCK, BLOCK, 0, s>>>(
+        A.n, A.ptr, A.col, A.val, A.diag, a->rows[2], a->H, a->alpha, a->beta, a->xs[1], a->res[1], a->b[2], a->x[1], ctl);
+  } else {
+    const int l = L - 1;
+    const DevCsr &A = a->A[l], &Q = a->G;
+    DIFVM_AMG_DISPATCH(k_amg_up, Q.sw, A.n, s, A.n, A.ptr, A.col, A.val, A.diag, Q.ptr, Q.col, Q.val, a->alpha, a->beta,
+                       a->xs[l], a->res[l], a->x[L], a->x[l], ctl);
+  }
+  for (int l = L - 2; l >= 1; --l) {
+    const DevCsr& Q = a->AP[l];
+    const DevCsr& A = a->A[l];
+    DIFVM_AMG_DISPATCH(k_amg_cup1, Q.sw, Q.n, s, Q.n, Q.ptr, Q.col, Q.val, Q.val2, A.diag, a->xs[l], a->res[l],
+                       a->x[l + 1], a->t[l], a->d0[l], c[l], ctl);
+    DIFVM_AMG_DISPATCH(k_amg_cup2, A.sw, A.n, s, A.n, A.ptr, A.col, A.val, A.diag, a->t[l], a->d0[l], a->x[l], c[l],
+                       ctl);
   }
   {
     const DevCsr& P = a->P0;

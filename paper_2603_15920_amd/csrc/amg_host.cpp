@@ -391,37 +391,40 @@ static AmgCsr add_product(const AmgCsr& X, double s, const AmgCsr& Y, const std:
   return C;
 }
 
-AmgFused amg_fuse(const AmgHierarchy& H) {
-  const AmgLevel& L = H.levels[1];
-  const AmgCsr& A = H.coarse[0];
+AmgFused amg_fuse(const AmgHierarchy& H, bool two) {
+  const size_t l = H.levels.size() - 1;
+  const AmgLevel& L = H.levels[l];
+  const AmgCsr& A = H.coarse[l - 1];
   const int n = A.n, n2 = H.n_coarsest;
   AmgFused F;
   const Cheb c = cheb_coefficients(0.1 * L.hi, L.hi);
   F.alpha = (1.0 + c.c_d) * c.inv_theta + c.c_r;
   F.beta = c.c_r * c.inv_theta;
-  AmgCsr W, X;  // A with its diagonal in the rows; D - alpha A
-  W.n = X.n = n;
+  AmgCsr W, X = L.AP;  // A with its diagonal in the rows; D (P - alpha D^-1 A P) on the pattern of A P
+  W.n = n;
   W.ptr.assign(1, 0);
+  W.col.reserve(A.col.size() + n);
+  W.val.reserve(A.val.size() + n);
   for (int i = 0; i < n; ++i) {
     W.col.push_back(i);
     W.val.push_back(A.diag[i]);
-    for (int q = A.ptr[i]; q < A.ptr[i + 1]; ++q) {
-      W.col.push_back(A.col[q]);
-      W.val.push_back(A.val[q]);
-    }
+    W.col.insert(W.col.end(), A.col.begin() + A.ptr[i], A.col.begin() + A.ptr[i + 1]);
+    W.val.insert(W.val.end(), A.val.begin() + A.ptr[i], A.val.begin() + A.ptr[i + 1]);
     W.ptr.push_back((int32_t)W.col.size());
+    for (int q = X.ptr[i]; q < X.ptr[i + 1]; ++q) X.val[q] = A.diag[i] * L.P_on_AP[q] - F.alpha * L.AP.val[q];
   }
-  X = W;
+  F.G = add_product(X, F.beta, W, &A.diag, L.AP, n2);  // D G
+  for (int i = 0; i < n; ++i)
+    for (int q = F.G.ptr[i]; q < F.G.ptr[i + 1]; ++q) F.G.val[q] /= A.diag[i];
+  if (!two) {
+    F.GT = transpose(F.G, n2);
+    return F;
+  }
+  X = W;  // D - alpha A
   for (size_t q = 0; q < X.val.size(); ++q) X.val[q] *= -F.alpha;
   for (int i = 0; i < n; ++i) X.val[X.ptr[i]] += A.diag[i];
   F.S = add_product(X, F.beta, W, &A.diag, W, n);
   F.RS = add_product(AmgCsr{}, 1.0, L.R, nullptr, F.S, n);
-  X = L.AP;  // D (P - alpha D^-1 A P) on the pattern of A P, then D G
-  for (int i = 0; i < n; ++i)
-    for (int q = X.ptr[i]; q < X.ptr[i + 1]; ++q) X.val[q] = A.diag[i] * L.P_on_AP[q] - F.alpha * L.AP.val[q];
-  F.G = add_product(X, F.beta, W, &A.diag, L.AP, n2);
-  for (int i = 0; i < n; ++i)
-    for (int q = F.G.ptr[i]; q < F.G.ptr[i + 1]; ++q) F.G.val[q] /= A.diag[i];
   return F;
 }
 
