@@ -65,7 +65,7 @@ struct AmgDev {
   std::vector<DevCsr> R, AP;     // R[l]: rows of level l+1, columns of l; AP[l] (l >= 1): rows of l; neither at
                                  // level L-1 >= 1
   std::vector<double*> b, bd, res, x;  // per level (index 0: res only; bd: D^-1 b, levels 1..L-1)
-  std::vector<double*> xs, t, d0;      // levels 0..L-1: pre-smoothed x, xs + P x_{l+1}, first
+  std::vector<double*> xs, t, d0;      // levels 1..L-1 (t, d0: L-2): pre-smoothed x, xs + P x_{l+1}, first
                                        // post-smoothing step
   std::vector<double> hi;        // levels 0..L-1: upper end of the Chebyshev interval
   double* cinv = nullptr;        // dense inverse of A_L, row-major
@@ -399,14 +399,13 @@ __global__ __launch_bounds__(BLOCK) void k_amg_cheb_post1(SellView K, const doub
   if (!LATE || (!stopped(flags) && in)) d0[i] = (ri - kt) / di * c.inv_theta;
 }
 
-// level 0, up, second pass: z = t + d0 + d1 with rh1 = theta d0 - D^-1 K d0, and per-tile partials
+// level 0, up, second pass: z = t + d0 + d1 (in t's place) with rh1 = theta d0 - D^-1 K d0, and per-tile partials
 // of r.z (part[k] by tile or by quarter, as the CG reads them).  One cell per thread, like the other
 // finest-level passes (four cells per thread left each thread's rows one after another).
 template <bool OFF16, bool FINE>
 __global__ __launch_bounds__(FINE ? QUARTER : TILE) void k_amg_cheb_post2(SellView K, Tiles T, const double* __restrict__ r,
-                                                             const double* __restrict__ t, const double* __restrict__ d0,
-                                                             double* __restrict__ z, double* __restrict__ part, Cheb c,
-                                                             StopFlags ctl) {
+                                                             const double* __restrict__ d0, double* __restrict__ z,
+                                                             double* __restrict__ part, Cheb c, StopFlags ctl) {
   const Span sp = span_of<FINE>(T);
   const int flags = load_stops(ctl);
   if (!FINE && stopped(flags)) return;
@@ -415,7 +414,7 @@ __global__ __launch_bounds__(FINE ? QUARTER : TILE) void k_amg_cheb_post2(SellVi
   const int i = sp.lo + (int)threadIdx.x;
   if (i < sp.hi) {
     SlotRange R = slots_of(K, i);
-    const double di = K.diag[i], d0i = d0[i], ti = t[i], ri = r[i];
+    const double di = K.diag[i], d0i = d0[i], ti = z[i], ri = r[i];
     double kd0 = di * d0i + sell_offdiag<OFF16>(K, i, R, [&](int j) { return d0[j]; });
     double rh1 = c.theta * d0i - kd0 / di;
     zi = ti + d0i + (c.c_d * d0i + c.c_r * rh1);
@@ -738,19 +737,19 @@ __global__ __launch_bounds__(BLOCK) void k_amg_h(int n2, const int32_t* __restri
   }
 }
 
-// level 0, up: t = xs + P xc (one thread per row; almost every row of the finest prolongator has at
+// level 0, up: t = xs + P xc in xs's place (one thread per row; almost every row of the finest prolongator has at
 // most four entries, so four in flight)
 template <bool LATE>
 __global__ __launch_bounds__(BLOCK) void k_amg_prolong(int n, const int32_t* __restrict__ ptr,
                                                        const int32_t* __restrict__ col, const double* __restrict__ val,
-                                                       const double* __restrict__ xs, const double* __restrict__ xc,
-                                                       double* __restrict__ t, StopFlags ctl) {
+                                                       const double* __restrict__ xc, double* __restrict__ t,
+                                                       StopFlags ctl) {
   int i = xcd_tile(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x;
   const int ii = min(i, n - 1);
   int lo = ptr[ii], hi = ptr[ii + 1];
   const int flags = load_stops(ctl);
   if (!LATE && (stopped(flags) || i >= n)) return;
-  const double xi = xs[ii];
+  const double xi = t[ii];
   double s = csr_lane_dot<1, 4>(lo, hi, col, val, [&](int j) { return xc[j]; });
   if (!LATE || (!stopped(flags) && i < n)) t[i] = xi + s;
 }
@@ -1297,9 +1296,9 @@ AmgDev* amg_create(difvm_mesh* m, SellMatrix K, const AmgOptions& opt) {
       size_t n = a->rows[l];
       a->res[l] = work(a, n);
       if (l < L_) {
-        a->xs.push_back(work(a, n));
-        a->t.push_back(work(a, n));
-        a->d0.push_back(work(a, n));
+        a->xs.push_back(l ? work(a, n) : nullptr);
+        a->t.push_back(l && l < L_ - 1 ? work(a, n) : nullptr);
+        a->d0.push_back(l && l < L_ - 1 ? work(a, n) : nullptr);
       }
       if (l > 0) {
         a->b[l] = work(a, n);
@@ -1394,7 +1393,7 @@ double amg_vcycle_bytes(const AmgDev* a) {
 
 template <bool LATE>
 static void launch_vcycle(const AmgDev* a, hipStream_t s, SellMatrix Km, const double* r, double* z, double* part,
-                          StopFlags ctl, CycleTest test, const CgStep* step) {
+                          StopFlags ctl, CycleTest test, const CgStep* step, double* res) {
   difvm_mesh* m = a->mesh;
   SellView K = sview(m, Km);
   const int L = a->L, nc = m->d.nc;
@@ -1402,18 +1401,21 @@ static void launch_vcycle(const AmgDev* a, hipStream_t s, SellMatrix Km, const d
   for (int l = 0; l < L; ++l) c[l] = cheb_coefficients(0.1 * a->hi[l], a->hi[l]);
   const Tiles T = tiles_of(m);
   const int G = grid_for(nc);
+  // xs and t of the finest level live in z, d0 in res, and res in a vector that the caller has free: at a million cells
+  // what an iteration touches, 250 MB, just fits the 256 MB cache (1,053,696 cells: 141 us per iteration with five
+  // vectors for these, 129 with two; up to 900,000 no difference)
   // down
   const CycleTest none{};
   if (step)
     (K.off16 ? k_amg_step_pre1<true> : k_amg_step_pre1<false>)<<<n_spans(m), QUARTER, 0, s>>>(
-        K, T, *step, a->xs[0], test.rr, test.k, c[0], test.ctl);
+        K, T, *step, z, test.rr, test.k, c[0], test.ctl);
   else
     (K.off16 ? k_amg_cheb_pre1<true, LATE> : k_amg_cheb_pre1<false, LATE>)<<<G + test.blocks, BLOCK, 0, s>>>(
-        K, T, test, r, a->xs[0], c[0], ctl);
+        K, T, test, r, z, c[0], ctl);
   // after the joint kernel the test is here: it needs every block's partials of r.r
   const CycleTest& t2 = step ? test : none;
   (K.off16 ? k_amg_cheb_pre2<true, LATE> : k_amg_cheb_pre2<false, LATE>)<<<G + t2.blocks, BLOCK, 0, s>>>(
-      K, T, t2, r, a->xs[0], a->res[0], ctl);
+      K, T, t2, r, z, res, ctl);
   for (int l = 0; l < L; ++l) {
     if (l > 0) {
       const DevCsr& A = a->A[l];
@@ -1441,7 +1443,7 @@ static void launch_vcycle(const AmgDev* a, hipStream_t s, SellMatrix Km, const d
     }
     const DevCsr& R = a->R[l];
     const double* dc = l + 1 < L ? a->A[l + 1].diag : nullptr;  // the coarsest level needs no D^-1 b
-    DIFVM_AMG_DISPATCH(k_amg_restrict, R.sw, R.n, s, R.n, R.ptr, R.col, R.val, a->res[l], dc, a->b[l + 1],
+    DIFVM_AMG_DISPATCH(k_amg_restrict, R.sw, R.n, s, R.n, R.ptr, R.col, R.val, l ? a->res[l] : res, dc, a->b[l + 1],
                        a->bd[l + 1], ctl);
   }
   // up
@@ -1465,14 +1467,11 @@ static void launch_vcycle(const AmgDev* a, hipStream_t s, SellMatrix Km, const d
     DIFVM_AMG_DISPATCH(k_amg_cup2, A.sw, A.n, s, A.n, A.ptr, A.col, A.val, A.diag, a->t[l], a->d0[l], a->x[l], c[l],
                        ctl);
   }
-  {
-    const DevCsr& P = a->P0;
-    k_amg_prolong<LATE><<<grid_for(P.n), BLOCK, 0, s>>>(P.n, P.ptr, P.col, P.val, a->xs[0], a->x[1], a->t[0], ctl);
-  }
-  (K.off16 ? k_amg_cheb_post1<true, LATE> : k_amg_cheb_post1<false, LATE>)<<<G, BLOCK, 0, s>>>(K, r, a->t[0], a->d0[0],
-                                                                                               c[0], ctl);
+  k_amg_prolong<LATE><<<G, BLOCK, 0, s>>>(nc, a->P0.ptr, a->P0.col, a->P0.val, a->x[1], z, ctl);
+  (K.off16 ? k_amg_cheb_post1<true, LATE> : k_amg_cheb_post1<false, LATE>)<<<G, BLOCK, 0, s>>>(K, r, z, res, c[0],
+                                                                                               ctl);
   (K.off16 ? k_amg_cheb_post2<true, LATE> : k_amg_cheb_post2<false, LATE>)<<<n_spans(m), LATE ? QUARTER : TILE, 0, s>>>(
-      K, T, r, a->t[0], a->d0[0], z, part, c[0], ctl);
+      K, T, r, res, z, part, c[0], ctl);
   DIFVM_HIP(hipGetLastError());
 }
 
@@ -1490,7 +1489,7 @@ void amg_pcg_block(const AmgDev* a, SellMatrix Km, const double* b, double* x, d
 }
 
 void amg_vcycle(const AmgDev* a, SellMatrix Km, const double* r, double* z, double* part, PcgCtl* ctls,
-                double* rr, int k, const CgStep* step) {
+                double* rr, int k, const CgStep* step, double* res) {
   difvm_mesh* m = a->mesh;
   const int nseg = m->d.nseg;
   const CycleTest test{ctls, rr, k, nseg, rr ? std::min(64, (nseg + 7) & ~7) : 0};
@@ -1498,7 +1497,7 @@ void amg_vcycle(const AmgDev* a, SellMatrix Km, const double* r, double* z, doub
   // host queues a cycle in well under one iteration's GPU time, and a replayed graph of the cycle
   // cost about 9 us of idle GPU between its end and the next kernel on the stream
   (fine_spans(m) ? launch_vcycle<true> : launch_vcycle<false>)(a, ctx_of(m).stream, Km, r, z, part, StopFlags{ctls, nseg},
-                                                               test, step);
+                                                               test, step, res ? res : a->res[0]);
 }
 
 }  // namespace difvm

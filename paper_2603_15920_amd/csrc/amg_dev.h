@@ -31,8 +31,9 @@ void amg_free(AmgDev* a);
 // of CG iterate k, whose r.r partials these are (as the product of iteration k + 1 does), so that the
 // cycle after the last iteration ends there.  step != nullptr (with rr, on meshes of fine_spans): the first kernel
 // also makes iteration k's update, storing r (= step->r_new) and the partials rr, and the second makes the test.
+// res: scratch of one value per cell (may be step->q); the hierarchy has its own otherwise.
 void amg_vcycle(const AmgDev* a, SellMatrix K, const double* r, double* z, double* part, PcgCtl* ctl,
-                double* rr = nullptr, int k = 0, const CgStep* step = nullptr);
+                double* rr = nullptr, int k = 0, const CgStep* step = nullptr, double* res = nullptr);
 // Whether a whole CG solve with this preconditioner fits one block (a mesh of one segment and at most four
 // tiles, two levels), and that solve: at most `chunk` further iterations in one launch; r and p keep what the next
 // launch needs.

@@ -33,7 +33,7 @@ enum { BI_SO_GO = 0, BI_SO_DONE = 1, BI_SO_BREAKDOWN = 2 };
 
 struct KrylovWork {
   int nc = 0, ntile = 0;
-  double *r = nullptr, *p = nullptr, *q = nullptr, *rh = nullptr, *v = nullptr, *s = nullptr, *z = nullptr,
+  double *r = nullptr, *p = nullptr, *q = nullptr, *rh = nullptr, *v = nullptr, *z = nullptr,
          *t = nullptr;
   double* colscaled = nullptr;   // [n_slots] off-diagonals of A D^-1 (BiCGStab)
   double* partials = nullptr;
@@ -59,7 +59,7 @@ static KrylovWork* make_work(difvm_mesh* m) {
     const Ctx& c = ctx_of(m);
     w->ctx = &c;
     w->r = dalloc<double>(c, n3); w->p = dalloc<double>(c, n3); w->q = dalloc<double>(c, n3);
-    w->rh = dalloc<double>(c, n3); w->v = dalloc<double>(c, n3); w->s = dalloc<double>(c, n3);
+    w->rh = dalloc<double>(c, n3); w->v = dalloc<double>(c, n3);
     w->z = dalloc<double>(c, n3); w->t = dalloc<double>(c, n3);
     w->colscaled = dalloc<double>(c, m->d.nslot);
     const int nseg = m->d.nseg;
@@ -83,7 +83,7 @@ void krylov_work_free(KrylovWork* w) {
   if (!w) return;
   if (w->ctx) {
     const Ctx& c = *w->ctx;
-    for (double* a : {w->r, w->p, w->q, w->rh, w->v, w->s, w->z, w->t, w->colscaled, w->partials}) dfree(c, a);
+    for (double* a : {w->r, w->p, w->q, w->rh, w->v, w->z, w->t, w->colscaled, w->partials}) dfree(c, a);
     dfree(c, w->pcg);
     dfree(c, w->bi);
   }
@@ -854,7 +854,8 @@ SolveResult pcg(difvm_mesh* m, SellMatrix A, const double* b, double* x, double 
   auto precondition = [&](int kk, const CgStep* step = nullptr) {
     if (!amg) return;
     ProfScope ps(m, "pcg_amg_vcycle", cycle_test ? kk + 1 : kk);  // a whole cycle if iteration kk + 1 runs
-    amg_vcycle(amg, A, step ? step->r_new : r, z, partB + NP, w->pcg, cycle_test && kk > 0 ? partB : nullptr, kk, step);
+    amg_vcycle(amg, A, step ? step->r_new : r, z, partB + NP, w->pcg, cycle_test && kk > 0 ? partB : nullptr, kk, step,
+               q);  // q is free until the next product
   };
   (fine ? k_pcg_init1<true> : k_pcg_init1<false>)<<<NP, NTB, 0, s>>>(V, T, b, x, r, part0);
   (amg ? fine ? k_pcg_init2<false, true> : k_pcg_init2<false, false>
@@ -942,7 +943,7 @@ SolveResult pcg(difvm_mesh* m, SellMatrix A, const double* b, double* x, double 
 //   init:   r = b - A x, rhat = r; off-diagonals of A D^-1          partials X = (b.b, r.r)
 //   dir_k:  (from X) stopping test of iterate k-1, beta; p = r + beta (p - omega v)
 //   v_k:    v = A D^-1 p                                            partials V = rhat.v
-//   s_k:    (from V) alpha; s = r - alpha v
+//   s_k:    (from V) alpha; s = r - alpha v, in r's place
 //   t_k:    t = A D^-1 s                                            partials T = (t.s, t.t, s.s)
 //   x_k:    (from T) test on s, omega; x += D^-1 (alpha p + omega s); r = s - omega t
 //                                                                   partials X = (r.r, rhat.r)
@@ -1240,9 +1241,8 @@ __global__ __launch_bounds__(FINE ? QUARTER : TILE) void k_bi_v(SellView A, cons
 
 // alpha, s = r - alpha v, one thread per value of the tile's rows (as k_bi_dir)
 template <int NC, bool FINE>
-__global__ __launch_bounds__(FINE ? QUARTER : TILE, FINE ? 1 : 8) void k_bi_s(Tiles T, int it, const double* __restrict__ r,
-                                               const double* __restrict__ v, double* __restrict__ s,
-                                               const double* __restrict__ part, BiState* sts, int nseg) {
+__global__ __launch_bounds__(FINE ? QUARTER : TILE, FINE ? 1 : 8) void k_bi_s(Tiles T, int it, double* __restrict__ r,
+                                               const double* __restrict__ v, const double* __restrict__ part, BiState* sts, int nseg) {
   constexpr int NT = FINE ? QUARTER : TILE;
   const Span ti = span_of<FINE>(T);
   BiState* st = sts + (size_t)(it & 1) * nseg + ti.s;
@@ -1272,7 +1272,7 @@ __global__ __launch_bounds__(FINE ? QUARTER : TILE, FINE ? 1 : 8) void k_bi_s(Ti
     const int e = e0 + q * NT + (int)threadIdx.x;
     if (e >= e1) continue;
     const int c = e % NC;
-    if (pick(act, c)) s[e] = __builtin_fma(-pick(alpha, c), vv[q], rv[q]);
+    if (pick(act, c)) r[e] = __builtin_fma(-pick(alpha, c), vv[q], rv[q]);
   }
 }
 
@@ -1319,8 +1319,8 @@ __global__ __launch_bounds__(FINE ? QUARTER : TILE) void k_bi_t(SellView A, cons
 template <int NC, bool FINE>
 __global__ __launch_bounds__(FINE ? QUARTER : TILE, FINE ? 1 : 8) void k_bi_x(SellView A, Tiles T, int it, double* __restrict__ x,
                                                double* __restrict__ r, const double* __restrict__ rh,
-                                               const double* __restrict__ p, const double* __restrict__ s,
-                                               const double* __restrict__ t, const double* __restrict__ part_in,
+                                               const double* __restrict__ p, const double* __restrict__ t,
+                                               const double* __restrict__ part_in,
                                                double* __restrict__ part, BiState* sts, int nseg) {
   constexpr int NT = FINE ? QUARTER : TILE;
   const Span ti = span_of<FINE>(T);
@@ -1333,7 +1333,7 @@ __global__ __launch_bounds__(FINE ? QUARTER : TILE, FINE ? 1 : 8) void k_bi_x(Se
     const size_t at = (size_t)ii * NC + c;
     xv[c] = x[at];
     pv[c] = p[at];
-    sv[c] = s[at];
+    sv[c] = r[at];  // s
     tv[c] = t[at];
     hv[c] = rh[at];
   }
@@ -1435,11 +1435,10 @@ static SolveResult bicgstab_nc(difvm_mesh* m, SellMatrix A, const double* b, dou
       const int it = ++done;
       k_bi_v<NC, FINE><<<G, NT, 0, s>>>(V, w->colscaled, T, it, w->p, w->v, w->rh, partV, w->bi, nseg);
       if (!FINE) k_bi_totals<NC><<<nseg, TILE, 0, s>>>(partV, T, tots);
-      k_bi_s<NC, FINE><<<G, NT, 0, s>>>(T, it, w->r, w->v, w->s, FINE ? partV : tots, w->bi, nseg);
-      k_bi_t<NC, FINE><<<G, NT, 0, s>>>(V, w->colscaled, T, it, w->s, w->t, partT, w->bi, nseg);
+      k_bi_s<NC, FINE><<<G, NT, 0, s>>>(T, it, w->r, w->v, FINE ? partV : tots, w->bi, nseg);
+      k_bi_t<NC, FINE><<<G, NT, 0, s>>>(V, w->colscaled, T, it, w->r, w->t, partT, w->bi, nseg);
       if (!FINE) k_bi_totals<3 * NC><<<nseg, TILE, 0, s>>>(partT, T, tots);
-      k_bi_x<NC, FINE><<<G, NT, 0, s>>>(V, T, it, x, w->r, w->rh, w->p, w->s, w->t, FINE ? partT : tots, partX, w->bi,
-                                         nseg);
+      k_bi_x<NC, FINE><<<G, NT, 0, s>>>(V, T, it, x, w->r, w->rh, w->p, w->t, FINE ? partT : tots, partX, w->bi, nseg);
       dir(it + 1);
     }
     DIFVM_HIP(hipGetLastError());
