@@ -46,7 +46,9 @@ struct SparseAcc {
 
 // CSR rows 0..n-1 (ptr, col, val) over n_cols columns: row(i, acc) adds row i's entries, keep(i, column,
 // value) says whether an entry is stored
-constexpr int ROWS_PER_THREAD = 1024;
+// a row takes 0.1 us (prolongator) to 2 us (product of a coarse level), starting a thread 20 us: with 256 rows a
+// thread the setup of 49,536 cells takes 15.9 ms, with 1,024 18.8
+constexpr int ROWS_PER_THREAD = 256;
 template <class Row, class Keep>
 void build_rows(int n, int n_cols, AmgCsr& C, bool sorted, Row&& row, Keep&& keep) {
   struct Part {
