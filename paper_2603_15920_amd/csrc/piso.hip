@@ -33,7 +33,13 @@ namespace difvm {
 // ---------------------------------------------------------------------------------------------
 // theta: time scheme weight of the matrix part (1 backward Euler, 1/2 Crank-Nicolson, 0 forward
 // Euler); the remaining 1 - theta of it is applied to U^n on the right-hand side
-template <int NC, int CONV>
+// W: slots of a row in flight together.  A row's loads are a chain (slot, then flux, geometry and the neighbour's
+// gradient), walked once per W slots.  Four take the three-component form to 200 registers and two waves per
+// SIMD; two to 124 and four waves.  Once the mesh has two waves for every SIMD the shorter chain pays:
+// 1,053,696 cells 109 us with four and 139 with two (157 with one; the floor of the 300 MB is 55), 162,000 17.0 and
+// 17.9; below, where each wave's own loads are all that a compute unit has to do, it does not: 71,784 cells 13.2 and 10.9.
+constexpr int MOMENTUM_FOUR = 256 * 4 * 2 * 64;  // cells
+template <int NC, int CONV, int W>
 __global__ __launch_bounds__(BLOCK) void k_momentum(MeshView<double> m, int table, double nu_all,
                                                     const double* __restrict__ nu_cell, double dt, double theta,
                                                     const double* __restrict__ flux, const double* __restrict__ U,
@@ -62,12 +68,9 @@ __global__ __launch_bounds__(BLOCK) void k_momentum(MeshView<double> m, int tabl
 #pragma unroll
     for (int e = 0; e < 3 * NC; ++e) gi[e] = gU[3 * NC * (size_t)i + e];
     const int8_t* codeU = m.bcode + table * m.nfb;
-    // slots in layout order; the first four with all their loads issued before any is used (walk_row; every
-    // index in range whatever the slot holds).  It takes the three-component form to 200 registers and two waves
-    // per SIMD, and still pays: what bounds it is the chain of a row's loads (slot, then flux, geometry and the
-    // neighbour's gradient), one of them per row instead of two.  1,053,696 cells 139 -> 109 us, 162,000
-    // 17.9 -> 17.0; one slot at a time (94 registers) 157, the floor of its 300 MB is 55.
-    walk_row<4>(row_len(m, i, R), [&](auto Wc, int k0) {
+    // slots in layout order; the first W with all their loads issued before any is used (walk_row; every
+    // index in range whatever the slot holds)
+    walk_row<W>(row_len(m, i, R), [&](auto Wc, int k0) {
       constexpr int N = decltype(Wc)::value;
       int sf[N], j[N];
 #pragma unroll
@@ -283,26 +286,19 @@ static void launch_momentum(const difvm_mesh* m, int conv, double theta, int tab
   MeshView<double> v = view<double>(d);
   dim3 G(grid_for(d.nc)), B(BLOCK);
   hipStream_t s = stream_of(m);
+  const bool four = NC == 1 || m->d.nc >= MOMENTUM_FOUR;
+#define DIFVM_MOMENTUM(CONV)                                                                                     \
+  (four ? k_momentum<NC, CONV, 4> : k_momentum<NC, CONV, NC == 3 ? 2 : 4>)<<<G, B, 0, s>>>(                        \
+      v, table, nu, nu_cell, dt, theta, flux, U, gradU, Ub, d.face_rO, d.face_rN, diag, upper, lower, slot_val, b)
   switch (conv) {
-    case DIFVM_CONV_UPWIND:
-      k_momentum<NC, DIFVM_CONV_UPWIND><<<G, B, 0, s>>>(v, table, nu, nu_cell, dt, theta, flux, U, gradU, Ub, d.face_rO,
-                                                        d.face_rN, diag, upper, lower, slot_val, b);
-      break;
-    case DIFVM_CONV_LINEAR:
-      k_momentum<NC, DIFVM_CONV_LINEAR><<<G, B, 0, s>>>(v, table, nu, nu_cell, dt, theta, flux, U, gradU, Ub, d.face_rO,
-                                                        d.face_rN, diag, upper, lower, slot_val, b);
-      break;
-    case DIFVM_CONV_SOU:
-      k_momentum<NC, DIFVM_CONV_SOU><<<G, B, 0, s>>>(v, table, nu, nu_cell, dt, theta, flux, U, gradU, Ub, d.face_rO,
-                                                     d.face_rN, diag, upper, lower, slot_val, b);
-      break;
-    case DIFVM_CONV_QUICK:
-      k_momentum<NC, DIFVM_CONV_QUICK><<<G, B, 0, s>>>(v, table, nu, nu_cell, dt, theta, flux, U, gradU, Ub, d.face_rO,
-                                                       d.face_rN, diag, upper, lower, slot_val, b);
-      break;
+    case DIFVM_CONV_UPWIND: DIFVM_MOMENTUM(DIFVM_CONV_UPWIND); break;
+    case DIFVM_CONV_LINEAR: DIFVM_MOMENTUM(DIFVM_CONV_LINEAR); break;
+    case DIFVM_CONV_SOU: DIFVM_MOMENTUM(DIFVM_CONV_SOU); break;
+    case DIFVM_CONV_QUICK: DIFVM_MOMENTUM(DIFVM_CONV_QUICK); break;
     default:
       throw Error{DIFVM_ERR_INVALID_ARG, "unknown convection scheme"};
   }
+#undef DIFVM_MOMENTUM
   DIFVM_HIP(hipGetLastError());
 }
 

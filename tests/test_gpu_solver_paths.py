@@ -5,7 +5,8 @@ The Krylov kernels take a quarter of a 1,024-cell tile per block up to 384 tiles
 BiCGStab also sums its partials in a kernel of its own); many tiny members reach the limit with few cells
 (a tile each).  Jacobi-CG of segments of at most four tiles runs in one block per segment; while the
 kernels are being timed (difvm_ctx_profile) the same solve takes the two kernels per iteration, whose
-results must be the same bits."""
+results must be the same bits.  The momentum assembly has two slots of a row in flight below 131,072 cells and
+four from there on."""
 import numpy as np
 import pytest
 
@@ -29,6 +30,30 @@ def momentum_solve(mesh, seg, flux, U, Ub, ncomp):
     st, it, _ = B.difvm_solve_bicgstab(M.h, A, ncomp, b, x, 1e-12, 200)
     assert st == 0
     return host(M.to_user(x, B.KIND_CELL)), it
+
+
+@pytest.mark.parametrize("member,members", [("tets", 42), ("tets", 43), ("hexes", 61)])
+def test_momentum_rows_keep_their_bits(member, members):
+    """rows of four and of six slots, on either side of the limit"""
+    m = mg.kuhn_cube(8, jitter=0.1, patches="walls", seed=5) if member == "tets" else mg.hex_box(14, 13, 12)
+    packed, starts = mg.pack([m] * members)
+    assert (packed.n_cells >= 131072) == (members >= 43)
+    rng = np.random.default_rng(8)
+    fi, fb = m.n_internal_faces, m.n_boundary_faces
+    flux, U, Ub = 0.1 * rng.standard_normal(fi + fb), rng.standard_normal((m.n_cells, 3)), rng.standard_normal((fb, 3))
+    out = []
+    for mesh, seg, f, u, ub in ((m, None, flux, U, Ub), (packed, starts, np.concatenate(
+            [np.tile(flux[:fi], members), np.tile(flux[fi:], members)]), np.tile(U, (members, 1)), np.tile(Ub, (members, 1)))):
+        M = B.Mesh(ctx(), mesh, seg_cell_start=seg)
+        D, b = empty(mesh.n_cells), empty((mesh.n_cells, 3))
+        A = B.ldu(D, empty(mesh.n_internal_faces), empty(mesh.n_internal_faces))
+        note("momentum", member, mesh.n_cells)
+        B.difvm_ldu_assemble_momentum(M.h, 0.01, 1e-2, M.to_internal(dev(f), B.KIND_FACE_FLUX),
+                                      M.to_internal(dev(u), B.KIND_CELL), M.to_internal(dev(ub), B.KIND_BFACE), A, b)
+        out.append((host(M.to_user(D, B.KIND_CELL)), host(M.to_user(b, B.KIND_CELL))))
+    for one, all_ in zip(*out):
+        for k in (0, members - 1):
+            np.testing.assert_array_equal(all_[starts[k]:starts[k + 1]], one)
 
 
 @pytest.mark.parametrize("members", [384, 385])
