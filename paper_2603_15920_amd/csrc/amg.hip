@@ -764,9 +764,9 @@ __global__ __launch_bounds__(BLOCK) void k_amg_prolong(int n, const int32_t* __r
 // by loads of 16 bytes per lane (30 by loads of 8) and 600 ns pass between a load and its use, so all of
 // it is laid out again for whole 1 KB loads (AmgBlock) and taken several loads at a time.  The inverse grows with
 // the square of its rows and bounds the largest of these meshes (8.9k of 39k cycles at 222 rows, 16.6k at 336).
-// Per iteration in us, eight launches -> this: 968 prisms 33 -> 6.3, 2,048 prisms 34 -> 8.0, 3,872 prisms (336 coarse
-// rows) 34 -> 17, 1,296 tets 33 -> 7.9, 3,888 tets 34 -> 16.  Replayed from a graph, ten PISO steps of
-// 968 / 1,922 / 2,178 / 4,050 prisms 7.4 / 7.9 / 7.9 / 8.6 -> 3.0 / 3.6 / 4.6 / 6.9 ms.  With rows of any length (hexahedra),
+// Per iteration in us, eight launches -> this: 968 prisms 33 -> 5.4, 2,048 34 -> 7.9, 3,872 (336 coarse rows) 34 -> 17,
+// 1,296 tets 33 -> 7.7, 3,072 34 -> 11.8, 3,888 34 -> 16.  Replayed from a graph, ten PISO steps of 968 / 1,922 / 2,178 /
+// 4,050 prisms 7.4 / 7.9 / 7.9 / 8.6 -> 3.0 / 3.6 / 4.6 / 6.9 ms.  With rows of any length (hexahedra),
 // read from L2 in each of the five products, it took 24 us at 1,728 cells and 47 at 4,096 against 35: they take
 // the eight launches, and so do more coarse rows (at 512 their reads alone are 16 us).
 // A launch makes at most `chunk` iterations; what a further launch needs is stored when it ends unconverged.
@@ -790,15 +790,16 @@ __device__ __forceinline__ void lds_barrier() {
 template <int C, int W>
 __global__ __launch_bounds__(BLOCK_NT) void k_amg_pcg_block(SellView K, int nt, AmgBlock M, const double* __restrict__ b,
                                                       double* __restrict__ x, double* __restrict__ rbuf,
-                                                      double* __restrict__ pbuf, int chunk, PcgCtl* ctl) {
+                                                      double* __restrict__ pbuf, double tol, int maxit, int chunk,
+                                                      bool first, PcgCtl* ctl) {
   constexpr int NT = BLOCK_NT, NTILE = NT * C / TILE, WAVES = NT / 64;
   static_assert(NTILE <= 4, "the tiles' sums fill one wave");
   __shared__ double va[C * NT], vb[C * NT], xs[C * NT], bc[BLOCK_COARSE], xc[BLOCK_COARSE], gs[2][64];
   __shared__ double2 xp[NT];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, n = K.nc;
-  if (ctl->done) return;
-  const double tol = ctl->tol;
-  const int maxit = ctl->maxit, k0 = ctl->next;
+  if (!first && ctl->done) return;
+  if (first && tid == 0) ctl_start(ctl, tol, maxit);
+  const int k0 = first ? 0 : ctl->next;
   double r[C], p[C], d[C], di[C];  // di: 1 / d
   // totals of NV values per cell (in the order of k_pcg_segment's); gs may be written again after the next barrier
   auto totals = [&](auto&& v, auto& tot) {
@@ -851,7 +852,7 @@ __global__ __launch_bounds__(BLOCK_NT) void k_amg_pcg_block(SellView K, int nt, 
   // to load the first of each before the pass in front of its own; an offset that is zero, which the
   // compiler does not know, keeps it from holding all of it in scratch memory from before the loop.
   constexpr bool AHEAD = C <= 4;
-  constexpr int UR = BLOCK_R_FOURS, UD = 8, CB = 4;  // fours of R, columns of the inverse, cells of P
+  constexpr int UR = BLOCK_R_FOURS, UD = 8, CB = C < 4 ? C : C % 4 ? 3 : 4;  // fours of R, columns of the inverse, cells of P
   const int h = M.ld / 2, G = NT / h, g = tid / h;
   ushort4 rj[UR], pj[CB];
   double2 rv[UR][2], dv[UD], pv[CB][2];
@@ -1477,14 +1478,20 @@ static void launch_vcycle(const AmgDev* a, hipStream_t s, SellMatrix Km, const d
 
 bool amg_pcg_in_block(const AmgDev* a) { return a->block.n2 > 0; }
 
-void amg_pcg_block(const AmgDev* a, SellMatrix Km, const double* b, double* x, double* r, double* p, int chunk,
-                   PcgCtl* ctl) {
+template <int W>
+static auto block_kernel(int ntile) {
+  return ntile == 1 ? k_amg_pcg_block<2, W>
+         : ntile == 2 ? k_amg_pcg_block<4, W>
+         : ntile == 3 ? k_amg_pcg_block<6, W>
+                      : k_amg_pcg_block<8, W>;
+}
+
+void amg_pcg_block(const AmgDev* a, SellMatrix Km, const double* b, double* x, double* r, double* p, double tol,
+                   int maxit, int chunk, bool first, PcgCtl* ctl) {
   const difvm_mesh* m = a->mesh;
   const SellView K = sview(m, Km);
-  const bool half = m->d.ntile <= 2;
-  auto kernel = K.uw == 4 ? half ? k_amg_pcg_block<4, 4> : k_amg_pcg_block<8, 4>
-                          : half ? k_amg_pcg_block<4, 3> : k_amg_pcg_block<8, 3>;
-  kernel<<<1, BLOCK_NT, 0, stream_of(m)>>>(K, m->d.ntile, a->block, b, x, r, p, chunk, ctl);
+  auto kernel = K.uw == 4 ? block_kernel<4>(m->d.ntile) : block_kernel<3>(m->d.ntile);
+  kernel<<<1, BLOCK_NT, 0, stream_of(m)>>>(K, m->d.ntile, a->block, b, x, r, p, tol, maxit, chunk, first, ctl);
   DIFVM_HIP(hipGetLastError());
 }
 

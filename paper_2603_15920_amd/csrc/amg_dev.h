@@ -35,11 +35,11 @@ void amg_free(AmgDev* a);
 void amg_vcycle(const AmgDev* a, SellMatrix K, const double* r, double* z, double* part, PcgCtl* ctl,
                 double* rr = nullptr, int k = 0, const CgStep* step = nullptr, double* res = nullptr);
 // Whether a whole CG solve with this preconditioner fits one block (a mesh of one segment and at most four
-// tiles, two levels), and that solve: at most `chunk` further iterations in one launch; r and p keep what the next
-// launch needs.
+// tiles, two levels), and that solve: at most `chunk` further iterations in one launch (the first makes the
+// control state); r and p keep what the next launch needs.
 bool amg_pcg_in_block(const AmgDev* a);
-void amg_pcg_block(const AmgDev* a, SellMatrix K, const double* b, double* x, double* r, double* p, int chunk,
-                   PcgCtl* ctl);
+void amg_pcg_block(const AmgDev* a, SellMatrix K, const double* b, double* x, double* r, double* p, double tol,
+                   int maxit, int chunk, bool first, PcgCtl* ctl);
 // rows per level (finest first) into rows[0..cap); returns the number of levels
 int amg_levels(const AmgDev* a, int* rows, int cap);
 // Algorithmic bytes of one V-cycle: every kernel's distinct inputs read once and outputs written

@@ -27,6 +27,7 @@ struct BiState {
   double bn[3], rho[3], alpha[3], omega[3], res[3], sres[3];  // rho = rhat.r entering the iteration
   int maxit, any;
   int iters[3], active[3], so[3], status[3];
+  int next[3], pad;  // iteration that a further launch of k_bi_segment starts with
 };
 // outcome of the test on s (BiState::so)
 enum { BI_SO_GO = 0, BI_SO_DONE = 1, BI_SO_BREAKDOWN = 2 };
@@ -471,8 +472,9 @@ __global__ __launch_bounds__(FINE ? QUARTER : BLOCK) void k_pcg_update(
 // vector in LDS, x, r, z (q in z's place) and the diagonal in registers (thread tid holds cells
 // tid + c NT), uniform rows of three or four slots too.  An iteration is three block barriers and two
 // reductions instead of two kernels; its time is their latency, which few waves keep short (every wave
-// repeats the scalar work).  Per iteration, two kernels -> this: 968 and 2,048 prisms 6.9 -> 1.9 us, 3,872
-// prisms 6.9 -> 2.7, 3,072 tets 7.2 -> 3.0, 1,728 hexes (rows read from L2 each time) 8.2 -> 5.4.  Above
+// repeats the scalar work), so a block holds no more cells than the largest segment's tiles.  Per iteration, two
+// kernels -> this: 968 prisms 6.8 -> 1.35 us, 2,048 6.9 -> 1.8, 3,872 6.9 -> 2.7, 3,072 tets 7.2 -> 2.6, 1,728 hexes (rows
+// read from L2 each time) 8.0 -> 5.3.  Above
 // four tiles the rows do not fit one compute unit's registers; read from L2 they took 8 to 9 us at five
 // to eight tiles and 16 at eleven against 7.1, so those segments take the two kernels.
 // A launch makes at most `chunk` iterations; what a further launch needs is stored when it ends unconverged.
@@ -484,8 +486,8 @@ constexpr int SEG_CHUNK = 2048;  // most iterations per launch: a launch stays u
 template <int NT, int C, int W>
 __global__ __launch_bounds__(NT) void k_pcg_segment(SellView A, Tiles T, const double* __restrict__ b,
                                                     double* __restrict__ x, double* __restrict__ rbuf,
-                                                    double* __restrict__ zbuf, double* __restrict__ pbuf, int chunk,
-                                                    PcgCtl* ctls) {
+                                                    double* __restrict__ zbuf, double* __restrict__ pbuf, double tol,
+                                                    int maxit, int chunk, bool first, PcgCtl* ctls) {
   constexpr int NTILE = NT * C / TILE, WAVES = NT / 64;
   constexpr bool REG = W > 0;
   static_assert(NTILE <= 4, "the tiles' sums fill one wave");
@@ -493,12 +495,12 @@ __global__ __launch_bounds__(NT) void k_pcg_segment(SellView A, Tiles T, const d
   __shared__ double gs[2][64];
   const int s = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   PcgCtl* ctl = ctls + s;
-  if (ctl->done) return;
+  if (!first && ctl->done) return;
+  if (first && tid == 0) ctl_start(ctl, tol, maxit);
   const int f = seg_first(T, s), nt = seg_count(T, s);
   const TileIdx t0 = tile_at(T, f), t1 = tile_at(T, f + nt - 1);
   const int lo = t0.lo, n = t1.hi - lo;  // the segment's cells are consecutive
-  const double tol = ctl->tol;
-  const int maxit = ctl->maxit, k0 = ctl->next;
+  const int k0 = first ? 0 : ctl->next;
   double xv[C], r[C], z[C], d[C];
   double own[REG ? C : 1];  // this thread's entries of sp
   // the totals of NV values per cell over the segment, in the order of the tiles' partials; v(k, c): value k
@@ -711,20 +713,23 @@ static int max_seg_tiles(const difvm_mesh* m) {
 }
 
 static void launch_pcg_segment(const difvm_mesh* m, int nt, const SellView& V, const Tiles& T, const double* b,
-                               double* x, KrylovWork* w, int chunk) {
+                               double* x, KrylovWork* w, double tol, int maxit, int chunk, bool first, PcgCtl* ctls) {
   const int G = m->d.nseg;
   hipStream_t s = stream_of(m);
-#define DIFVM_SEG(NT, C, W) \
-  k_pcg_segment<NT, C, W><<<G, NT, 0, s>>>(V, T, b, x, w->r, w->z, w->p, chunk, w->pcg)
-  if (V.uw == 4) {
-    if (nt <= 2) DIFVM_SEG(256, 8, 4);
-    else DIFVM_SEG(512, 8, 4);
-  } else if (V.uw == 3) {
-    if (nt <= 2) DIFVM_SEG(256, 8, 3);
-    else DIFVM_SEG(512, 8, 3);
-  } else {
-    DIFVM_SEG(512, 8, 0);
+// as many cells as the tiles hold
+#define DIFVM_SEG_TILES(W)             \
+  switch (nt) {                        \
+    case 1: DIFVM_SEG(256, 4, W); break; \
+    case 2: DIFVM_SEG(256, 8, W); break; \
+    case 3: DIFVM_SEG(512, 6, W); break; \
+    default: DIFVM_SEG(512, 8, W);     \
   }
+#define DIFVM_SEG(NT, C, W) \
+  k_pcg_segment<NT, C, W><<<G, NT, 0, s>>>(V, T, b, x, w->r, w->z, w->p, tol, maxit, chunk, first, ctls)
+  if (V.uw == 4) DIFVM_SEG_TILES(4)
+  else if (V.uw == 3) DIFVM_SEG_TILES(3)
+  else DIFVM_SEG(512, 8, 0);
+#undef DIFVM_SEG_TILES
 #undef DIFVM_SEG
   DIFVM_HIP(hipGetLastError());
 }
@@ -732,11 +737,7 @@ static void launch_pcg_segment(const difvm_mesh* m, int nt, const SellView& V, c
 // per-segment control state set on the device (no host buffer, so the launch can be captured)
 __global__ void k_pcg_ctl_init(PcgCtl* ctls, int nseg, double tol, int maxit) {
   int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= nseg) return;
-  PcgCtl c{};
-  c.tol = tol;
-  c.maxit = maxit;
-  ctls[g] = c;
+  if (g < nseg) ctl_start(ctls + g, tol, maxit);
 }
 
 // copies n doubles (solver states are made of doubles and ints, 8-byte multiples)
@@ -804,18 +805,18 @@ SolveResult pcg(difvm_mesh* m, SellMatrix A, const double* b, double* x, double 
   Tiles T = tiles_of(m);
   const int nseg = m->d.nseg;
   const size_t prof_mark = ctx_of(m).prof.pending.size();  // timed launches of this solve start here
-  k_pcg_ctl_init<<<(nseg + 63) / 64, 64, 0, s>>>(w->pcg, nseg, tol, maxit);
   const int seg_tiles = max_seg_tiles(m);
   if ((amg ? amg_pcg_in_block(amg) : seg_tiles <= SEG_TILES) && !ctx_of(m).prof.on) {
     // one block per segment makes the whole solve (while the kernels of an iteration are being timed, it
     // is made by them: the same results)
     const int budget = qo ? std::min(qo->budget, maxit) : maxit;
     const size_t bytes = pcg_state_bytes(m);
+    PcgCtl* ctls = qo ? static_cast<PcgCtl*>(qo->state_out) : w->pcg;
     int made = 0;
     do {
       const int chunk = std::min(SEG_CHUNK, budget - made);
-      if (amg) amg_pcg_block(amg, A, b, x, w->r, w->p, chunk, w->pcg);
-      else launch_pcg_segment(m, seg_tiles, V, T, b, x, w, chunk);
+      if (amg) amg_pcg_block(amg, A, b, x, w->r, w->p, tol, maxit, chunk, made == 0, ctls);
+      else launch_pcg_segment(m, seg_tiles, V, T, b, x, w, tol, maxit, chunk, made == 0, ctls);
       made += chunk;
       if (qo) continue;
       post_poll(m, w, w->pcg, bytes, 0);
@@ -824,14 +825,12 @@ SolveResult pcg(difvm_mesh* m, SellMatrix A, const double* b, double* x, double 
       for (int g = 0; g < nseg; ++g) all = all && hs[g].done;
       if (all) break;
     } while (made < budget);
-    if (qo) {
-      copy_state(qo->state_out, w->pcg, bytes, s);
-      return SolveResult{};
-    }
+    if (qo) return SolveResult{};
     SolveResult R = pcg_result(m, w->host_state[0], nullptr);
     if (hint) *hint = R.iters[0];
     return R;
   }
+  k_pcg_ctl_init<<<(nseg + 63) / 64, 64, 0, s>>>(w->pcg, nseg, tol, maxit);
   const int GS = pcg_spmv_launch_grid(m);
   const bool fine = fine_spans(m);
   const int NP = n_spans(m), NTB = fine ? QUARTER : TILE;  // partials of one value; threads of the init kernels
@@ -1373,6 +1372,222 @@ __global__ __launch_bounds__(FINE ? QUARTER : TILE, FINE ? 1 : 8) void k_bi_x(Se
   put_partial<2 * NC, NT, FINE>(acc, part, T.ntile, ti);
 }
 
+// ---------------------------------------------------------------------------------------------
+// BiCGStab of small segments with uniform rows of three or four slots, one block per segment and component and
+// the whole solve in one launch (as k_pcg_segment): the gathered vector (p, then s) and x in LDS, the rest and
+// the scaled rows in registers.  Same sums in the same order as the kernels above, so the same bits.  Five
+// barriers and three reductions an iteration instead of five kernels.  Ten PISO steps replayed from a graph (each with
+// one solve of three components, some five iterations, and with the launches that make and copy the solvers' states
+// gone): 968 / 1,922 / 2,178 / 4,050 prisms 2.95 / 3.61 / 4.58 / 6.92 -> 2.05 / 2.78 / 3.36 / 6.19 ms.
+// Block (s, c) writes its component's fields of the segment's state; the first launch makes them.
+// ---------------------------------------------------------------------------------------------
+template <int NT, int C, int W>
+__global__ __launch_bounds__(NT) void k_bi_segment(SellView A, Tiles T, int nc, const double* __restrict__ b,
+                                                   double* __restrict__ x, double* __restrict__ rbuf,
+                                                   double* __restrict__ hbuf, double* __restrict__ pbuf, double tol,
+                                                   int maxit, int chunk, bool first, BiState* sts) {
+  constexpr int NTILE = NT * C / TILE, WAVES = NT / 64;
+  static_assert(NTILE <= 4, "the tiles' sums fill one wave");
+  __shared__ double sp[C * NT], sx[C * NT];
+  __shared__ double gs[3][64];
+  const int s = blockIdx.x / nc, comp = blockIdx.x % nc, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  BiState* st = sts + s;
+  if (!first && !st->active[comp]) return;
+  const int f = seg_first(T, s), nt = seg_count(T, s);
+  const TileIdx t0 = tile_at(T, f), t1 = tile_at(T, f + nt - 1);
+  const int lo = t0.lo, n = t1.hi - lo;  // the segment's cells are consecutive
+  auto totals = [&](auto&& v, auto& tot) {  // as in k_pcg_segment
+#pragma clang fp contract(off)
+    constexpr int NV = sizeof(tot) / sizeof(double);
+    wave_sums<NV * C>([&](int e) { return e % C * NT + tid < n ? v(e / C, e % C) : 0.0; },
+                      [&](int e, double sum) { gs[e / C][e % C * WAVES + wid] = sum; });
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      double t = row_sum(gs[k][lane]);
+      if (lane / TILE_WAVES >= nt) t = 0.0;
+      t = swap_add16(t, t);
+      tot[k] = wave_first(NTILE > 2 ? swap_add32(t, t) : t);
+    }
+  };
+  double av[C][W], r[C], rh[C], p[C], v[C], t[C], d[C];
+  int jv[C][W];
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    // cells past the segment: an empty row
+    const int me = c * NT + tid;
+    const bool in = me < n;
+    const int i = in ? lo + me : lo, base = (i >> 6) * (SLICE * W) + (i & (SLICE - 1));  // uniform rows
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+      const double a = A.val[base + k * SLICE];
+      const int j = A.off16[base + k * SLICE];
+      av[c][k] = in ? a : 0.0;
+      jv[c][k] = me + (in ? j : 0);
+    }
+    const size_t at = (size_t)i * nc + comp;
+    d[c] = in ? A.diag[i] : 1.0;
+    sx[me] = in ? x[at] : 0.0;
+    sp[me] = sx[me];
+    r[c] = in ? (first ? b[at] : rbuf[at]) : 0.0;
+    rh[c] = in && !first ? hbuf[at] : 0.0;
+    p[c] = in && !first ? pbuf[at] : 0.0;
+  }
+  // out(c, own[c] + off-diagonals of row c on the vector in sp)
+  auto rows = [&](auto&& own, auto&& out) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      double acc = own(c);
+#pragma unroll
+      for (int k = 0; k < W; ++k) acc = __builtin_fma(av[c][k], sp[jv[c][k]], acc);
+      out(c, acc);
+    }
+  };
+  double one[1], two[2], three[3], bn, rho, res;
+  int it = 1, status = 0;
+  bool active = true, bad = false;
+  if (first) {
+    __syncthreads();
+    double bv[C];
+    rows([&](int c) { return d[c] * sp[c * NT + tid]; },
+         [&](int c, double ax) {
+           bv[c] = r[c];
+           r[c] = rh[c] = p[c] = c * NT + tid < n ? bv[c] - ax : 0.0;
+         });
+    totals([&](int k, int c) { return k == 0 ? bv[c] * bv[c] : r[c] * r[c]; }, two);
+    bn = sqrt(two[0]);
+    const double rn = sqrt(two[1]);
+    rho = two[1];
+    res = bn == 0.0 ? 0.0 : rn / bn;
+    active = !(bn == 0.0 || rn <= tol * bn);
+    if (active && maxit <= 0) {
+      active = false;
+      status = DIFVM_WARN_NOT_CONVERGED;
+    } else if (active && rho == 0.0) {
+      active = false;
+      status = DIFVM_WARN_BREAKDOWN;
+    }
+    if (tid == 0) {
+      if (comp == 0) {
+        st->tol = tol;
+        st->maxit = maxit;
+        st->any = 0;
+      }
+      st->bn[comp] = bn;
+      st->res[comp] = res;
+      st->iters[comp] = 0;
+      st->next[comp] = 1;
+      st->rho[comp] = rho;
+      st->status[comp] = status;
+      st->active[comp] = active ? 1 : 0;
+    }
+    if (bn == 0.0)
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+        if (const int me = c * NT + tid; me < n) x[(size_t)(lo + me) * nc + comp] = 0.0;
+    if (!active) return;
+    // columns scaled by 1/d, through sp (the sums' barrier is behind the last reads)
+#pragma unroll
+    for (int c = 0; c < C; ++c) sp[c * NT + tid] = d[c];
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+      for (int k = 0; k < W; ++k) av[c][k] = av[c][k] / sp[jv[c][k]];
+  } else {
+#pragma unroll
+    for (int c = 0; c < C; ++c) sp[c * NT + tid] = d[c];
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+      for (int k = 0; k < W; ++k) av[c][k] = av[c][k] / sp[jv[c][k]];
+    bn = st->bn[comp];
+    rho = st->rho[comp];
+    res = st->res[comp];
+    it = st->next[comp];
+  }
+  __syncthreads();
+  for (int made = 0; active && made < chunk; ++made, ++it) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) sp[c * NT + tid] = p[c];
+    __syncthreads();
+    rows([&](int c) { return p[c]; }, [&](int c, double y) { v[c] = y; });
+    totals([&](int, int c) { return rh[c] * v[c]; }, one);
+    const double alpha = rho / one[0];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      r[c] = __builtin_fma(-alpha, v[c], r[c]);
+      sp[c * NT + tid] = r[c];
+    }
+    __syncthreads();
+    rows([&](int c) { return r[c]; }, [&](int c, double y) { t[c] = y; });
+    totals([&](int k, int c) { return k == 0 ? t[c] * r[c] : k == 1 ? t[c] * t[c] : r[c] * r[c]; }, three);
+    const double sn = sqrt(three[2]), omega = three[0] / three[1];
+    const bool small = sn <= tol * bn;
+    bad = !small && three[1] == 0.0;
+    if (bad) {  // x, count and residual stay the previous iterate's
+      active = false;
+      status = DIFVM_WARN_BREAKDOWN;
+      break;
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const int me = c * NT + tid;
+      const double y = p[c] / d[c], z = r[c] / d[c];
+      sx[me] = __builtin_fma(alpha, y, small ? sx[me] : __builtin_fma(omega, z, sx[me]));
+    }
+    if (small) {
+      active = false;
+      res = sn / bn;
+      break;
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) r[c] = __builtin_fma(-omega, t[c], r[c]);
+    __syncthreads();  // gs is read
+    totals([&](int k, int c) { return k == 0 ? r[c] * r[c] : rh[c] * r[c]; }, two);
+    const double rn = sqrt(two[0]), rho_old = rho;
+    res = rn / bn;
+    if (rn <= tol * bn) {
+      active = false;
+      break;
+    }
+    if (it >= maxit) {
+      active = false;
+      status = DIFVM_WARN_NOT_CONVERGED;
+      break;
+    }
+    rho = two[1];
+    if (rho == 0.0) {
+      active = false;
+      status = DIFVM_WARN_BREAKDOWN;
+      break;
+    }
+    const double beta = (rho / rho_old) * (alpha / omega);
+#pragma unroll
+    for (int c = 0; c < C; ++c) p[c] = __builtin_fma(beta, __builtin_fma(-omega, v[c], p[c]), r[c]);
+  }
+  if (tid == 0) {
+    st->iters[comp] = active || bad ? it - 1 : it;
+    st->res[comp] = res;
+    st->status[comp] = status;
+    st->active[comp] = active ? 1 : 0;
+    st->rho[comp] = rho;
+    st->next[comp] = it;
+  }
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+    if (const int me = c * NT + tid; me < n) {
+      const size_t at = (size_t)(lo + me) * nc + comp;
+      x[at] = sx[me];
+      if (active) {
+        rbuf[at] = r[c];
+        hbuf[at] = rh[c];
+        pbuf[at] = p[c];
+      }
+    }
+}
+
 __global__ void k_bi_state_init(BiState* sts, int nseg, double tol, int maxit) {
   int g = blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= nseg) return;
@@ -1392,7 +1607,7 @@ SolveResult bicgstab_result(const difvm_mesh* m, int ncomp, const void* host_sta
   bool all = true;
   for (int g = 0; g < nseg; ++g) {
     const BiState& st = hs[g];
-    all = all && !st.any;
+    for (int c = 0; c < ncomp; ++c) all = all && !st.active[c];
     SegResult& sr = R.seg[g];
     sr.status = 0;
     for (int c = 0; c < ncomp; ++c) {
@@ -1408,6 +1623,14 @@ SolveResult bicgstab_result(const difvm_mesh* m, int ncomp, const void* host_sta
   return R;
 }
 
+template <int W>
+static auto bi_segment_kernel(int nt) {
+  return nt == 1 ? k_bi_segment<256, 4, W>
+         : nt == 2 ? k_bi_segment<256, 8, W>
+         : nt == 3 ? k_bi_segment<512, 6, W>
+                   : k_bi_segment<512, 8, W>;
+}
+
 template <int NC, bool FINE>
 static SolveResult bicgstab_nc(difvm_mesh* m, SellMatrix A, const double* b, double* x, double tol, int maxit,
                                const QueueOnly* qo, int* hint) {
@@ -1417,6 +1640,30 @@ static SolveResult bicgstab_nc(difvm_mesh* m, SellMatrix A, const double* b, dou
   Tiles T = tiles_of(m);
   constexpr int NT = FINE ? QUARTER : TILE;
   const int G = n_spans(m), nseg = m->d.nseg;
+  const size_t bytes = bicgstab_state_bytes(m);
+  if (const int nt = max_seg_tiles(m); nt <= SEG_TILES && V.off16 && (V.uw == 3 || V.uw == 4)) {
+    const int budget = qo ? std::min(qo->budget, maxit) : maxit;
+    BiState* sts = qo ? static_cast<BiState*>(qo->state_out) : w->bi;
+    auto kernel = V.uw == 4 ? bi_segment_kernel<4>(nt) : bi_segment_kernel<3>(nt);
+    int made = 0;
+    do {
+      const int chunk = std::min(SEG_CHUNK, budget - made);
+      kernel<<<nseg * NC, nt <= 2 ? 256 : 512, 0, s>>>(V, T, NC, b, x, w->r, w->rh, w->p, tol, maxit, chunk, made == 0, sts);
+      DIFVM_HIP(hipGetLastError());
+      made += chunk;
+      if (qo) continue;
+      post_poll(m, w, sts, bytes, 0);
+      const BiState* hs = static_cast<const BiState*>(wait_poll(w, 0));
+      bool any = false;
+      for (int g = 0; g < nseg; ++g)
+        for (int c = 0; c < NC; ++c) any = any || hs[g].active[c];
+      if (!any) break;
+    } while (made < budget);
+    if (qo) return SolveResult{};
+    SolveResult R = bicgstab_result(m, NC, static_cast<const BiState*>(w->host_state[0]), nullptr);
+    if (hint) *hint = std::max(R.iters[0], std::max(R.iters[1], R.iters[2]));
+    return R;
+  }
   k_bi_state_init<<<(nseg + 63) / 64, 64, 0, s>>>(w->bi, nseg, tol, maxit);
   double* partX = w->partials;
   double* partV = partX + 2 * NC * (size_t)G;
@@ -1445,7 +1692,6 @@ static SolveResult bicgstab_nc(difvm_mesh* m, SellMatrix A, const double* b, dou
   };
   // the state after the iterations queued so far
   auto state = [&]() { return w->bi + (size_t)((done + 1) & 1) * nseg; };
-  const size_t bytes = bicgstab_state_bytes(m);
   if (qo) {
     queue_iters(std::min(qo->budget, maxit));
     copy_state(qo->state_out, state(), bytes, s);

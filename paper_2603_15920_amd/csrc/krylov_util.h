@@ -232,5 +232,11 @@ struct PcgCtl {
   int maxit, done, iters, status;
   int next, pad;  // iterations made by those launches so far
 };
+__device__ __forceinline__ void ctl_start(PcgCtl* ctl, double tol, int maxit) {
+  PcgCtl c{};
+  c.tol = tol;
+  c.maxit = maxit;
+  *ctl = c;
+}
 
 }  // namespace difvm

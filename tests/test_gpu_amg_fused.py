@@ -47,16 +47,16 @@ def test_cycle_symmetric_and_solves(name):
     B.difvm_amg_destroy(amg)
 
 
-# one block for the whole solve (one tile of tets; 2,048 and 4,050 prisms; 3,888 tets) and five tiles; members that stop at different iterations, one before the first; the largest mesh of quarter-tile blocks
+# one block for the whole solve (one tile of tets; 2,048, 2,178 and 4,050 prisms; 3,888 tets) and five tiles; members that stop at different iterations, one before the first; the largest mesh of quarter-tile blocks
 # (384 tiles) and the next one; hexahedra (rows of six slots); iteration caps
-@pytest.mark.parametrize("name", ["kuhn5", "prisms 2048", "prisms 4050", "tets 3888", "kuhn9", "members", "hex", "384 tiles", "385 tiles"])
+@pytest.mark.parametrize("name", ["kuhn5", "prisms 2048", "prisms 2178", "prisms 4050", "tets 3888", "kuhn9", "members", "hex", "384 tiles", "385 tiles"])
 @pytest.mark.parametrize("maxit", [1, 4, 200])
 def test_joint_update_matches_separate(name, maxit):
     """the whole solve in one block, or the CG update inside the cycle's first kernel, against the update and
     every pass of the cycle as kernels of their own (taken while kernels are timed by name): equal iterations and status, iterates equal up to rounding carried through the iterations"""
     lap = lambda n: mg.kuhn_cube(n, jitter=0.1, patches="walls", seed=5)
     m = {"kuhn5": lambda: lap(5), "kuhn9": lambda: lap(9), "hex": lambda: mg.hex_box(14, 13, 12),
-         "prisms 2048": lambda: mg.cavity(32), "prisms 4050": lambda: mg.cavity(45),
+         "prisms 2048": lambda: mg.cavity(32), "prisms 2178": lambda: mg.cavity(33), "prisms 4050": lambda: mg.cavity(45),
          "tets 3888": lambda: mg.kuhn_cube(1, jitter=0.1, patches="walls", nxyz=(8, 9, 9), seed=5),
          "members": lambda: mg.pack([lap(8), lap(5), lap(9)]),
          "384 tiles": lambda: mg.kuhn_cube(1, patches="walls", nxyz=(32, 32, 64)),

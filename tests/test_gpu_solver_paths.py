@@ -56,6 +56,34 @@ def test_momentum_rows_keep_their_bits(member, members):
             np.testing.assert_array_equal(all_[starts[k]:starts[k + 1]], one)
 
 
+@pytest.mark.parametrize("shape", ["tets", "prisms"])
+@pytest.mark.parametrize("ncomp", [1, 3])
+@pytest.mark.parametrize("small", [True, False])
+def test_bicgstab_segment_members_keep_their_bits(shape, ncomp, small):
+    """members of one to four tiles, all in the one-block form or (beside a larger one) in the general form,
+    against their standalone solves (one block): the same bits and counts"""
+    one = (lambda n: mg.kuhn_cube(n, jitter=0.1, patches="walls", seed=n)) if shape == "tets" else mg.cavity
+    ms = [one(n) for n in ((2, 5, 7, 8) if shape == "tets" else (8, 22, 32, 45))] + ([] if small else [one(
+        10 if shape == "tets" else 50)])
+    packed, starts = mg.pack(ms)
+    rng = np.random.default_rng(8)
+    flux = [0.1 * rng.standard_normal(m.n_internal_faces + m.n_boundary_faces) for m in ms]
+    U = rng.standard_normal((packed.n_cells, 3))
+    Ub = rng.standard_normal((packed.n_boundary_faces, 3))
+    flux_p = np.concatenate([f[:m.n_internal_faces] for f, m in zip(flux, ms)] +
+                            [f[m.n_internal_faces:] for f, m in zip(flux, ms)])
+    note("bicgstab segments", shape, ncomp, small)
+    x, it = momentum_solve(packed, starts, flux_p, U, Ub, ncomp)
+    its, fb = [], 0
+    for k, m in enumerate(ms):
+        c = slice(starts[k], starts[k + 1])
+        xk, itk = momentum_solve(m, None, flux[k], U[c], Ub[fb:fb + m.n_boundary_faces], ncomp)
+        fb += m.n_boundary_faces
+        its.append(itk)
+        np.testing.assert_array_equal(x[c], xk)
+    assert list(it)[:ncomp] == list(np.max(its, axis=0))[:ncomp]
+
+
 @pytest.mark.parametrize("members", [384, 385])
 @pytest.mark.parametrize("ncomp", [1, 3])
 def test_bicgstab_totals_limit(members, ncomp):
