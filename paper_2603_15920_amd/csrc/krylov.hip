@@ -96,47 +96,38 @@ void krylov_work_free(KrylovWork* w) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// matrix helpers (SellView, sell_row: krylov_util.h)
+// matrix helpers (SellView: krylov_util.h)
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(BLOCK) void k_sell_from_ldu(int nc, int nfi, const int32_t* __restrict__ slice_start, int uw,
+// Slot values from face values, the rows that fill the last slice included (their slots are padding: zeros), so
+// that no clearing pass is needed; a row's first four slots in flight together (one at a time before).  Clearing pass
+// and this kernel -> this: 1,053,696 cells 33.8 -> 15.2 us, 162,000 9.5 -> 4.4.
+__global__ __launch_bounds__(BLOCK) void k_sell_from_ldu(int rows, int nfi, const int32_t* __restrict__ slice_start, int uw,
                                                          const int32_t* __restrict__ slot_face, const double* __restrict__ up,
                                                          const double* __restrict__ lo, double* __restrict__ val) {
   int i = xcd_tile(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x;
-  if (i >= nc) return;
+  if (i >= rows) return;
   SlotRange R = slots_of(slice_start, uw, i);
-  for (int k = 0; k < R.width; ++k) {
-    int at = R.base + k * SLICE;
-    int sf = slot_face[at];
-    double a = 0.0;
-    if (sf != SLOT_PAD && sf < nfi) a = sf < 0 ? lo[-sf - 1] : up[sf];
-    val[at] = a;
-  }
-}
-
-template <int NC>
-__global__ __launch_bounds__(BLOCK) void k_sell_spmv(SellView A, const double* __restrict__ x, double* __restrict__ y) {
-  int i = xcd_tile(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x;
-  if (i >= A.nc) return;
-  double acc[NC];
-  sell_row<NC>(A, i, x, acc);
+  walk_row<4>(R.width, [&](auto Wc, int k0) {
+    constexpr int N = decltype(Wc)::value;
+    int sf[N];
+    double a[N];
 #pragma unroll
-  for (int c = 0; c < NC; ++c) y[(size_t)i * NC + c] = acc[c];
+    for (int k = 0; k < N; ++k) sf[k] = slot_face[R.base + (k0 + k) * SLICE];
+#pragma unroll
+    for (int k = 0; k < N; ++k) a[k] = (sf[k] < 0 ? lo : up)[slot_face_index(sf[k], nfi)];  // others read entry 0
+#pragma unroll
+    for (int k = 0; k < N; ++k) val[R.base + (k0 + k) * SLICE] = slot_internal(sf[k], nfi) ? a[k] : 0.0;
+  });
 }
 
 void sell_from_ldu(const difvm_mesh* m, const double* upper, const double* lower, double* val) {
   const DMesh& d = m->d;
-  // padding rows of the last slice are never read by row kernels; clear the whole array once so no
-  // slot holds stale values
-  DIFVM_HIP(hipMemsetAsync(val, 0, sizeof(double) * (size_t)d.nslot, stream_of(m)));
-  k_sell_from_ldu<<<grid_for(d.nc), BLOCK, 0, stream_of(m)>>>(d.nc, d.nfi, d.slice_start, d.uw, d.slot_face, upper,
-                                                              lower ? lower : upper, val);
-  DIFVM_HIP(hipGetLastError());
-}
-
-void sell_spmv(const difvm_mesh* m, int ncomp, SellMatrix A, const double* x, double* y) {
-  SellView v = sview(m, A);
-  if (ncomp == 1) k_sell_spmv<1><<<grid_for(v.nc), BLOCK, 0, stream_of(m)>>>(v, x, y);
-  else k_sell_spmv<3><<<grid_for(v.nc), BLOCK, 0, stream_of(m)>>>(v, x, y);
+  if (!lower) lower = upper;
+  if (d.nfi == 0) upper = lower = val;  // the caller may pass NULL; entry 0 is read and not used
+  const int rows = d.nslice * SLICE;
+  if (d.nslot == 0) return;
+  k_sell_from_ldu<<<grid_for(rows), BLOCK, 0, stream_of(m)>>>(rows, d.nfi, d.slice_start, d.uw, d.slot_face, upper, lower,
+                                                              val);
   DIFVM_HIP(hipGetLastError());
 }
 

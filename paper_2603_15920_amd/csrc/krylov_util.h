@@ -25,45 +25,12 @@ inline SellView sview(const difvm_mesh* m, SellMatrix A) {
   return {m->d.nc, m->d.cell_nslot, m->d.slice_start, m->d.slot_col, A.val, A.diag, m->d.slot_off16, m->d.uw};
 }
 
-// (A x)_i for NC interleaved components; padding and boundary slots carry val = 0, col = i.  The
-// row's slots in layout order (the slice's width; padding adds nothing), the first four with every
-// load issued before any is used (walk_row).
-template <int NC>
-__device__ __forceinline__ void sell_row(const SellView& A, int i, const double* __restrict__ x, double (&acc)[NC]) {
-  SlotRange R = slots_of(A, i);
-  double di = A.diag[i];
-#pragma unroll
-  for (int c = 0; c < NC; ++c) acc[c] = di * x[(size_t)i * NC + c];
-  const bool off16 = A.off16 != nullptr;  // the same for every thread: a uniform branch
-  walk_row<4>(R.width, [&](auto Wc, int k0) {
-    constexpr int N = decltype(Wc)::value;
-    double a[N], xj[N][NC];
-    int j[N];
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-      int at = R.base + (k0 + k) * SLICE;
-      a[k] = A.val[at];
-      j[k] = off16 ? i + A.off16[at] : A.col[at];
-    }
-#pragma unroll
-    for (int k = 0; k < N; ++k)
-#pragma unroll
-      for (int c = 0; c < NC; ++c) xj[k][c] = x[(size_t)j[k] * NC + c];
-#pragma unroll
-    for (int k = 0; k < N; ++k)
-#pragma unroll
-      for (int c = 0; c < NC; ++c) acc[c] += a[k] * xj[k][c];
-  });
-}
-
 // ---------------------------------------------------------------------------------------------
-// Reduction tiles: TILE = 1024 cells per block (4 per thread), listed per segment.  A segment is one
+// Reduction tiles: TILE = 1024 cells, listed per segment.  A segment is one
 // independent mesh of a block-diagonal batch (a single mesh is one segment); its dot products are
 // the fixed-order sums of its own tiles' partials, so a batch member computes exactly what it would
 // alone.
 // ---------------------------------------------------------------------------------------------
-constexpr int CPT = TILE / BLOCK;  // cells per thread
-
 struct Tiles {
   int ntile;
   int one_nc;  // > 0: one segment of that many cells (tile t starts at cell t TILE), else 0

@@ -40,7 +40,6 @@ struct SellMatrix {
   const double* val;
 };
 void sell_from_ldu(const difvm_mesh* m, const double* upper, const double* lower, double* val);
-void sell_spmv(const difvm_mesh* m, int ncomp, SellMatrix A, const double* x, double* y);
 
 struct SegResult {
   int iters[3] = {0, 0, 0};
