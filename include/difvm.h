@@ -145,7 +145,10 @@ difvm_status difvm_ctx_set_allocator(difvm_ctx* ctx, void* (*alloc)(size_t bytes
  * difvm_piso_set_graph) are not timed.  difvm_ctx_profile_read
  * synchronises, returns per-kernel counts of timed launches and their summed event durations
  * (kernel names in out[k].name), and clears the record.  Launches of CG iterations queued after the
- * solve had stopped (they return at once) are reported under "<name> (idle)". */
+ * solve had stopped (they return at once) are reported under "<name> (idle)".  While timing is enabled,
+ * solves that one launch would make, or whose update is part of the preconditioner's first kernel (small
+ * meshes), take the named kernels: the same iterations and, with Jacobi, the same bits; with AMG equal up to
+ * rounding. */
 typedef struct {
   char name[32];
   int32_t launches;
@@ -293,7 +296,8 @@ difvm_status difvm_halo_unpack(const difvm_mesh* mesh, int dtype, int ncomp, con
  * Knobs that change how work is spread over the GPU but not what any output computes: threads per
  * block of the operator kernels (one cell or face per thread, no reductions), and the grid of the
  * PCG product kernel (one block per 1024-cell tile, or a persistent grid whose blocks walk several
- * tiles; every tile's partial sum is formed the same way).  Outputs are bitwise identical for every
+ * tiles; every tile's partial sum is formed the same way; meshes of at most 384 tiles take a block per quarter
+ * of a tile, or per segment, whatever its value).  Outputs are bitwise identical for every
  * value.  Each mesh starts with 256 threads and one block per tile. */
 enum {
   DIFVM_TUNE_INTERP_F64 = 0, DIFVM_TUNE_INTERP_F32 = 1,
