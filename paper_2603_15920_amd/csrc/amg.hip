@@ -14,11 +14,12 @@
 // power-iteration estimate of rho(D_l^-1 A_l) on the stored coarse operators, capped by their
 // Gershgorin bound.  A sweep takes two passes over the level's operator: from zero, D^-1 b gives d0
 // without one; on the way up the first pass uses b_l - A_l t_l = res_l - (A_l P_l) x_{l+1}, with
-// A_l P_l stored, so prolongation and that residual are one pass on levels l >= 1 (level 0 smooths
-// with the operator of the current solve and keeps the prolongation a pass of its own).  Degree-2 Chebyshev on every level takes about half the
+// A_l P_l stored, so prolongation and that residual are one pass on levels 1 <= l < L-1 (level 0 smooths
+// with the operator of the current solve and keeps the prolongation a pass of its own; level L-1 and the
+// coarsest together take two or three launches, AmgFused).  Degree-2 Chebyshev on every level takes about half the
 // CG iterations of one damped-Jacobi step per level, which more than pays for the extra passes.
 // Each stage is one kernel: row kernels on the cell-slot layout for level 0, CSR kernels with SW
-// lanes per row (rows summed by a fixed shuffle tree) elsewhere, so every result is deterministic.
+// lanes per row (rows summed by a fixed tree of lane exchanges) elsewhere, so every result is deterministic.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -654,7 +655,7 @@ __global__ __launch_bounds__(BLOCK) void k_amg_up(int n, const int32_t* __restri
 //   xs = alpha bd - beta D^-1 A bd,  resd = D^-1 S bd
 // and rows of level 2 (a wave each) in the others, b2 = (R S) bd.  With the pass below it stands for the
 // six of the level and the dense solve: on meshes of few tiles a cycle's time is its number of launches
-// (each some 3 us on the device and 2.5 to 5 for the host), while the 4.5 times as many entries of S stay
+// (each some 3 us on the device and 2.7 for the host), while the 4.5 times as many entries of S stay
 // in the caches.  A CG iteration's 14 launches become 10: 48,000 cells 58 to 42 us, 93,750 61 to 47,
 // 162,000 67 to 52 (31, 38 and 45 us where the host is fast enough for the device to be the limit).  Eight
 // or 32 lanes per row measured the same or slower, 64 slower (38 to 42 us at 93,750 cells).
