@@ -797,7 +797,10 @@ SolveResult pcg(difvm_mesh* m, SellMatrix A, const double* b, double* x, double 
   const int nseg = m->d.nseg;
   const size_t prof_mark = ctx_of(m).prof.pending.size();  // timed launches of this solve start here
   const int seg_tiles = max_seg_tiles(m);
-  if ((amg ? amg_pcg_in_block(amg) : seg_tiles <= SEG_TILES) && !ctx_of(m).prof.on) {
+  // launches inside a captured step are never timed, so a step captured meanwhile is the one that replays keep
+  const Profiler& prof = ctx_of(m).prof;
+  const bool timed = prof.on && !ctx_of(m).capturing;
+  if ((amg ? amg_pcg_in_block(amg) : seg_tiles <= SEG_TILES) && !timed) {
     // one block per segment makes the whole solve (while the kernels of an iteration are being timed, it
     // is made by them: the same results)
     const int budget = qo ? std::min(qo->budget, maxit) : maxit;
@@ -839,8 +842,7 @@ SolveResult pcg(difvm_mesh* m, SellMatrix A, const double* b, double* x, double 
   // on they compute for all, which changes nothing a stopped segment reads)
   // the cycle's first kernel makes iterate kk's stopping test, so that the last cycle ends with it; while every
   // launch is being timed the product makes it and every timed cycle is a whole one
-  const Profiler& prof = ctx_of(m).prof;
-  const bool cycle_test = !(prof.on && prof.stride == 1);
+  const bool cycle_test = !(timed && prof.stride == 1);
   auto precondition = [&](int kk, const CgStep* step = nullptr) {
     if (!amg) return;
     ProfScope ps(m, "pcg_amg_vcycle", cycle_test ? kk + 1 : kk);  // a whole cycle if iteration kk + 1 runs
@@ -855,7 +857,7 @@ SolveResult pcg(difvm_mesh* m, SellMatrix A, const double* b, double* x, double 
   precondition(0);
   // on meshes of few tiles the update is made by the cycle's first kernel (while kernels are being timed by
   // name, by its own: the same results)
-  const bool joint = amg && fine && !prof.on;
+  const bool joint = amg && fine && !timed;
   auto update = [&](int kk) {
     if (joint) {
       const CgStep step{x, Pk[kk & 1], Rk[(kk - 1) & 1], q, partA, Rk[kk & 1]};
