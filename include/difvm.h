@@ -145,10 +145,10 @@ difvm_status difvm_ctx_set_allocator(difvm_ctx* ctx, void* (*alloc)(size_t bytes
  * difvm_piso_set_graph) are not timed.  difvm_ctx_profile_read
  * synchronises, returns per-kernel counts of timed launches and their summed event durations
  * (kernel names in out[k].name), and clears the record.  Launches of CG iterations queued after the
- * solve had stopped (they return at once) are reported under "<name> (idle)".  While timing is enabled,
- * solves that one launch would make, or whose update is part of the preconditioner's first kernel (small
- * meshes), take the named kernels: the same iterations and, with Jacobi, the same bits; with AMG equal up to
- * rounding. */
+ * solve had stopped (they return at once) are reported under "<name> (idle)".  Timing
+ * changes no result: on small meshes a CG solve that one launch would make with Jacobi, and a CG update that is
+ * part of the AMG cycle's first kernel, are made by the named kernels while timing is enabled, with the same bits;
+ * an AMG solve made by one launch is timed as that launch ("pcg_amg_block"). */
 typedef struct {
   char name[32];
   int32_t launches;

@@ -277,7 +277,7 @@ __device__ __forceinline__ double sell_offdiag(const SellView& K, int i, SlotRan
 #pragma unroll
     for (int k = 0; k < N; ++k) fj[k] = f(j[k]);
 #pragma unroll
-    for (int k = 0; k < N; ++k) acc += a[k] * fj[k];
+    for (int k = 0; k < N; ++k) acc = __builtin_fma(a[k], fj[k], acc);
   });
   return acc;
 }
@@ -285,6 +285,15 @@ __device__ __forceinline__ double sell_offdiag(const SellView& K, int i, SlotRan
 // The degree-2 Chebyshev sweep in D^-1 A over [lo, hi] (hi bounds the spectrum of D^-1 A), the same
 // before and after the coarse correction.  From x with residual rh0 = D^-1 (b - A x):  d0 = rh0 / theta,  rh1 = rh0 - D^-1 K d0,  d1 = c_d d0 + c_r rh1,
 // x <- x + d0 + d1 (coefficients: Cheb, amg.h).
+// That sweep from zero at a finest-level cell: r its right-hand side, d the diagonal, s the off-diagonal part of K on
+// cheb_d0 (one arithmetic, written out, for both kernels that make it: a solve has the same bits with either).
+__device__ __forceinline__ double cheb_d0(double r, double d, const Cheb& c) { return r / d * c.inv_theta; }
+__device__ __forceinline__ double cheb_from_zero(double r, double d, double s, const Cheb& c) {
+#pragma clang fp contract(off)
+  const double d0 = cheb_d0(r, d, c), rh1 = r / d - __builtin_fma(d, d0, s) / d;
+  return d0 + __builtin_fma(c.c_r, rh1, c.c_d * d0);
+}
+
 // Row range of cell I of a finest-level pass, loaded at a clamped index, without a branch around the load, so
 // that it is in flight together with the flag reads.  Threads past the last cell take that cell's row and
 // store nothing: every lane stays active for the vote.
@@ -310,11 +319,9 @@ __global__ __launch_bounds__(BLOCK) void k_amg_cheb_pre1(SellView K, Tiles T, Cy
   DIFVM_AMG_TEST;
   int i = xcd_tile(blockIdx.x - test.blocks, gridDim.x - test.blocks) * BLOCK + threadIdx.x;
   DIFVM_AMG_CELL(i);
-  double di = K.diag[i], rh0 = r[i] / di;
-  double d0 = rh0 * c.inv_theta;
-  double kd0 = di * d0 + sell_offdiag<OFF16>(K, i, R, [&](int j) { return r[j] / K.diag[j] * c.inv_theta; });
-  double rh1 = rh0 - kd0 / di;
-  if (!LATE || (!stopped(flags) && in)) xs[i] = d0 + (c.c_d * d0 + c.c_r * rh1);
+  const double di = K.diag[i], ri = r[i];
+  const double s = sell_offdiag<OFF16>(K, i, R, [&](int j) { return cheb_d0(r[j], K.diag[j], c); });
+  if (!LATE || (!stopped(flags) && in)) xs[i] = cheb_from_zero(ri, di, s, c);
 }
 
 // The same on meshes of few tiles (fine_spans), joined with the update of the CG iteration before it: x and r, the
@@ -359,17 +366,16 @@ __global__ __launch_bounds__(QUARTER) void k_amg_step_pre1(SellView K, Tiles T, 
   double acc = 0.0;
 #pragma unroll
   for (int s = 0; s < W; ++s)
-    if (s < n0) acc += a[s] * (residual(rj[s], qj[s]) / dj[s] * c.inv_theta);
+    if (s < n0) acc = __builtin_fma(a[s], cheb_d0(residual(rj[s], qj[s]), dj[s], c), acc);
   for (int s = W; s < R.width; ++s) {
     const int at = R.base + s * SLICE, j = slot_col_of<OFF16>(K, i, at);
-    acc += K.val[at] * (residual(st.r[j], st.q[j]) / K.diag[j] * c.inv_theta);
+    acc = __builtin_fma(K.val[at], cheb_d0(residual(st.r[j], st.q[j]), K.diag[j], c), acc);
   }
   double v[1] = {0.0};
   if (i0 < ti.hi) {
-    const double rh0 = ri / di, d0 = rh0 * c.inv_theta, rh1 = rh0 - (di * d0 + acc) / di;
     if (!done) st.x[i] = __builtin_fma(alpha, pi, xi);
     st.r_new[i] = ri;
-    xs[i] = d0 + (c.c_d * d0 + c.c_r * rh1);
+    xs[i] = cheb_from_zero(ri, di, acc, c);
     v[0] = ri * ri;
   }
   put_partial<1, QUARTER, true>(v, rr, T.ntile, ti);

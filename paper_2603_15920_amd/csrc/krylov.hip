@@ -800,17 +800,21 @@ SolveResult pcg(difvm_mesh* m, SellMatrix A, const double* b, double* x, double 
   // launches inside a captured step are never timed, so a step captured meanwhile is the one that replays keep
   const Profiler& prof = ctx_of(m).prof;
   const bool timed = prof.on && !ctx_of(m).capturing;
-  if ((amg ? amg_pcg_in_block(amg) : seg_tiles <= SEG_TILES) && !timed) {
-    // one block per segment makes the whole solve (while the kernels of an iteration are being timed, it
-    // is made by them: the same results)
+  if (amg ? amg_pcg_in_block(amg) : seg_tiles <= SEG_TILES && !timed) {
+    // one block per segment makes the whole solve (with Jacobi, while the kernels of an iteration are being timed,
+    // it is made by them: the same bits)
     const int budget = qo ? std::min(qo->budget, maxit) : maxit;
     const size_t bytes = pcg_state_bytes(m);
     PcgCtl* ctls = qo ? static_cast<PcgCtl*>(qo->state_out) : w->pcg;
     int made = 0;
     do {
       const int chunk = std::min(SEG_CHUNK, budget - made);
-      if (amg) amg_pcg_block(amg, A, b, x, w->r, w->p, tol, maxit, chunk, made == 0, ctls);
-      else launch_pcg_segment(m, seg_tiles, V, T, b, x, w, tol, maxit, chunk, made == 0, ctls);
+      if (amg) {
+        ProfScope ps(m, "pcg_amg_block");
+        amg_pcg_block(amg, A, b, x, w->r, w->p, tol, maxit, chunk, made == 0, ctls);
+      } else {
+        launch_pcg_segment(m, seg_tiles, V, T, b, x, w, tol, maxit, chunk, made == 0, ctls);
+      }
       made += chunk;
       if (qo) continue;
       post_poll(m, w, w->pcg, bytes, 0);
@@ -856,7 +860,7 @@ SolveResult pcg(difvm_mesh* m, SellMatrix A, const double* b, double* x, double 
   DIFVM_HIP(hipGetLastError());
   precondition(0);
   // on meshes of few tiles the update is made by the cycle's first kernel (while kernels are being timed by
-  // name, by its own: the same results)
+  // name, by its own: the same bits)
   const bool joint = amg && fine && !timed;
   auto update = [&](int kk) {
     if (joint) {
