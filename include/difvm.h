@@ -319,7 +319,8 @@ difvm_status difvm_mesh_get_launch(const difvm_mesh* mesh, int32_t knob, int32_t
  * stream, scratch inputs allocated and freed here, one warm-up and repeated launches) and keeps the
  * fastest.  The PCG grid's candidates are one block per tile, 1024, 512 and 256 blocks, and the
  * grids that give every block at most 2 or 4 of the tiles its XCD owns.  cache_path (may be NULL) names a JSON file of choices keyed by GPU architecture, knob and
- * mesh size bucket (floor(log2(cells)), and whether the mesh has one or several segments): knobs
+ * mesh size bucket (floor(log2(cells)), and whether the mesh has one or several segments; the PCG grid of a
+ * mesh of at most 384 tiles, where it has no effect, has an entry of its own, 0): knobs
  * found there are applied without timing, the others are timed and the file is rewritten with them
  * added.  n_timed (may be NULL) receives the number of knobs timed.  Synchronises.  Errors:
  * DIFVM_ERR_INVALID_ARG for an unreadable or unwritable cache file. */

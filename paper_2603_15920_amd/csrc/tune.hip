@@ -12,6 +12,7 @@
 
 #include "abi_util.h"
 #include "device.h"
+#include "krylov_util.h"
 #include "ops.h"
 
 namespace difvm {
@@ -151,7 +152,10 @@ int tune(difvm_mesh* m, const char* cache_path) {
     Scratch S64(ctx_of(m)), S32(ctx_of(m));
     bool made64 = false, made32 = false;
     for (int k = 0; k < DIFVM_TUNE_COUNT; ++k) {
-      std::string key = prefix + KNOB_NAME[k] + suffix;
+      // on meshes of few tiles the PCG product takes a block per quarter of a tile whatever its grid: every candidate
+      // would time the same, and what won by noise must not reach the larger meshes of the bucket
+      const bool no_grid = !op_knob(k) && fine_spans(m);
+      std::string key = prefix + KNOB_NAME[k] + suffix + (no_grid ? "|quarter" : "");
       auto it = cache.find(key);
       if (it != cache.end()) {
         check_launch(k, it->second);
@@ -180,7 +184,7 @@ int tune(difvm_mesh* m, const char* cache_path) {
           if (std::find(grids.begin(), grids.end(), g) == grids.end()) grids.push_back(g);
         }
         for (int v : grids) {
-          if (v && v >= d.ntile) continue;
+          if (v && (no_grid || v >= d.ntile)) continue;
           double t = time_pcg_spmv(m, v, 10, e0, e1);
           if (t < best) { best = t; best_v = v; }
         }
