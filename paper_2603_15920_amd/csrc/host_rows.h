@@ -3,7 +3,6 @@
 
 #include <algorithm>
 #include <exception>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -11,8 +10,9 @@ namespace difvm {
 
 // f(chunk, first, last) over consecutive chunks of n rows, at least per_thread rows each, on at most eight
 // threads (the caller's among them).  Rows are independent, so what a row computes does not depend on
-// the chunks.  The first exception of any chunk is rethrown here; where no thread can be started its chunk
-// runs on the caller's.
+// the chunks.  The first exception of any chunk is rethrown here; where no thread can be started (the system refuses
+// it, or the memory for its state) its chunk runs on the caller's: nothing may leave this function while
+// threads run.
 constexpr int MAX_CHUNKS = 8;
 inline int n_chunks(int n, int per_thread) {
   int hw = (int)std::thread::hardware_concurrency();
@@ -31,15 +31,16 @@ void parallel_rows(int n, int per_thread, F&& f) {
   };
   std::vector<std::thread> th;
   th.reserve(T);
-  std::vector<int> here = {0};
+  int here[MAX_CHUNKS], n_here = 0;
+  here[n_here++] = 0;
   for (int t = 1; t < T; ++t) {
     try {
       th.emplace_back(run, t);
-    } catch (const std::system_error&) {
-      here.push_back(t);
+    } catch (...) {
+      here[n_here++] = t;
     }
   }
-  for (int t : here) run(t);
+  for (int k = 0; k < n_here; ++k) run(here[k]);
   for (auto& x : th) x.join();
   for (int t = 0; t < T; ++t)
     if (err[t]) std::rethrow_exception(err[t]);
