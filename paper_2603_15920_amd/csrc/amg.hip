@@ -88,6 +88,12 @@ T* up(AmgDev* a, const std::vector<T>& v, hipStream_t s) {
   upload(p, v, s);
   return p;
 }
+// Waits for the stream when it goes out of scope: declared after host arrays that uploads read, so that an exception
+// (a failed allocation) does not free them under a copy.
+struct Drain {
+  hipStream_t s;
+  ~Drain() { (void)hipStreamSynchronize(s); }
+};
 double* work(AmgDev* a, size_t n) {
   double* p = dalloc<double>(ctx_of(a->mesh), n);
   a->allocs.push_back(p);
@@ -1167,6 +1173,7 @@ static AmgBlock amg_block(AmgDev* a, const AmgHierarchy& H, hipStream_t s) {
   };
   std::vector<int32_t> lrow, lptr = {0}, lcol;
   std::vector<double> lval;
+  const Drain drain{s};
   for (int i = 0; i < n; ++i) {
     const int q4 = std::min(P.ptr[i + 1], P.ptr[i] + 4);
     for (int q = P.ptr[i]; q < q4; ++q) put(pcol[i], pval[i], pval[ROWS + i], q - P.ptr[i], P.col[q], P.val[q]);
@@ -1207,7 +1214,6 @@ static AmgBlock amg_block(AmgDev* a, const AmgHierarchy& H, hipStream_t s) {
   k_amg_pad<<<n2, BLOCK, 0, s>>>(n2, B.ld, a->cinv, inv);
   DIFVM_HIP(hipGetLastError());
   B.inv = reinterpret_cast<double2*>(inv);
-  DIFVM_HIP(hipStreamSynchronize(s));  // the host arrays end here
   B.c = cheb_coefficients(0.1 * a->hi[0], a->hi[0]);
   B.n2 = n2;
   return B;
@@ -1318,7 +1324,8 @@ AmgDev* amg_create(difvm_mesh* m, SellMatrix K, const AmgOptions& opt) {
     a->cinv = up(a, H.coarsest_dense, s);
     dense_inverse_spd(ctx_of(m), H.n_coarsest, a->cinv, s);
     if (L_ == 1) a->block = amg_block(a, H, s);
-    AmgFused F;  // kept until the synchronisation below
+    AmgFused F;
+    const Drain drain{s};
     if (L_ >= 2) {
       const bool two = L_ == 2 && fine_spans(m) && (size_t)a->rows[1] * a->rows[2] <= FUSE_MAX_DENSE;
       F = amg_fuse(H, two);
