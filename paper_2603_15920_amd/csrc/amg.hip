@@ -1101,9 +1101,10 @@ __global__ void k_zero_int(int* p) {
 // M <- M^-1 for the dense SPD coarsest matrix (device, n x n); throws when a pivot is not positive
 void dense_inverse_spd(const Ctx& c, int n, double* M, hipStream_t s) {
   double* rc = dalloc<double>(c, 2 * (size_t)n);
-  int* bad = dalloc<int>(c, 1);
+  int* bad = nullptr;
   int hbad = 0;
   try {
+    bad = dalloc<int>(c, 1);
     k_zero_int<<<1, 64, 0, s>>>(bad);
     const int ge = (int)(((size_t)n * n + BLOCK - 1) / BLOCK);
     for (int k = 0; k < n; ++k) {

@@ -62,3 +62,10 @@ def failing_setups(name, after_failure):
 @pytest.mark.parametrize("name", MESHES)
 def test_setup_fails_and_works_again(name):
     failing_setups(name, lambda n, left: None)
+
+
+@pytest.mark.parametrize("name", MESHES)
+def test_failed_setup_gives_everything_back(name):
+    left = {}
+    failing_setups(name, left.__setitem__)
+    assert not any(left.values()), left
