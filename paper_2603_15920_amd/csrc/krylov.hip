@@ -470,7 +470,9 @@ __global__ __launch_bounds__(FINE ? QUARTER : BLOCK) void k_pcg_update(
 // to eight tiles and 16 at eleven against 7.1, so those segments take the two kernels.
 // A launch makes at most `chunk` iterations; what a further launch needs is stored when it ends unconverged.
 // ---------------------------------------------------------------------------------------------
-constexpr int SEG_CHUNK = 2048;  // most iterations per launch: a launch stays under some 12 ms
+// most iterations per launch, which so stays under some 16 ms (7.4 us per iteration at 4,096 hexes), and of
+// k_amg_pcg_block under 5 (17 us)
+constexpr int SEG_CHUNK = 2048, AMG_CHUNK = 256;
 
 // NT threads with C cells each; W: slots of every row, kept in registers (0: rows of any length, read in every
 // iteration)
@@ -808,7 +810,7 @@ SolveResult pcg(difvm_mesh* m, SellMatrix A, const double* b, double* x, double 
     PcgCtl* ctls = qo ? static_cast<PcgCtl*>(qo->state_out) : w->pcg;
     int made = 0;
     do {
-      const int chunk = std::min(SEG_CHUNK, budget - made);
+      const int chunk = std::min(amg ? AMG_CHUNK : SEG_CHUNK, budget - made);
       if (amg) {
         ProfScope ps(m, "pcg_amg_block");
         amg_pcg_block(amg, A, b, x, w->r, w->p, tol, maxit, chunk, made == 0, ctls);
