@@ -54,3 +54,36 @@ def test_amg_block_directions_stay_conjugate_over_launches(name):
         note("cosines at", cap, conj, orth)
         assert abs(conj) <= 1e-4 and abs(orth) <= 1e-4
     B.difvm_amg_destroy(amg)
+
+
+@pytest.mark.parametrize("layers", [170, 340, 510, 680])
+@pytest.mark.parametrize("ncomp", [1, 3])
+def test_bicgstab_block_over_launches(layers, ncomp):
+    """Flat tets (one to four tiles), a zero tolerance: no component stops before its cap.  The solve in one block per
+    component against the kernels of an iteration, which the mesh takes beside a member of six tiles (long stopped, at
+    a residual of 1e-161): the same bits of iterate and residual at the seam and after it."""
+    m = mg.kuhn_cube(1, jitter=0.1, patches="walls", nxyz=(1, 1, layers), seed=5)
+    both, starts = mg.pack([m, mg.kuhn_cube(10, patches="walls")])
+    rng = np.random.default_rng(8)
+    rhs = rng.standard_normal((both.n_cells, 3))[:, :ncomp]
+    runs = {}
+    for key, mesh, seg, b in (("block", m, None, rhs[:m.n_cells]), ("kernels", both, starts, rhs)):
+        M = B.Mesh(ctx(), mesh, seg_cell_start=seg)
+        A = B.ldu(empty(mesh.n_cells), empty(mesh.n_internal_faces), empty(mesh.n_internal_faces))
+        zero = dev(np.zeros((mesh.n_cells, 3)))
+        B.difvm_ldu_assemble_momentum(M.h, 1.0, 1e3, dev(np.zeros(mesh.n_faces)), zero,
+                                      dev(np.zeros((mesh.n_boundary_faces, 3))), A, empty((mesh.n_cells, 3)))
+        b = M.to_internal(dev(b if ncomp == 3 else b[:, 0]), B.KIND_CELL)
+        for cap in (2047, 2048, 2049, 2060):
+            x = b.clone().zero_()
+            note("bicgstab", key, layers, ncomp, cap)
+            st, it, res = B.difvm_solve_bicgstab(M.h, A, ncomp, b, x, 0.0, cap)
+            runs[key, cap] = host(M.to_user(x, B.KIND_CELL))[:m.n_cells], np.array(res[:ncomp])
+            assert list(it[:ncomp]) == [cap] * ncomp
+            if key == "block":
+                assert st == B.WARN_NOT_CONVERGED
+    for cap in (2047, 2048, 2049, 2060):
+        for one, other in zip(runs["block", cap], runs["kernels", cap]):
+            assert np.isfinite(one).all()
+            np.testing.assert_array_equal(one, other)
+    assert (runs["block", 2049][1] != runs["block", 2048][1]).all()
