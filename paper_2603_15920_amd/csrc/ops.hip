@@ -27,12 +27,12 @@ namespace difvm {
 // user order at 1,053,696 cells in FP64, against one thread per row with scattered stores: 9 values per
 // row 180 to 34.6 us (4.4 TB/s), 3 values 40 to 17.3 us.
 constexpr int PERM_ROWS = BLOCK;
-template <class T, int NC>  // NC = 0: ncomp values per row, known at run time
+// The values per row are a constant of the kernel: divided by at run time, rows of 4 and 6 FP32 values took 2.96 and
+// 3.40 us at 3,072 cells, longer than one thread per row (2.64, 2.92); now 2.56 and 2.88.
+template <class T, int NC>
 __global__ __launch_bounds__(BLOCK) void k_permute(int n1, int n, const int32_t* __restrict__ m1,
                                                    const int32_t* __restrict__ m2, const uint8_t* __restrict__ flip,
-                                                   int flip_src, int ncomp, const T* __restrict__ src,
-                                                   T* __restrict__ dst) {
-  const int nc = NC ? NC : ncomp;
+                                                   int flip_src, const T* __restrict__ src, T* __restrict__ dst) {
   const int base = xcd_tile(blockIdx.x, gridDim.x) * PERM_ROWS, i = base + (int)threadIdx.x;
   int old = 0;
   T sg = T(1);
@@ -48,20 +48,17 @@ __global__ __launch_bounds__(BLOCK) void k_permute(int n1, int n, const int32_t*
     row_of[threadIdx.x] = old;
     sign_of[threadIdx.x] = sg;
     __syncthreads();
-    const int cnt = min(PERM_ROWS, n - base) * nc;
-    dst += (size_t)base * nc;
-    constexpr int UN = NC ? NC : 1;  // a block's values: NC per thread
-    for (int q0 = threadIdx.x; q0 < cnt; q0 += UN * BLOCK) {
-      T v[UN];
+    const int cnt = min(PERM_ROWS, n - base) * NC, q0 = threadIdx.x;  // a block's values: NC per thread
+    dst += (size_t)base * NC;
+    T v[NC];
 #pragma unroll
-      for (int u = 0; u < UN; ++u) {
-        const int q = min(q0 + u * BLOCK, cnt - 1), r = q / nc;
-        v[u] = sign_of[r] * src[(size_t)row_of[r] * nc + (q - r * nc)];
-      }
-#pragma unroll
-      for (int u = 0; u < UN; ++u)
-        if (q0 + u * BLOCK < cnt) dst[q0 + u * BLOCK] = v[u];
+    for (int u = 0; u < NC; ++u) {
+      const int q = min(q0 + u * BLOCK, cnt - 1), r = q / NC;
+      v[u] = sign_of[r] * src[(size_t)row_of[r] * NC + (q - r * NC)];
     }
+#pragma unroll
+    for (int u = 0; u < NC; ++u)
+      if (q0 + u * BLOCK < cnt) dst[q0 + u * BLOCK] = v[u];
   }
 }
 
@@ -103,10 +100,21 @@ void permute_t(const difvm_mesh* m, int ncomp, int kind, int dir, const T* src, 
   if (!n) return;
   const int G = grid_for(n, PERM_ROWS);
   hipStream_t s = stream_of(m);
-  if (ncomp == 1) k_permute<T, 1><<<G, BLOCK, 0, s>>>(n1, n, m1, m2, flip, !to, 1, src, dst);
-  else if (ncomp == 3) k_permute<T, 3><<<G, BLOCK, 0, s>>>(n1, n, m1, m2, flip, !to, 3, src, dst);
-  else if (ncomp == 9) k_permute<T, 9><<<G, BLOCK, 0, s>>>(n1, n, m1, m2, flip, !to, 9, src, dst);
-  else k_permute<T, 0><<<G, BLOCK, 0, s>>>(n1, n, m1, m2, flip, !to, ncomp, src, dst);
+  switch (ncomp) {
+#define DIFVM_PERMUTE(NC) \
+  case NC: k_permute<T, NC><<<G, BLOCK, 0, s>>>(n1, n, m1, m2, flip, !to, src, dst); break
+    DIFVM_PERMUTE(1);
+    DIFVM_PERMUTE(2);
+    DIFVM_PERMUTE(3);
+    DIFVM_PERMUTE(4);
+    DIFVM_PERMUTE(5);
+    DIFVM_PERMUTE(6);
+    DIFVM_PERMUTE(7);
+    DIFVM_PERMUTE(8);
+    DIFVM_PERMUTE(9);
+#undef DIFVM_PERMUTE
+    default: throw Error{DIFVM_ERR_INVALID_ARG, "ncomp must be in 1..9"};
+  }
   DIFVM_HIP(hipGetLastError());
 }
 
