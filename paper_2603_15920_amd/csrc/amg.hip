@@ -772,7 +772,7 @@ __global__ __launch_bounds__(BLOCK) void k_amg_prolong(int n, const int32_t* __r
 // most BLOCK_COARSE coarse rows), the whole solve in one block and launch, as k_pcg_segment does for Jacobi-CG: K's
 // rows, the diagonal, r and p in registers (thread tid holds cells tid + c BLOCK_NT), x in LDS, the vector that a
 // product gathers in LDS too, in two arrays by turns so that one barrier parts two passes.  An iteration is
-// twelve barriers and three reductions instead of eight kernels.  What does not fit is read from L2 in every cycle,
+// thirteen barriers (one more where P has rows of more than four entries) and three reductions instead of eight kernels.  What does not fit is read from L2 in every cycle,
 // R and the coarse inverse (with more than four cells per thread P too): one compute unit gets 55 bytes a cycle
 // by loads of 16 bytes per lane (30 by loads of 8) and 600 ns pass between a load and its use, so all of
 // it is laid out again for whole 1 KB loads (AmgBlock) and taken several loads at a time.  The inverse grows with
@@ -1417,9 +1417,9 @@ static void launch_vcycle(const AmgDev* a, hipStream_t s, SellMatrix Km, const d
   for (int l = 0; l < L; ++l) c[l] = cheb_coefficients(0.1 * a->hi[l], a->hi[l]);
   const Tiles T = tiles_of(m);
   const int G = grid_for(nc);
-  // xs and t of the finest level live in z, d0 in res, and res in a vector that the caller has free: at a million cells
-  // what an iteration touches, 250 MB, just fits the 256 MB cache (1,053,696 cells: 141 us per iteration with five
-  // vectors for these, 129 with two; up to 900,000 no difference)
+  // xs and t of the finest level live in z, d0 in res, and res in a vector that the caller has free (q): at 1,053,696
+  // cells an iteration touches the matrix and the hierarchy, 183 MB, and six vectors of 8.4 instead of ten, 233 MB
+  // instead of 267, which fits the 256 MB cache (141 to 129 us per iteration; up to 900,000 cells no difference)
   // down
   const CycleTest none{};
   if (step)

@@ -461,11 +461,14 @@ __global__ __launch_bounds__(FINE ? QUARTER : BLOCK) void k_pcg_update(
 // ---------------------------------------------------------------------------------------------
 // Jacobi-PCG of small segments, one block per segment and the whole solve in one launch: the direction
 // vector in LDS, x, r, z (q in z's place) and the diagonal in registers (thread tid holds cells
-// tid + c NT), uniform rows of three or four slots too.  An iteration is three block barriers and two
+// tid + c NT), uniform rows of three or four slots too.  An iteration is four block barriers and two
 // reductions instead of two kernels; its time is their latency, which few waves keep short (every wave
-// repeats the scalar work), so a block holds no more cells than the largest segment's tiles.  Per iteration, two
-// kernels -> this: 968 prisms 6.8 -> 1.35 us, 2,048 6.9 -> 1.8, 3,872 6.9 -> 2.7, 3,072 tets 7.2 -> 2.6, 1,728 hexes (rows
-// read from L2 each time) 8.0 -> 5.3.  Above
+// repeats the scalar work), so with rows in registers a block holds no more cells than the largest segment's tiles.
+// Per iteration, two kernels -> this: 968 prisms 6.8 -> 1.35 us, 2,048 6.9 -> 1.8, 3,872 6.9 -> 2.7, 3,072 tets 7.2 -> 2.6.
+// Other rows (hexahedra, mixed cells) are read from L2 in every iteration, always by 512 threads, and its time grows
+// with the cells: 512 hexes 6.7 -> 3.3, 1,000 7.3 -> 3.9, 1,728 7.5 -> 4.9, 2,744 7.6 -> 6.1, 4,096 7.6 -> 7.4, which is why
+// they too stop at four tiles.  In packs: 64 x 4,096 hexes 11.2 -> 7.5, 256 x 1,728 19.5 -> 6.5, 1,024 x 64
+// 12.4 -> 10.6.  (Blocks as large as the tiles would take 3.5 us at 1,000 hexes and 5.7 at 2,744, but 5.4 at 1,728.)  Above
 // four tiles the rows do not fit one compute unit's registers; read from L2 they took 8 to 9 us at five
 // to eight tiles and 16 at eleven against 7.1, so those segments take the two kernels.
 // A launch makes at most `chunk` iterations; what a further launch needs is stored when it ends unconverged.
@@ -1374,7 +1377,7 @@ __global__ __launch_bounds__(FINE ? QUARTER : TILE, FINE ? 1 : 8) void k_bi_x(Se
 // ---------------------------------------------------------------------------------------------
 // BiCGStab of small segments with uniform rows of three or four slots, one block per segment and component and
 // the whole solve in one launch (as k_pcg_segment): the gathered vector (p, then s) and x in LDS, the rest and
-// the scaled rows in registers.  Same sums in the same order as the kernels above, so the same bits.  Five
+// the scaled rows in registers.  Same sums in the same order as the kernels above, so the same bits.  Six
 // barriers and three reductions an iteration instead of five kernels.  Ten PISO steps replayed from a graph (each with
 // one solve of three components, some five iterations, and with the launches that make and copy the solvers' states
 // gone): 968 / 1,922 / 2,178 / 4,050 prisms 2.95 / 3.61 / 4.58 / 6.92 -> 2.05 / 2.78 / 3.36 / 6.19 ms.
