@@ -15,25 +15,30 @@
 
 namespace difvm {
 
+__device__ __forceinline__ double dc_dot(const double* g, double x, double y, double z) {
+  return __builtin_fma(g[2], z, __builtin_fma(g[0], x, g[1] * y));
+}
+
 // phi^HO - phi^U of one component.  self_up: self is the upwind cell; ws: interpolation weight of
-// self; ps/po: values; gs/go: gradients (3 entries); rs/ro: x_f - x_self and x_f - x_other.
+// self; ps/po: values; gs/go: gradients (3 entries); rs/ro: x_f - x_self and x_f - x_other.  Fused where written: left
+// to the compiler, what is fused differs from slot to slot of a row whose slots are taken several at a time.
 template <int CONV>
 __device__ __forceinline__ double dc_delta(bool self_up, double ws, double ps, double po, const double* gs,
                                            const double* go, const double4& rs, const double4& ro) {
   double pC = self_up ? ps : po;
   if constexpr (CONV == DIFVM_CONV_LINEAR) {
-    return (ws * ps + (1.0 - ws) * po) - pC;
+    return __builtin_fma(ws, ps, (1.0 - ws) * po) - pC;
   } else {
     const double* gC = self_up ? gs : go;
     const double4& rC = self_up ? rs : ro;
     if constexpr (CONV == DIFVM_CONV_SOU) {
-      return gC[0] * rC.x + gC[1] * rC.y + gC[2] * rC.z;
+      return dc_dot(gC, rC.x, rC.y, rC.z);
     } else {
       static_assert(CONV == DIFVM_CONV_QUICK, "unknown convection scheme");
       const double4& rD = self_up ? ro : rs;
       double pD = self_up ? po : ps;
-      double gd = gC[0] * (rC.x - rD.x) + gC[1] * (rC.y - rD.y) + gC[2] * (rC.z - rD.z);  // g_C . (x_D - x_C)
-      return 0.25 * (pD - pC) + 0.25 * gd;
+      double gd = dc_dot(gC, rC.x - rD.x, rC.y - rD.y, rC.z - rD.z);  // g_C . (x_D - x_C)
+      return __builtin_fma(0.25, gd, 0.25 * (pD - pC));
     }
   }
 }

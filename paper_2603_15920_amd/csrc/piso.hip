@@ -233,8 +233,8 @@ __global__ __launch_bounds__(BLOCK) void k_dc(MeshView<double> m, const double* 
         double sF = nb ? F[k] : -F[k];
 #pragma unroll
         for (int c = 0; c < NC; ++c)
-          acc[c] += sF * dc_delta<CONV>(dc_self_up(F[k], nb), wself, pi[c], pj[k][c], gC[k] + 3 * c, gC[k] + 3 * c,
-                                        rs[k], ro[k]);
+          acc[c] = __builtin_fma(sF, dc_delta<CONV>(dc_self_up(F[k], nb), wself, pi[c], pj[k][c], gC[k] + 3 * c,
+                                                    gC[k] + 3 * c, rs[k], ro[k]), acc[c]);
       }
     });
   }
