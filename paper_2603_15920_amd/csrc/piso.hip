@@ -225,6 +225,19 @@ __global__ __launch_bounds__(BLOCK) void k_dc(MeshView<double> m, const double* 
 #pragma unroll
         for (int e = 0; e < 3 * NC; ++e) gC[k][e] = LIN ? 0.0 : g[3 * NC * (size_t)up + e];
       }
+      // SOU: formed for all slots before the first branch (each behind its own 79 us instead of 76, caches warm; QUICK's the
+      // other way round 144 instead of 138)
+      double dl[SOU ? N : 1][NC];
+      if constexpr (SOU) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+          bool nb = sf[k] < 0;
+          double wself = nb ? 1.0 - wf[k] : wf[k];
+#pragma unroll
+          for (int c = 0; c < NC; ++c)
+            dl[k][c] = dc_delta<CONV>(dc_self_up(F[k], nb), wself, pi[c], pj[k][c], gC[k] + 3 * c, gC[k] + 3 * c, rs[k], ro[k]);
+        }
+      }
 #pragma unroll
       for (int k = 0; k < N; ++k) {
         if (!slot_internal(sf[k], m.nfi)) continue;
@@ -232,9 +245,12 @@ __global__ __launch_bounds__(BLOCK) void k_dc(MeshView<double> m, const double* 
         double wself = nb ? 1.0 - wf[k] : wf[k];
         double sF = nb ? F[k] : -F[k];
 #pragma unroll
-        for (int c = 0; c < NC; ++c)
-          acc[c] = __builtin_fma(sF, dc_delta<CONV>(dc_self_up(F[k], nb), wself, pi[c], pj[k][c], gC[k] + 3 * c,
-                                                    gC[k] + 3 * c, rs[k], ro[k]), acc[c]);
+        for (int c = 0; c < NC; ++c) {
+          double d;
+          if constexpr (SOU) d = dl[k][c];
+          else d = dc_delta<CONV>(dc_self_up(F[k], nb), wself, pi[c], pj[k][c], gC[k] + 3 * c, gC[k] + 3 * c, rs[k], ro[k]);
+          acc[c] = __builtin_fma(sF, d, acc[c]);
+        }
       }
     });
   }
